@@ -366,8 +366,8 @@ fq_status fq_gemm(fq_op op, const fq_qtensor *A, const fq_qtensor *B, void *C,
  * every 4 items of the k-loop.  The FP32 additions therefore round at the magnitude of the biased
  * partial sums: the result differs from fq_gemm's by up to about 2e-4 of max |C| (measured; the
  * bound does not grow with K), inside the 1e-3 this library's outputs are held to, but it is not
- * the oracle's result bit for bit.  fq_gemm stays the reference path.  Arguments and errors as
- * fq_gemm.
+ * the oracle's result bit for bit.  (Outputs that fq_gemm computes on smaller tiles are computed by
+ * the same exact kernels here.)  fq_gemm stays the reference path.  Arguments and errors as fq_gemm.
  */
 fq_status fq_gemm_biased(fq_op op, const fq_qtensor *A, const fq_qtensor *B, void *C,
                          fq_out_dtype cdt, int64_t ldc, void *hip_stream);
@@ -394,6 +394,8 @@ fq_status fq_gemm_plain(fq_op op, const fq_qtensor *A, const fq_qtensor *B, void
  * current device's count, or the value of the environment variable FQ_GEMM_CUS if that is set
  * to a positive number (fq_gemm reads the same variable; meant for tuning and tests).  The
  * plan never changes results: every output element is accumulated in Alg. 1's order.
+ * Outputs of less than about a chip's worth of these tiles are computed on smaller tiles instead
+ * (32 x 32, 128 x 64 or 128 x 128, chosen by fq_gemm from the shape), with the same results.
  */
 fq_status fq_gemm_tile_plan(int32_t rows_out, int32_t cols_out, int32_t compute_units,
                             int32_t plan[3]);

@@ -34,9 +34,11 @@
 //     part and leaves the dequantizing pipeline about 10 % faster.)
 // The accumulation order per output element is exactly Alg. 1's (k ascending,
 // main term then residual term) in both geometries, so results match a
-// sequential evaluation bit for bit and do not depend on the tile plan.
+// sequential evaluation bit for bit and do not depend on the tile plan.  Outputs too small for a
+// chip's worth of these tiles are computed by the kernels of fq_gemm_tile.hip, also bit for bit.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdlib>
 
 #include "fq_device.h"
@@ -887,6 +889,7 @@ struct TilePlan {
   int n_main;    // workgroups computing 2 x 2-block tiles
   int main_tj;   // tile columns they cover (block columns [0, 2*main_tj))
   int tail_tj;   // 1 x 3-block tile columns covering the remaining block columns
+  double cost;   // rounds of the chip, in units of one 2 x 2 tile per compute unit
 };
 
 // All of the output in 2 x 2-block tiles, unless their number leaves the last round of the
@@ -896,7 +899,8 @@ struct TilePlan {
 TilePlan plan_tiles(int nib, int njb, int cus) {
   const int tiles_i = (nib + 1) / 2, tiles_j = (njb + 1) / 2;
   const int total = tiles_i * tiles_j;
-  const TilePlan all{total, tiles_j, 0};
+  const double cost_all = cus > 0 ? (total + cus - 1) / cus : 1;
+  const TilePlan all{total, tiles_j, 0, cost_all};
   if (cus <= 0 || total <= cus || total % cus == 0) return all;
   const int rounds = total / cus;
   const int cm = std::min(tiles_j, rounds * cus / tiles_i);
@@ -904,10 +908,41 @@ TilePlan plan_tiles(int nib, int njb, int cus) {
   if (cm <= 0 || tail_cols <= 0) return all;
   const int tail_tj = (tail_cols + 2) / 3;
   const int n_tail = nib * tail_tj;
-  const double cost_all = (total + cus - 1) / cus;
   const double cost_split = (cm * tiles_i + cus - 1) / cus + 0.75 * ((n_tail + cus - 1) / cus);
-  if (cost_split + 0.05 < cost_all) return TilePlan{cm * tiles_i, cm, tail_tj};
+  if (cost_split + 0.05 < cost_all) return TilePlan{cm * tiles_i, cm, tail_tj, cost_split};
   return all;
+}
+
+// Tile of fq_gemm_tile.hip for this output, or kNone: the tiles above.  Estimated nanoseconds per
+// k-block (K = 128) of the busiest compute unit, from measurements over 256 <= M, N <= 4096 and
+// 512 <= K <= 11008 (33 rows too); the launch and the ends of the kernel cost all forms about the
+// same 3 us.  A form has a latency below which a k-block does not get however few tiles there are,
+// and a throughput:
+//   32 x 32     240, or 80 per tile and compute unit            (33 x 11008 x 4096; 512 x 4096 x 4096)
+//   128 x 64    520, or 390                                     (512 x 4096 x 4096; 3072^3)
+//   128 x 128   850 alone on its compute unit, 1360 a pair (two are resident)
+//   256 x 256   2400 (2250 on an idle chip), one is resident    (4096^3)
+// So 2048 x 4096 x 4096 takes 128 x 128 tiles (48 us against 52 with 128 x 64 and 76 with 256 x 256),
+// 3072^3 128 x 64 (46.5, 51 with 128 x 128, 61 with 256 x 256) and 4096^3 256 x 256 (81 us, 89 with
+// 128 x 128); 512 x 4096 x 4096 takes 128 x 64 (19.5 us, 23.5 with 32 x 32) and 256 x 11008 x 4096
+// 32 x 32 (28.7 us, 44 with 128 x 64).  64 x 64 tiles were never better than the nearer of their
+// neighbours by more than 3 %.
+SmallTile plan_small(int M, int N, const TilePlan& big, int cus) {
+  const double c = cus > 0 ? cus : 256;
+  auto tiles = [&](int r, int s) { return (double)((M + r - 1) / r) * ((N + s - 1) / s) / c; };
+  auto whole = [](double n) { return n <= 2.0 ? std::ceil(n) : n; };   // few tiles: the fullest unit counts
+  const double pairs = std::floor(tiles(128, 128) / 2.0), rest = tiles(128, 128) - 2.0 * pairs;
+  const double est[3] = {std::max(240.0, 80.0 * tiles(32, 32)), std::max(520.0, 390.0 * whole(tiles(128, 64))),
+                         1360.0 * pairs + (rest > 1.0 ? 1360.0 : rest > 0.0 ? 850.0 : 0.0)};
+  const SmallTile kind[3] = {SmallTile::k32x32, SmallTile::k128x64, SmallTile::k128x128};
+  double best = 2400.0 * big.cost;
+  SmallTile tile = SmallTile::kNone;
+  for (int i = 0; i < 3; ++i)
+    if (est[i] < best) {
+      best = est[i];
+      tile = kind[i];
+    }
+  return tile;
 }
 
 // Compute units the planner assumes: the device's, or the value of the environment variable
@@ -949,7 +984,10 @@ hipError_t launch_gemm(const GemmParams& p_in, bool debug, hipStream_t st) {
   }
   if (p_in.nib == 0 || p_in.njb == 0) return hipSuccess;
   GemmParams p = p_in;
-  const TilePlan plan = plan_tiles(p.nib, p.njb, planning_cus());
+  const int cus = planning_cus();
+  const TilePlan plan = plan_tiles(p.nib, p.njb, cus);
+  if (const SmallTile tile = plan_small(p.M, p.N, plan, cus); tile != SmallTile::kNone)
+    return launch_gemm_small(p, tile, st);
   p.n_main = plan.n_main;
   p.main_tj = plan.main_tj;
   p.tail_tj = plan.tail_tj;

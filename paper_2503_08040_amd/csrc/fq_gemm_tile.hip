@@ -1,0 +1,440 @@
+// Fallback block GEMM for outputs that 256 x 256 tiles do not fill the chip with (few tokens, small
+// layers, ragged batches): Alg. 1 of the paper on smaller tiles.
+//
+// Same operands, same accumulation order per output element (k ascending, main term then residual
+// term, binary32 FMAs) and therefore the same bits as gemm_kernel of fq_gemm.hip, which stays the
+// kernel for outputs of about a chip's worth of 256 x 256 tiles and more.  That kernel gives a
+// compute unit one 256 x 256 tile; an output of 64 such tiles leaves three quarters of the chip
+// idle, and one of 33 rows multiplies mostly padding.  Here the contraction is never split (the
+// order of the FP32 terms is part of the interface), so parallelism comes from the tile size alone:
+//   gemm_wave_kernel            one wavefront per 32 x 32 tile, both operands straight from global
+//                               memory into registers, no LDS, no barrier
+//   gemm_tile_kernel<2>   128 x 64 tiles, 4 wavefronts of 32 x 64
+//   gemm_tile_kernel<4>   128 x 128 tiles, 4 wavefronts of 32 x 128
+// A wavefront owns 32 whole rows, so its A operands go from global memory into registers and only
+// the B operands, which the wavefronts of a column share, pass through LDS.  What bounds them is the
+// 64 bytes a compute unit's vector cache delivers per cycle: a 32 x 32 x 128 step costs 8, 3 and 2 KiB
+// of operands in the three forms (1 KiB in gemm_kernel), and with the loads taken out of the loop
+// 4096^3 runs at 1773 and 2008 TOP/s on the first two instead of 486 and 1525; with a single wavefront on
+// a SIMD it is the issue of its own loads, matrix and vector instructions one after the other (500 to
+// 550 cycles per step).  Smaller tiles win while the chip is not full, larger ones from then on;
+// plan_small in fq_gemm.hip has the rule.
+// Measured (GEMM alone, bf16 output, 5 % of the blocks flagged, gemm_kernel -> the form chosen):
+// 33 x 4096 x 11008 70.6 -> 12.4 us, 256 x 11008 x 4096 182 -> 28.7 us, 777 x 1544 x 2200
+// 34.6 -> 10.9 us, 2048^3 42.5 -> 17.7 us, 2048 x 4096 x 4096 76 -> 48 us.
+//
+// The MFMA operands are swapped (D = B A^T): a lane then holds consecutive columns of one row of C
+// and stores them without a transposition through LDS.
+#include <type_traits>
+
+#include "fq_device.h"
+#include "fq_kernels.h"
+
+namespace fq {
+
+namespace {
+
+
+constexpr int kXcds = 8;          // accelerator complex dies, each with a private L2
+constexpr int kGroupN = 4;        // tile columns per rasterization group
+constexpr int kTileThreads = 256;
+constexpr int kFragRows = 4096;   // bytes of one 32-row group of a block (128 contraction positions)
+
+// Row (of the 32 in a group) that lane i of operand half ch = 0, 1 supplies.  The result registers
+// of lane group g = i / 4 are 4 consecutive operand rows; with this order the two halves give a lane
+// 8 consecutive columns of C, columns 8 g + 4 ch' ..., and both the first 8 and the 16 lanes of an
+// LDS read fall into distinct banks (ch' = ch or 1 - ch by g, which store_unit undoes).
+__device__ __forceinline__ int perm_col(int i, int ch) {
+  const int g = i >> 2;
+  const int sigma = (g ^ (g >> 1)) & 1;        // 0, 1, 1, 0
+  return 8 * g + 4 * (ch ^ sigma) + (i & 3);
+}
+
+// 16 columns x 16 rows x 64: lane l supplies operand row l % 16 and contraction bytes of group l / 16.
+__device__ __forceinline__ v4i mfma16(const v4i& b, const v4i& a, const v4i& c) {
+  return __builtin_amdgcn_mfma_i32_16x16x64_i8(b, a, c, 0, 0, 0);
+}
+
+// Writes a lane's 16 values of a 32 x 32 sub-tile: element 4 q + r, quadrant q = 2 ch + rh (column half
+// ch, row half rh).  bad: a flagged block of these rows found no residual slot, the rows become NaN.
+__device__ __forceinline__ void store_unit(const GemmParams& p, const float (&acc)[16], int row0, int col0,
+                                           int lane, bool bad) {
+  const int g = lane >> 4;
+  const bool swap = ((g ^ (g >> 1)) & 1) != 0;
+  const int col = col0 + 8 * g;
+#pragma unroll
+  for (int rh = 0; rh < 2; ++rh) {
+    const int row = row0 + 16 * rh + (lane & 15);
+    float v[8];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float x = acc[4 * rh + r], y = acc[8 + 4 * rh + r];   // quadrants (ch 0, rh), (ch 1, rh)
+      v[r] = bad ? __int_as_float(0x7FC00000) : (swap ? y : x);
+      v[4 + r] = bad ? __int_as_float(0x7FC00000) : (swap ? x : y);
+    }
+    if (row >= p.M || col >= p.N) continue;
+    if (p.out_bf16) {
+      uint16_t* dst = reinterpret_cast<uint16_t*>(p.c) + (int64_t)row * p.ldc + col;
+      if (p.vec_ok && col + 8 <= p.N) {
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        v4i o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          f32x2 t = {v[2 * i], v[2 * i + 1]};
+          o[i] = __builtin_bit_cast(int, __builtin_convertvector(t, bf16x2));
+        }
+        *reinterpret_cast<v4i*>(dst) = o;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (col + e < p.N) dst[e] = (uint16_t)float_to_bf16_bits(v[e]);
+      }
+    } else {
+      float* dst = reinterpret_cast<float*>(p.c) + (int64_t)row * p.ldc + col;
+      if (p.vec_ok && col + 8 <= p.N) {
+        reinterpret_cast<float4*>(dst)[0] = make_float4(v[0], v[1], v[2], v[3]);
+        reinterpret_cast<float4*>(dst)[1] = make_float4(v[4], v[5], v[6], v[7]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (col + e < p.N) dst[e] = v[e];
+      }
+    }
+  }
+}
+
+// Keeps a wave-uniform address in scalar registers: loads then take the scalar-base form, and no
+// vector register is written as an address while loads into its neighbours are in flight.
+typedef const __attribute__((address_space(1))) int8_t gbl_i8;
+typedef const __attribute__((address_space(1))) v4i gbl_v4i;
+__device__ __forceinline__ gbl_i8* scalar_ptr(const int8_t* q) {
+  gbl_i8* g = (gbl_i8*)q;
+  asm("" : "+s"(g));
+  return g;
+}
+// The per-lane part of such an address, opaque so that it stays a 32-bit offset at its use.
+__device__ __forceinline__ unsigned lane_offset(unsigned v) {
+  asm("" : "+v"(v));
+  return v;
+}
+__device__ __forceinline__ v4i load16(gbl_i8* base, unsigned off, int imm) {
+  return *(gbl_v4i*)(base + off + imm);
+}
+
+// Workgroup b of `total` -> its place in the tile order: workgroups are dealt to the XCDs round-robin,
+// so each XCD gets a contiguous run of tiles, whose B blocks then come through one L2.
+__device__ __forceinline__ int xcd_run(int b, int total) {
+  const int xcd = b % kXcds, l = b / kXcds;
+  const int q = total / kXcds, rem = total % kXcds;
+  return xcd * q + min(xcd, rem) + l;
+}
+
+}  // namespace
+
+// Scales and residual slots of 64 consecutive k-blocks, one per lane: the main and the residual scale
+// product and the slot of block (ib, k0 + lane).  Read back with v_readlane, they cost the k-loop no
+// scalar loads, whose unordered counter would wait for the youngest of them at every use.
+struct KLane { float s, t; int slot; };
+
+__device__ __forceinline__ KLane load_klane(const GemmParams& p, int ib, int jb, int k0, int lane) {
+  const int k = min(k0 + lane, p.nkb - 1);
+  KLane r;
+  r.slot = p.a_slot ? p.a_slot[ib * p.a_si + k * p.a_sk] : -1;
+  const float sb = p.b_scales[jb * p.b_sj + k * p.b_sk];
+  r.s = p.a_scales[ib * p.a_si + k * p.a_sk] * sb;
+  r.t = p.a_slot ? p.a_res_scales[max(r.slot, 0)] * sb : 0.0f;
+  return r;
+}
+__device__ __forceinline__ int lane_int(int v, int k) { return __builtin_amdgcn_readlane(v, k & 63); }
+__device__ __forceinline__ float lane_float(float v, int k) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k & 63));
+}
+
+// ---- one wavefront per 32 x 32 output tile, operands straight from global memory.  kD k-blocks are in
+// flight (32 registers each); the steps of a trip are straight-line code, so that the compiler's wait
+// for a k-block leaves the younger ones in flight.
+template <int kD>
+__global__ __launch_bounds__(64, 2) void gemm_wave_kernel(GemmParams p) {
+  const int lane = threadIdx.x;
+  const int nrg = (p.M + 31) >> 5;
+  const int L = xcd_run(blockIdx.x, gridDim.x);
+  const int cg = L / nrg, rg = L - cg * nrg;
+  const int ib = rg >> 2, jb = cg >> 2;
+  const int nkb = p.nkb;
+  const int kg = lane >> 4, l15 = lane & 15;
+  const int koff = (kg >> 1) * 1024 + (kg & 1) * 512;
+  const unsigned aoff = koff + l15 * 16;
+  const unsigned boff[2] = {(unsigned)(koff + perm_col(l15, 0) * 16), (unsigned)(koff + perm_col(l15, 1) * 16)};
+  const int8_t* const abase = p.a_codes + (int64_t)ib * nkb * kBlockBytes + (rg & 3) * kFragRows;
+  const int8_t* const rbase = p.a_res + (rg & 3) * kFragRows;
+  const int8_t* const bbase = p.b_codes + (int64_t)jb * nkb * kBlockBytes + (cg & 3) * kFragRows;
+
+  v4i A[kD][2][2], B[kD][2][2], R[2][2];
+  float acc[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+  bool bad = false;
+
+  auto load_main = [&](int k, v4i (&a)[2][2], v4i (&b)[2][2]) {
+    k = min(k, nkb - 1);
+    gbl_i8* as = scalar_ptr(abase + (int64_t)k * kBlockBytes);
+    gbl_i8* bs = scalar_ptr(bbase + (int64_t)k * kBlockBytes);
+    const unsigned ao = lane_offset(aoff), bo0 = lane_offset(boff[0]), bo1 = lane_offset(boff[1]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        b[i][ks] = load16(bs, i ? bo1 : bo0, ks * 2048);
+        a[i][ks] = load16(as, ao, i * 256 + ks * 2048);
+      }
+  };
+  auto load_res = [&](int slot) {
+    gbl_i8* as = scalar_ptr(rbase + (int64_t)slot * kBlockBytes);
+    const unsigned ao = lane_offset(aoff);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+        R[i][ks] = load16(as, ao, i * 256 + ks * 2048);
+  };
+  auto fold = [&](const v4i (&a)[2][2], const v4i (&b)[2][2], float s) {
+    v4i P[4];
+    const v4i z = {0, 0, 0, 0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) P[q] = mfma16(b[q >> 1][0], a[q & 1][0], z);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) P[q] = mfma16(b[q >> 1][1], a[q & 1][1], P[q]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[4 * q + r] = __builtin_fmaf((float)P[q][r], s, acc[4 * q + r]);
+  };
+
+  if (nkb > 0) {
+#pragma unroll
+    for (int d = 0; d < kD; ++d) load_main(d, A[d], B[d]);
+    for (int k0 = 0; k0 < nkb; k0 += 64) {
+      const KLane kl = load_klane(p, ib, jb, k0, lane);
+      bad |= __ballot(kl.slot == -2) != 0;
+      const int n = min(64, nkb - k0);
+      int slot = lane_int(kl.slot, 0);
+      if (slot >= 0) load_res(slot);
+      auto step = [&](int k, int d, bool reload) {
+        fold(A[d], B[d], lane_float(kl.s, k));
+        if (slot >= 0) fold(R, B[d], lane_float(kl.t, k));
+        if (reload) load_main(k0 + k + kD, A[d], B[d]);
+        slot = k + 1 < n ? lane_int(kl.slot, k + 1) : -1;
+        if (slot >= 0) load_res(slot);
+      };
+      int k = 0;
+      for (; k + kD <= n; k += kD) {
+#pragma unroll
+        for (int d = 0; d < kD; ++d) step(k + d, d, true);
+      }
+      // what is left is the end of the contraction (64 is a multiple of kD)
+#pragma unroll
+      for (int d = 0; d < kD - 1; ++d) {
+        if (k + d >= n) break;
+        step(k + d, d, false);
+      }
+    }
+  }
+  store_unit(p, acc, rg * 32, cg * 32, lane, bad);
+}
+
+// ---- one workgroup of four wavefronts per output tile of 128 rows x 32 kWU columns, every wavefront 32
+// rows x kWU column groups ("units"), kWU = 2 or 4
+
+// Empty volatile asm: pins the source order of pure instructions without emitting code.
+__device__ __forceinline__ void pin(v4i& x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void pin(float& a, float& b) { asm volatile("" : "+v"(a), "+v"(b)); }
+
+// One unit: the 32 x 32 sub-tile of one column group.  kPar: parity of the unit in the wavefront's
+// sequence of units.  Multiplies a with bq[kPar] into P[kPar], fetches the next unit's B operands
+// from b_next into bq[kPar ^ 1] and folds the finished tile P[kPar ^ 1] of the unit before it into
+// `acc` with the scale f of that unit: per slot one MFMA, the two FMAs of the elements converted in the
+// slot before, two converts.
+template <int kPar>
+__device__ __forceinline__ void tile_unit(v4i (&P)[2][4], v4i (&bq)[2][2][2], float (&acc)[16], const v4i (&a)[2][2],
+                                          const int8_t* b_next, const int (&boff)[2], float f) {
+  float T[2] = {0.0f, 0.0f};
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+    const int ks = n >> 2, q = n & 3, ch = q >> 1, rh = q & 1;
+    const v4i z = {0, 0, 0, 0};
+    P[kPar][q] = mfma16(bq[kPar][ch][ks], a[rh][ks], ks ? P[kPar][q] : z);
+    if (n < 4) {
+      const int ich = n >> 1, iks = n & 1;
+      bq[kPar ^ 1][ich][iks] = *reinterpret_cast<const v4i*>(b_next + boff[ich] + iks * 2048);
+    }
+    pin(P[kPar][q]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (n > 0) {
+      acc[2 * n - 2] = __builtin_fmaf(T[0], f, acc[2 * n - 2]);
+      acc[2 * n - 1] = __builtin_fmaf(T[1], f, acc[2 * n - 1]);
+      pin(acc[2 * n - 2], acc[2 * n - 1]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    T[0] = (float)P[kPar ^ 1][n >> 1][2 * (n & 1)];
+    T[1] = (float)P[kPar ^ 1][n >> 1][2 * (n & 1) + 1];
+    pin(T[0], T[1]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  acc[14] = __builtin_fmaf(T[0], f, acc[14]);
+  acc[15] = __builtin_fmaf(T[1], f, acc[15]);
+  pin(acc[14], acc[15]);
+}
+
+// Units [kFrom, kTo) of a wavefront with kWU units per k-block, every one with its
+// successor in the same B stage bs.  sp: scale of the unit folded by unit 0, s: by the others.
+template <int kWU, int kFrom, int kTo>
+__device__ __forceinline__ void tile_units(v4i (&P)[2][4], v4i (&bq)[2][2][2], float (&acc)[kWU][16],
+                                           const v4i (&a)[2][2], const int8_t* bs, const int (&boff)[2], float s,
+                                           float sp) {
+  if constexpr (kFrom < kTo) {
+    tile_unit<kFrom & 1>(P, bq, acc[(kFrom + kWU - 1) % kWU], a, bs + (kFrom + 1) % kWU * kFragRows, boff,
+                         kFrom ? s : sp);
+    tile_units<kWU, kFrom + 1, kTo>(P, bq, acc, a, bs, boff, s, sp);
+  }
+}
+
+// The B blocks of k-block k + 1 go from registers into the other LDS stage in front of the last unit of
+// k-block k, behind it the barrier, then the loads for k + 2; A operands are requested one k-block
+// ahead.  (Direct global-to-LDS loads were tried: with them in the loop the compiler waits for every
+// load at the first use of an A operand; deeper register rings measured the same.)
+template <int kWU>
+__global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(GemmParams p, int tiles_i, int tiles_j) {
+  constexpr int kStageBytes = kWU * kFragRows;
+  constexpr int kBL = kWU;                        // 1 KiB loads of a wavefront per B stage
+  __shared__ __attribute__((aligned(1024))) int8_t lds[2 * kStageBytes];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nkb = p.nkb;
+  int ti, tj;
+  {
+    const int L = xcd_run(blockIdx.x, gridDim.x);
+    const int group = kGroupN * tiles_i;
+    const int g0 = (L / group) * kGroupN;
+    const int gn = min(kGroupN, tiles_j - g0);
+    const int within = L - (L / group) * group;
+    tj = g0 + within % gn;
+    ti = within / gn;
+  }
+  const int cg0 = tj * kWU, ib = ti, jb = cg0 >> 2, rg = 4 * ti + w;
+  const int kg = lane >> 4, l15 = lane & 15;
+  const int koff = (kg >> 1) * 1024 + (kg & 1) * 512;
+  const unsigned aoff = koff + l15 * 16;
+  const int boff[2] = {koff + perm_col(l15, 0) * 16, koff + perm_col(l15, 1) * 16};
+  const int8_t* const abase = p.a_codes + (int64_t)ib * nkb * kBlockBytes + w * kFragRows;
+  const int8_t* const rbase = p.a_res + w * kFragRows;
+  const int8_t* const bbase = p.b_codes + (int64_t)jb * nkb * kBlockBytes + (cg0 & 3) * kFragRows + w * (kBL * 1024);
+
+  float acc[kWU][16];
+  v4i bq[2][2][2], P[2][4];
+#pragma unroll
+  for (int u = 0; u < kWU; ++u)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[u][e] = 0.0f;
+  bool bad = false;
+
+  auto load_a = [&](const int8_t* ptr, v4i (&a)[2][2]) {
+    gbl_i8* src = scalar_ptr(ptr);
+    const unsigned ao = lane_offset(aoff);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) a[i][ks] = load16(src, ao, i * 256 + ks * 2048);
+  };
+  // this wavefront's share of a B stage: registers, then LDS
+  auto load_b = [&](int k, v4i (&b)[kBL]) {
+    gbl_i8* src = scalar_ptr(bbase + (int64_t)min(k, nkb - 1) * kBlockBytes);
+    const unsigned bo = lane_offset((unsigned)lane * 16u);
+#pragma unroll
+    for (int i = 0; i < kBL; ++i) b[i] = load16(src, bo, i * 1024);
+  };
+  auto write_b = [&](int stage, const v4i (&b)[kBL]) {
+    int8_t* dst = lds + stage * kStageBytes + w * (kBL * 1024) + lane * 16;
+#pragma unroll
+    for (int i = 0; i < kBL; ++i) *reinterpret_cast<v4i*>(dst + i * 1024) = b[i];
+  };
+
+  if (nkb > 0) {
+    v4i A[2][2][2], R[2][2], bn[kBL];
+    load_b(0, bn);
+    load_a(abase, A[0]);
+    write_b(0, bn);
+    load_b(1, bn);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      bq[0][i >> 1][i & 1] = *reinterpret_cast<const v4i*>(lds + boff[i >> 1] + (i & 1) * 2048);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) P[1][q] = v4i{0, 0, 0, 0};
+    float sp = 0.0f;      // scale of the unit whose tile is still to be folded
+    for (int k0 = 0; k0 < nkb; k0 += 64) {
+      const KLane kl = load_klane(p, ib, jb, k0, lane);
+      bad |= __ballot(kl.slot == -2) != 0;
+      const int kend = min(k0 + 64, nkb);
+      // k-block k of parity j: its A operands are in A[j], its B blocks in LDS stage j
+      auto step = [&](int k, auto j_c) {
+        constexpr int j = decltype(j_c)::value;
+        v4i (&a)[2][2] = A[j];
+        const int slot = lane_int(kl.slot, k);
+        load_a(abase + (int64_t)min(k + 1, nkb - 1) * kBlockBytes, A[j ^ 1]);
+        if (slot >= 0) load_a(rbase + (int64_t)slot * kBlockBytes, R);
+        float s = lane_float(kl.s, k);
+        const float t = lane_float(kl.t, k);
+        const int8_t* const bs = lds + j * kStageBytes;
+        tile_units<kWU, 0, kWU - 1>(P, bq, acc, a, bs, boff, s, sp);
+        if (slot >= 0) {
+          // the residual product re-uses the B blocks on chip; its last unit is the common one below
+          tile_unit<1>(P, bq, acc[kWU - 2], a, bs, boff, s);
+          tile_units<kWU, 0, kWU - 1>(P, bq, acc, R, bs, boff, t, s);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) a[i >> 1][i & 1] = R[i >> 1][i & 1];
+          s = t;
+        }
+        write_b(j ^ 1, bn);
+        load_b(k + 2, bn);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        tile_unit<1>(P, bq, acc[kWU - 2], a, lds + (j ^ 1) * kStageBytes, boff, s);
+        sp = s;
+      };
+      int k = k0;
+      for (; k + 2 <= kend; k += 2) {
+        step(k, std::integral_constant<int, 0>{});
+        step(k + 1, std::integral_constant<int, 1>{});
+      }
+      if (k < kend) step(k, std::integral_constant<int, 0>{});
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e)     // the last unit
+      acc[kWU - 1][e] = __builtin_fmaf((float)P[1][e >> 2][e & 3], sp, acc[kWU - 1][e]);
+  }
+#pragma unroll
+  for (int u = 0; u < kWU; ++u)
+    store_unit(p, acc[u], rg * 32, (cg0 + u) * 32, lane, bad);
+}
+
+template <int kWU>
+static void launch_tiles(const GemmParams& p, hipStream_t st) {
+  const int tj = (p.N + 32 * kWU - 1) / (32 * kWU);
+  hipLaunchKernelGGL(gemm_tile_kernel<kWU>, dim3(p.nib * tj), dim3(kTileThreads), 0, st, p, p.nib, tj);
+}
+
+hipError_t launch_gemm_small(const GemmParams& p, SmallTile tile, hipStream_t st) {
+  switch (tile) {
+    case SmallTile::k32x32: {
+      const int units = ((p.M + 31) / 32) * ((p.N + 31) / 32);
+      hipLaunchKernelGGL(gemm_wave_kernel<4>, dim3(units), dim3(64), 0, st, p);
+      break;
+    }
+    case SmallTile::k128x64: launch_tiles<2>(p, st); break;
+    case SmallTile::k128x128: launch_tiles<4>(p, st); break;
+    case SmallTile::kNone: break;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace fq

@@ -130,6 +130,9 @@ struct RmsParams {
 hipError_t launch_quantize(const QuantParams& p, hipStream_t st);
 hipError_t launch_untile(const int8_t* tiled, int rows, int cols, int8_t* dense, hipStream_t st);
 hipError_t launch_gemm(const GemmParams& p, bool debug, hipStream_t st);
+// fq_gemm_tile.hip: the same product on smaller tiles, for outputs that do not fill the chip
+enum class SmallTile { kNone, k32x32, k128x64, k128x128 };
+hipError_t launch_gemm_small(const GemmParams& p, SmallTile tile, hipStream_t st);
 // groups of 32 / 64 (and the plain 128 kernel): fq_group.hip
 hipError_t launch_quantize_group(const QuantParams& p, hipStream_t st);
 hipError_t launch_gemm_group(const GemmParams& p, bool debug, hipStream_t st);
