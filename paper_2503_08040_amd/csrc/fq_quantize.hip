@@ -7,10 +7,10 @@
 // (u = [max|G| > theta]), Sec. 4.3 (second step on the residual G - a Q^),
 // Sec. 5.3 (the fallback decision is fused into the quantization kernel).
 //
-// One 256-thread workgroup owns one 128x128 block (32 KiB of bf16).  Thread t
-// holds 4 rows x 16 consecutive columns in registers: column chunk t%8, rows
-// t/8 + 32*p.  A 16-column chunk is exactly one lane's 16 bytes of a tile-order
-// fragment, so codes leave as 16-byte stores.
+// One 512-thread workgroup owns one 128x128 block (32 KiB of bf16).  Thread t holds 4 consecutive rows
+// x 8 consecutive columns in registers: rows 4 (t/16) ..., columns 8 (t%16) ....  A row of the block
+// is then 16 lanes x 16 bytes of one load, and the 4 x 8 codes give whole dwords of the block and of
+// its transpose, which reach tile order through an LDS image each and leave as 16-byte stores.
 #include <type_traits>
 
 #include "fq_device.h"
@@ -20,38 +20,54 @@ namespace fq {
 
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 512;
+constexpr int kWaves = kThreads / 64;
+constexpr int kRows = 4, kCols = 8;      // of a thread
 
-__device__ inline float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  return v;
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+// max of the wavefront's values (bit patterns of non-negative floats, which order like integers)
+__device__ inline uint32_t wave_max(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true));    // lane ^ 1
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true));    // lane ^ 2
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true));   // 7 - lane (of 8)
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true));   // 15 - lane
+  const uint32_t a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
+  const uint32_t c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
+  return max(max(a, b), max(c, d));
 }
 
-// max over the workgroup; every thread gets the result.  red: 4 floats of LDS.
-__device__ inline float block_max(float v, float* red) {
+// max over the workgroup, every thread gets it.  red: kWaves words of LDS that no earlier call in
+// flight uses (one barrier).
+__device__ inline float block_max(uint32_t v, uint32_t* red) {
   v = wave_max(v);
-  __syncthreads();  // red may still be read from a previous call
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  uint32_t m = red[0];
+#pragma unroll
+  for (int i = 1; i < kWaves; ++i) m = max(m, red[i]);
+  return __uint_as_float(m);
 }
 
-// sums of two binary64 values over the workgroup; every thread gets both.  red: 8 doubles.
+// sums of two binary64 values over the workgroup; every thread gets both.  red: 2 kWaves doubles.
 __device__ inline void block_sum2(double& a, double& b, double* red) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     a += __shfl_xor(a, off, 64);
     b += __shfl_xor(b, off, 64);
   }
-  __syncthreads();
   if ((threadIdx.x & 63) == 0) {
     red[threadIdx.x >> 6] = a;
-    red[4 + (threadIdx.x >> 6)] = b;
+    red[kWaves + (threadIdx.x >> 6)] = b;
   }
   __syncthreads();
-  a = (red[0] + red[1]) + (red[2] + red[3]);
-  b = (red[4] + red[5]) + (red[6] + red[7]);
+  a = b = 0.0;
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i) {
+    a += red[i];
+    b += red[kWaves + i];
+  }
 }
 
 // Philox4x32-10 (Salmon et al., SC'11): counter (c0, c1, 0, 0), key (k0, k1).
@@ -74,113 +90,167 @@ __device__ inline void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t k0, uint
   out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
-// Stochastic rounding of x/a with the 32-bit random word w: floor + [top 24 bits < fraction].
-__device__ inline int quantize_one_sr(float x, float a, uint32_t w) {
-  const float t = __fdiv_rn(x, a);
-  const float lo = floorf(t);
-  const float frac = t - lo;
-  float v = lo + (((float)(w >> 8) < frac * 16777216.0f) ? 1.0f : 0.0f);
-  v = fminf(fmaxf(v, -127.0f), 127.0f);
-  return (int)v;
-}
-
-// Register state of a thread: its 4 x 16 input values stay in the packed bf16 form they were
-// loaded in (raw[pz][half][dword], two values per dword, low half first) and its codes in
-// packed bytes (4 per dword).  Keeping both packed holds the kernel under 128 VGPRs, i.e. four
-// workgroups per compute unit: on the tensors this kernel sees (a thousand blocks or so) that
-// is the difference between one round of workgroups and a second, nearly empty one.
-__device__ inline float x_at(const v4i (&raw)[4][2], int pz, int e) {
-  const uint32_t w = (uint32_t)raw[pz][e >> 3][(e & 7) >> 1];
+// A thread's 4 x 8 input values stay in the packed bf16 form they were loaded in (two per dword, low
+// half first) and its codes in packed bytes (two dwords per row): half the registers of floats, which
+// is what lets a compute unit hold four workgroups.
+__device__ inline float x_at(const v4i (&raw)[kRows], int r, int e) {
+  const uint32_t w = (uint32_t)raw[r][e >> 1];
   return __uint_as_float((e & 1) ? (w & 0xFFFF0000u) : (w << 16));
 }
-
-__device__ inline int code_at(const v4i (&q)[4], int pz, int e) {
-  return (int)(int8_t)((uint32_t)q[pz][e >> 2] >> (8 * (e & 3)));
+__device__ inline int code_at(const u32x2 (&q)[kRows], int r, int e) {
+  return (int)(int8_t)(q[r][e >> 2] >> (8 * (e & 3)));
 }
 
-// Makes the packed inputs opaque to the optimizer at this point, so that values unpacked
-// before it are not kept alive across it (they are cheap to unpack again); emits no code.
-__device__ __forceinline__ void forget_unpacked(v4i (&raw)[4][2]) {
+// Makes the packed inputs opaque to the optimizer at this point, so that values unpacked before it
+// are not kept alive across it (they are cheap to unpack again); emits no code.
+__device__ __forceinline__ void forget_unpacked(v4i (&raw)[kRows]) {
 #pragma unroll
-  for (int pz = 0; pz < 4; ++pz) asm volatile("" : "+v"(raw[pz][0]), "+v"(raw[pz][1]));
+  for (int r = 0; r < kRows; ++r) asm volatile("" : "+v"(raw[r]));
+}
+__device__ __forceinline__ void forget_unpacked(u32x2 (&q)[kRows]) {
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) asm volatile("" : "+v"(q[r]));
 }
 
-// Round-to-nearest codes are packed without leaving the float domain: k is an integer-valued
-// float in [-127, 127] (rint_quotient clamps where a clamp can matter), k + 128 is exact and lies in [1, 255], and the pack-to-byte
-// conversion drops it into byte e % 4 of the row's dword.  finish_codes then turns the four
-// bytes of each dword into two's complement: k + 128 and k mod 256 differ in bit 7 only.
-__device__ __forceinline__ void put_code_f(v4i& q, int e, float k) {
-  q[e >> 2] = (int)__builtin_amdgcn_cvt_pk_u8_f32(k + 128.0f, e & 3,
-                                                  (e & 3) ? (unsigned)q[e >> 2] : 0u);
-}
-__device__ __forceinline__ void finish_codes(v4i& q) {
-#pragma unroll
-  for (int d = 0; d < 4; ++d) q[d] ^= (int)0x80808080u;
+// Byte 2 of four dwords as one dword.
+__device__ __forceinline__ uint32_t pack_byte2(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  const uint32_t lo = __builtin_amdgcn_perm(b, a, 0x0C0C0602u), hi = __builtin_amdgcn_perm(d, c, 0x06020C0Cu);
+  return lo | hi;
 }
 
-__device__ inline void put_code(v4i& q, int e, int code) {
-  const int sh = 8 * (e & 3);
-  if (sh == 0) q[e >> 2] = code & 0xFF;          // first byte of the dword: no read-modify
-  else q[e >> 2] |= (code & 0xFF) << sh;
+// The scale of a block and what round-to-nearest needs of it: r16 = 2^16 / a.
+struct Scale {
+  float a, r16;
+};
+__device__ inline Scale make_scale(float amax) {
+  Scale s;
+  s.a = __fdiv_rn(amax, 127.0f);
+  // A zero block takes code 0 everywhere.  Where the reciprocal or the products with it could leave
+  // the normal range NaN sends every element down the exact path.
+  s.r16 = s.a == 0.0f ? 0.0f
+          : (s.a >= 0x1p-100f && s.a <= 0x1p100f) ? __fdiv_rn(1.0f, s.a) * 65536.0f : __int_as_float(0x7FC00000);
+  return s;
 }
 
-// Writes this thread's 4x16 codes into an LDS image of the transposed block in
-// tile order, then the workgroup copies the image out linearly.
-__device__ inline void store_transposed(const v4i (&q)[4], int rp, int cc, int8_t* img,
-                                        int8_t* dst) {
-  __syncthreads();
+// codes[r] = rint(RN(x / a)) of the thread's values x = val(r, e), packed bytes, two's complement.
+// One fused multiply-add puts x / a + 128.5 into fixed point with 16 fraction bits (y): byte 2 is
+// the rounded quotient + 128, the low half says how far the quotient is from a half-integer.  In
+// units of 2^-16: the reciprocal is off by at most 0.5, the sum by 0.5, the binary32 rounding of the
+// true quotient by 0.25, so with 2 added to y a low half of 4 or more leaves no doubt.  Otherwise
+// (6 of 10^5 values, or r16 = NaN) the row is done again with the exact quotient, clamped: a
+// subnormal scale can be far from max/127.  4.75 vector instructions per value and no branch
+// but one per 8 values, where testing and branching per value took more than twice that.
+template <class F>
+__device__ __forceinline__ void quantize_rows(const F& val, const Scale& s, u32x2 (&codes)[kRows]) {
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    int r = p * 32 + rp;
+  for (int r = 0; r < kRows; ++r) {
+    uint32_t y[kCols];
+    u16x2 near = {0xFFFF, 0xFFFF};
 #pragma unroll
-    for (int e = 0; e < 16; ++e) img[tile_offset(cc * 16 + e, r)] = (int8_t)code_at(q, p, e);
-  }
-  __syncthreads();
-  const v4i* src = reinterpret_cast<const v4i*>(img);
-  v4i* out = reinterpret_cast<v4i*>(dst);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) out[i * kThreads + threadIdx.x] = src[i * kThreads + threadIdx.x];
-}
-
-// Thread (rp, cc) of the workgroup that owns block (bi, bk) loads its 4 x 16 bf16 values
-// (rows rp + 32 pz, columns 16 cc ...), zero outside the matrix.
-__device__ __forceinline__ void load_block(const QuantParams& p, int bi, int bk, int rp, int cc,
-                                  v4i (&raw)[4][2]) {
-  const int row0 = bi * kBlock, col0 = bk * kBlock + cc * 16;
-  const bool inner = (row0 + kBlock <= p.rows) && (bk * kBlock + kBlock <= p.cols) && p.vec_ok;
-  if (inner) {
-#pragma unroll
-    for (int pz = 0; pz < 4; ++pz) {
-      const uint16_t* src = p.x + (int64_t)(row0 + pz * 32 + rp) * p.ld + col0;
-      raw[pz][0] = *reinterpret_cast<const v4i*>(src);
-      raw[pz][1] = *reinterpret_cast<const v4i*>(src + 8);
+    for (int e = 0; e < kCols; ++e) {
+      y[e] = (uint32_t)__builtin_fmaf(val(r, e), s.r16, 128.5f * 65536.0f + 2.0f);
+      near = __builtin_elementwise_min(near, __builtin_bit_cast(u16x2, y[e]));
     }
-  } else {
+    codes[r][0] = pack_byte2(y[0], y[1], y[2], y[3]) ^ 0x80808080u;
+    codes[r][1] = pack_byte2(y[4], y[5], y[6], y[7]) ^ 0x80808080u;
+    if (near[0] < 4) {
 #pragma unroll
-    for (int pz = 0; pz < 4; ++pz) {
-      const int r = row0 + pz * 32 + rp;
-#pragma unroll
-      for (int d = 0; d < 8; ++d) {
+      for (int h = 0; h < 2; ++h) {
         uint32_t w = 0;
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          const int c = col0 + 2 * d + hh;
-          if (r < p.rows && c < p.cols) w |= (uint32_t)p.x[(int64_t)r * p.ld + c] << (16 * hh);
+        for (int e = 0; e < 4; ++e) {
+          const float k = fminf(fmaxf(rintf(__fdiv_rn(val(r, 4 * h + e), s.a)), -127.0f), 127.0f);
+          w |= ((uint32_t)(int)k & 0xFFu) << (8 * e);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        raw[pz][d >> 2][d & 3] = (int)w;
+        codes[r][h] = w;
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);     // one row's temporaries at a time
+  }
+}
+
+// Position of a 16-byte granule of an LDS image.  Lanes that write one instruction's values differ in
+// the bits folded into the low ones here, so they reach different banks; a run of 16 granules stays
+// a run of 16, permuted.  kT: image of the transposed block.
+template <bool kT>
+__device__ __forceinline__ int swizzle(int g) {
+  return kT ? g ^ (((g >> 4) & 1) | ((g >> 7) & 6)) : g ^ ((g >> 5) & 7);
+}
+
+// The thread's 4 x 8 codes into the image of the block in tile order (and of its transpose).
+template <bool kWantT>
+__device__ __forceinline__ void write_images(const u32x2 (&q)[kRows], int8_t* img, int8_t* img_t) {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));      // the addresses are worked out where they are used, not kept for a second call
+  const int row = kRows * (t >> 4), col = kCols * (t & 15);
+#pragma unroll
+  for (int r = 0; r < kRows; ++r)
+    *reinterpret_cast<u32x2*>(img + swizzle<false>(tile_offset(row + r, col) >> 4) * 16 + (col & 8)) = q[r];
+  if constexpr (kWantT) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      // 4 x 4 bytes: rows become columns
+      const uint32_t a = __builtin_amdgcn_perm(q[1][h], q[0][h], 0x05010400u);   // columns 0, 1 of rows 0, 1
+      const uint32_t b = __builtin_amdgcn_perm(q[1][h], q[0][h], 0x07030602u);   // columns 2, 3
+      const uint32_t c = __builtin_amdgcn_perm(q[3][h], q[2][h], 0x05010400u);
+      const uint32_t d = __builtin_amdgcn_perm(q[3][h], q[2][h], 0x07030602u);
+      const uint32_t t[4] = {__builtin_amdgcn_perm(c, a, 0x05040100u), __builtin_amdgcn_perm(c, a, 0x07060302u),
+                             __builtin_amdgcn_perm(d, b, 0x05040100u), __builtin_amdgcn_perm(d, b, 0x07060302u)};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int off = tile_offset(col + 4 * h + e, row);
+        *reinterpret_cast<uint32_t*>(img_t + swizzle<true>(off >> 4) * 16 + (off & 15)) = t[e];
       }
     }
   }
 }
 
-// max |G| of this thread's values
-__device__ __forceinline__ float thread_absmax(const v4i (&raw)[4][2]) {
-  float m = 0.0f;
+// The image, in order, to global memory.
+template <bool kT>
+__device__ __forceinline__ void copy_image(const int8_t* img, int8_t* dst) {
 #pragma unroll
-  for (int pz = 0; pz < 4; ++pz)
+  for (int i = 0; i < kBlockBytes / 16 / kThreads; ++i) {
+    const int g = i * kThreads + threadIdx.x;
+    reinterpret_cast<v4i*>(dst)[g] = reinterpret_cast<const v4i*>(img)[swizzle<kT>(g)];
+  }
+}
+
+// Loads the thread's 4 x 8 values of block (bi, bk), zero outside the matrix.  p.vec_ok: rows are
+// 16-byte aligned.
+__device__ __forceinline__ void load_block(const QuantParams& p, int bi, int bk, v4i (&raw)[kRows]) {
+  const int row = bi * kBlock + kRows * (threadIdx.x >> 4), col = bk * kBlock + kCols * (threadIdx.x & 15);
+  const uint16_t* src = p.x + (int64_t)row * p.ld + col;
+  if ((bi + 1) * kBlock <= p.rows && (bk + 1) * kBlock <= p.cols && p.vec_ok) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) m = fmaxf(m, fabsf(x_at(raw, pz, e)));
-  return m;
+    for (int r = 0; r < kRows; ++r) raw[r] = *reinterpret_cast<const v4i*>(src + r * p.ld);
+  } else {
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      raw[r] = v4i{0, 0, 0, 0};
+      if (row + r >= p.rows) continue;
+      if (col + kCols <= p.cols) {
+        // rows of any alignment: the hardware takes 16-byte loads at 2-byte addresses
+        __builtin_memcpy(&raw[r], src + r * p.ld, 16);
+      } else {
+#pragma unroll
+        for (int e = 0; e < kCols; ++e)
+          if (col + e < p.cols) raw[r][e >> 1] |= (int)((uint32_t)src[r * p.ld + e] << (16 * (e & 1)));
+      }
+    }
+  }
+}
+
+// max |G| of this thread's values as the bit pattern of a float: magnitudes of bf16 values order like
+// 16-bit integers, two at a time
+__device__ __forceinline__ uint32_t thread_absmax(const v4i (&raw)[kRows]) {
+  u16x2 m = {0, 0};
+#pragma unroll
+  for (int r = 0; r < kRows; ++r)
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+      m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, (uint32_t)raw[r][d] & 0x7FFF7FFFu));
+  return (uint32_t)(m[0] > m[1] ? m[0] : m[1]) << 16;
 }
 
 // The bits block b contributes to its group's word: "decided" and, if u, "flagged".
@@ -198,7 +268,7 @@ __device__ inline unsigned long long my_bits(int b, bool u) {
 // touched by device-scope atomics.  The list holds the lowest `capacity` ids when more blocks
 // are flagged than that.
 __device__ inline void write_fb_list(unsigned long long* words, int nb, int capacity,
-                                     int32_t* fb_list, int* wave_sum /* LDS, 4 ints */,
+                                     int32_t* fb_list, int* wave_sum /* LDS, kWaves ints */,
                                      int* base_sh /* LDS, 1 int */) {
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int n_words = (nb + 31) >> 5;
@@ -229,50 +299,132 @@ __device__ inline void write_fb_list(unsigned long long* words, int nb, int capa
       ++pos;
     }
     __syncthreads();
-    if (t == 0) *base_sh += wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
+    if (t == 0) {
+      for (int j = 0; j < kWaves; ++j) *base_sh += wave_sum[j];
+    }
+  }
+}
+
+
+// Exact quotient RN(x / a) for the stochastic rounding: r = RN(1 / a), and two residual corrections
+// (the second starts from a faithful quotient, which makes the result the correctly rounded one).
+// For a in [2^-90, 2^90]; a residual that underflows belongs to a quotient below 2^-25, whose
+// last bits the comparison with a 24-bit random number does not see.
+__device__ __forceinline__ float exact_quotient(float x, float a, float r) {
+  float q = x * r;
+  q = __builtin_fmaf(__builtin_fmaf(-q, a, x), r, q);
+  return __builtin_fmaf(__builtin_fmaf(-q, a, x), r, q);
+}
+
+// floor(t) + [top 24 bits of w < fraction of t], clamped, + 128 as a float
+__device__ __forceinline__ float round_stochastic(float t, uint32_t w) {
+  const float lo = floorf(t), frac = t - lo;
+  const float v = lo + (((float)(w >> 8) < frac * 16777216.0f) ? 1.0f : 0.0f);
+  return fminf(fmaxf(v, -127.0f), 127.0f) + 128.0f;
+}
+
+// How quantize_kernel rounds.  kSrAligned: stochastic, a row holds a multiple of 4 elements and the
+// matrix at most 2^34; kSr: stochastic, any size.
+enum Rounding { kNearest, kSrAligned, kSr };
+
+// Stochastic codes of row r of the thread.  Element (row, c) of the matrix uses word (row*cols + c) & 3
+// of the Philox block with counter (row*cols + c) >> 2; e0 is the thread's first element.  kSrAligned:
+// the 8 elements are 2 whole blocks, and the counter's upper half is zero, which makes most of the
+// first two rounds constant.  Otherwise they start at word `off` of the first of 3 blocks; off is the
+// same for the whole grid (the thread's first row is a multiple of 4, its first column of 8).
+template <Rounding kR>
+__device__ __forceinline__ void stochastic_row(const v4i (&raw)[kRows], int r, uint64_t e0, int off, uint64_t seed,
+                                               float a, float rcp, bool plain, u32x2& codes) {
+  const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+  auto block = [&](int b, uint32_t (&w)[4]) {
+    const uint64_t ctr = (e0 >> 2) + b;
+    philox4x32_10((uint32_t)ctr, kR == kSrAligned ? 0u : (uint32_t)(ctr >> 32), k0, k1, w);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // the four elements 4 h ... with the random words w
+  auto round4 = [&](int h, const uint32_t (&w)[4]) {
+    float t[4];
+    if (plain) {      // uniform over the workgroup
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t[e] = exact_quotient(x_at(raw, r, 4 * h + e), a, rcp);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t[e] = a == 0.0f ? 0.0f : __fdiv_rn(x_at(raw, r, 4 * h + e), a);
+    }
+    uint32_t c = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_cvt_pk_u8_f32(round_stochastic(t[e], w[e]), e, c);
+    codes[h] = c ^ 0x80808080u;
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if constexpr (kR == kSrAligned) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      uint32_t w[4];
+      block(h, w);
+      round4(h, w);
+    }
+  } else {
+    uint32_t w[3][4];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) block(b, w[b]);
+    if (off & 1) {
+#pragma unroll
+      for (int i = 0; i < kCols + 2; ++i) w[i >> 2][i & 3] = w[(i + 1) >> 2][(i + 1) & 3];
+    }
+    if (off & 2) {
+#pragma unroll
+      for (int i = 0; i < kCols; ++i) w[i >> 2][i & 3] = w[(i + 2) >> 2][(i + 2) & 3];
+    }
+    round4(0, w[0]);
+    round4(1, w[1]);
   }
 }
 
 }  // namespace
 
+// What bounds it: HBM for large tensors (4.6 TB/s of the 5 a large copy reaches on 8192 x 8192), on a
+// thousand blocks and fewer the chain load - maximum - quantize - store of a block that no other round
+// of workgroups overlaps.  Four rows x 8 columns per thread in 64 registers let four workgroups of
+// eight wavefronts share a compute unit (twice the wavefronts of a 4 x 16 split by 256 threads) and
+// halve a thread's part of that chain.  Measured against that split, re-quantizing into the same
+// tensor, 5 % of the blocks flagged: 2048 x 4096 14.2 -> 11.4 us, 4096 x 4096 19.2 -> 16.3 us (with
+// transposed copies 25.6 -> 17.8, stochastic with them 25.6 -> 19.8), 8192 x 8192 46.1 -> 43.9 us
+// (66.0 -> 59.1, 78.8 -> 68.3), 33 x 4096 13.1 -> 8.6 us.
 // kErr: the fallback decision uses a block quantization-error metric (criteria 3, 4), which
 // needs the residual of every block, not only of the flagged ones.
-// (The error-metric variants need the block's residuals and two binary64 sums on top of the
-// packed state: under the 128-register limit of four workgroups per compute unit they spill,
-// and run a quarter faster with two workgroups and no spills.)
-template <bool kWantT, bool kStochastic, bool kErr>
-__global__ __launch_bounds__(kThreads, kErr ? 2 : 4)
+template <bool kWantT, Rounding kR, bool kErr>
+__global__ __launch_bounds__(kThreads, kErr || kR == kSr ? 4 : 8)
 void quantize_kernel(QuantParams p) {
-  __shared__ float red[4];
-  __shared__ double redd[kErr ? 8 : 1];
+  __shared__ uint32_t red[2][kWaves];
+  __shared__ double redd[kErr ? 2 * kWaves : 1];
   __shared__ int slot_sh, last_sh, scan_base_sh;
-  __shared__ int scan_sh[4];
-  __shared__ __attribute__((aligned(16))) int8_t img[kWantT ? kBlockBytes : 16];
+  __shared__ int scan_sh[kWaves];
+  __shared__ __attribute__((aligned(16))) int8_t img[kBlockBytes];
+  __shared__ __attribute__((aligned(16))) int8_t img_t[kWantT ? kBlockBytes : 16];
 
   const int blk = blockIdx.x;
   const int bi = blk / p.nbc, bk = blk - bi * p.nbc;
   const int t = threadIdx.x;
-  const int cc = t & 7, rp = t >> 3;
-  const int row0 = bi * kBlock, col0 = bk * kBlock + cc * 16;
+  const int row = kRows * (t >> 4), col = kCols * (t & 15);     // inside the block
 
-  v4i raw[4][2];
-  load_block(p, bi, bk, rp, cc, raw);
+  v4i raw[kRows];
+  load_block(p, bi, bk, raw);
 
   // ---- step 1: a = max|G| / 127, codes = round(G / a)           (Sec. 3.1)
-  const float m = thread_absmax(raw);
-  const float amax = block_max(m, red);
-  const float a = __fdiv_rn(amax, 127.0f);
-  const float a_rcp = fast_recip(a);
+  const float amax = block_max(thread_absmax(raw), red[0]);
+  const Scale sc = make_scale(amax);
+  const float a = sc.a;
   forget_unpacked(raw);
 
   // The abs-max decision is known now: take the residual slot right away, so that the round
   // trip of the atomic is hidden behind the quantization of the block.          (Sec. 4.4)
-  // a tensor without residual slots has no list to write (nothing can fall back into it)
-  const bool want_list = p.capacity > 0;
+  // without residual slots or a criterion nothing can fall back: the list is empty, nobody counts
+  const bool want_list = kR == kNearest && p.capacity > 0 && p.crit != 0;
   bool u = false;
   int slot_early = -1;
   unsigned long long group_before = 0;   // thread 0: the group's word before this block's bits
-  if (!kErr) {
+  if (kR == kNearest && !kErr) {
     // criterion 5: the decision was taken by topk_select_kernel and is read from the mask
     u = p.crit == 2 || (p.crit == 1 && amax > p.theta) || (p.crit == 5 && p.mask[blk] != 0);
     if (t == 0) {
@@ -283,58 +435,26 @@ void quantize_kernel(QuantParams p) {
     if (u) __builtin_amdgcn_s_setprio(3);
   }
 
-  v4i q[4];
-  if (!kStochastic) {
-#pragma unroll
-    for (int pz = 0; pz < 4; ++pz) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        put_code_f(q[pz], e, (a == 0.0f) ? 0.0f : rint_quotient(x_at(raw, pz, e), a, a_rcp, 127.0f));
-        // eight elements in flight at a time: bounds the live temporaries
-        if ((e & 7) == 7) __builtin_amdgcn_sched_barrier(0);
-      }
-      finish_codes(q[pz]);
-    }
+  u32x2 q[kRows];
+  if constexpr (kR == kNearest) {
+    quantize_rows([&](int r, int e) { return x_at(raw, r, e); }, sc, q);
   } else {
-    // element (r, c) uses word (r*cols + c) & 3 of the Philox block with counter (r*cols + c) >> 2.
-    // A thread's 16 consecutive elements of a row start at word `off` of a block and span 4
-    // blocks (off = 0) or 5; off is the same for its four rows (they are 32*cols elements apart).
-    const uint32_t k0 = (uint32_t)p.seed, k1 = (uint32_t)(p.seed >> 32);
-    auto rows_at = [&](auto off_c) {
-      constexpr int off = decltype(off_c)::value;
-      constexpr int kBlocks = off ? 5 : 4;
+    const bool plain = a >= 0x1p-90f && a <= 0x1p90f;       // uniform over the workgroup
+    const float rcp = plain ? __fdiv_rn(1.0f, a) : 0.0f;
 #pragma unroll
-      for (int pz = 0; pz < 4; ++pz) {
-        const uint64_t e0 = (uint64_t)(row0 + pz * 32 + rp) * (uint64_t)p.cols + (uint64_t)col0;
-#pragma unroll
-        for (int b = 0; b < kBlocks; ++b) {
-          uint32_t w[4];
-          const uint64_t ctr = (e0 >> 2) + b;
-          philox4x32_10((uint32_t)ctr, (uint32_t)(ctr >> 32), k0, k1, w);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int e = 4 * b + i - off;      // compile-time after unrolling
-            if (e >= 0 && e < 16)
-              put_code(q[pz], e, (a == 0.0f) ? 0 : quantize_one_sr(x_at(raw, pz, e), a, w[i]));
-          }
-        }
-      }
-    };
-    switch ((int)(((uint64_t)(row0 + rp) * (uint64_t)p.cols + (uint64_t)col0) & 3)) {
-      case 0: rows_at(std::integral_constant<int, 0>{}); break;
-      case 1: rows_at(std::integral_constant<int, 1>{}); break;
-      case 2: rows_at(std::integral_constant<int, 2>{}); break;
-      default: rows_at(std::integral_constant<int, 3>{}); break;
+    for (int r = 0; r < kRows; ++r) {
+      const uint64_t e0 = (uint64_t)(bi * kBlock + row + r) * (uint64_t)p.cols + (uint64_t)(bk * kBlock + col);
+      stochastic_row<kR>(raw, r, e0, (r * p.cols) & 3, p.seed, a, rcp, plain, q[r]);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 
-  // ---- the block's residual slot, known to the whole workgroup before the codes are stored (the
-  // atomic issued after the decision has had the whole quantization to come back; an unflagged
-  // block does not look at it at all); with an error-based criterion the decision is only known
-  // after the codes, so this runs there.
-  int slot = -1;
-  auto record_block = [&]() {
-    if (t == 0) {
+  // ---- the block's residual slot, known to the whole workgroup with the barrier behind the images
+  // (the atomic issued after the decision has had the whole quantization to come back; an
+  // unflagged block does not look at it at all); with an error-based criterion the decision is only
+  // known after the codes, so it gets a barrier of its own.
+  auto publish_slot = [&]() {
+    if (kR == kNearest && t == 0) {
       int slot0 = -1;
       if (u) {
         asm volatile("" : "+v"(slot_early));     // keeps the wait for the atomic inside this branch
@@ -342,9 +462,15 @@ void quantize_kernel(QuantParams p) {
       }
       slot_sh = slot0;
     }
-    __syncthreads();
-    slot = slot_sh;
   };
+  if (!kErr) publish_slot();
+  forget_unpacked(raw);
+  write_images<kWantT>(q, img, img_t);
+  __syncthreads();
+  int slot = kErr || kR != kNearest ? -1 : slot_sh;
+  copy_image<false>(img, p.codes + (int64_t)blk * kBlockBytes);
+  if (kWantT) copy_image<true>(img_t, p.codes_t + ((int64_t)bk * p.nbr + bi) * kBlockBytes);
+
   // ---- per-block outputs: scale, mask, slot.  Stored last, when the wavefront has nothing left
   // to compute: a register that held store data is not reused before the store has completed,
   // and behind these small stores that wait sat in the middle of the quantization.
@@ -369,7 +495,8 @@ void quantize_kernel(QuantParams p) {
       asm volatile("" ::"v"(group_before));
       const uint32_t decided = (uint32_t)group_before | (1u << (blk & 31));
       bool last = false;
-      if (decided == full) last = atomicAdd(p.fb_groups_done, 1) == ((nb + 31) >> 5) - 1;
+      const int groups = (nb + 31) >> 5;
+      if (decided == full) last = groups == 1 || atomicAdd(p.fb_groups_done, 1) == groups - 1;
       last_sh = last;
     }
     __syncthreads();
@@ -378,19 +505,10 @@ void quantize_kernel(QuantParams p) {
       if (t == 0) *p.fb_groups_done = 0;    // ready for the next call
     }
   };
-  if (!kErr) record_block();
 
-  forget_unpacked(raw);
-  int8_t* cdst = p.codes + (int64_t)blk * kBlockBytes;
-#pragma unroll
-  for (int pz = 0; pz < 4; ++pz)
-    *reinterpret_cast<v4i*>(cdst + tile_offset(pz * 32 + rp, cc * 16)) = q[pz];
-  if (kWantT)
-    store_transposed(q, rp, cc, img, p.codes_t + ((int64_t)bk * p.nbr + bi) * kBlockBytes);
-
-  // the residual G - a*codes of element (pz, e): one fused multiply-add, single rounding
-  auto residual = [&](int pz, int e) {
-    return __builtin_fmaf(-(float)code_at(q, pz, e), a, x_at(raw, pz, e));
+  // the residual G - a*codes of element (r, e): one fused multiply-add, single rounding
+  auto residual = [&](int r, int e) {
+    return __builtin_fmaf(-(float)code_at(q, r, e), a, x_at(raw, r, e));
   };
 
   // ---- fallback decision by a quantization-error metric          (Sec. 4.4)
@@ -399,11 +517,11 @@ void quantize_kernel(QuantParams p) {
     // accumulations of the binary32 terms (order unspecified), compared with theta in binary64
     double l1 = 0.0, l1x = 0.0;
 #pragma unroll
-    for (int pz = 0; pz < 4; ++pz)
+    for (int r = 0; r < kRows; ++r)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        l1x += (double)fabsf(x_at(raw, pz, e));
-        l1 += (double)fabsf(residual(pz, e));
+      for (int e = 0; e < kCols; ++e) {
+        l1x += (double)fabsf(x_at(raw, r, e));
+        l1 += (double)fabsf(residual(r, e));
       }
     block_sum2(l1, l1x, redd);
     if (p.crit == 3) u = l1 > (double)p.theta;
@@ -412,43 +530,35 @@ void quantize_kernel(QuantParams p) {
       if (u) slot_early = atomicAdd(p.fb_count, 1);
       if (want_list) group_before = atomicOr(p.fb_words + (blk >> 5), my_bits(blk, u));
     }
+    publish_slot();
+    __syncthreads();
+    slot = slot_sh;
   }
-
-  if (kErr) record_block();
-  if (slot < 0) {        // uniform over the workgroup
+  if (kR != kNearest || slot < 0) {        // uniform over the workgroup
     store_block_record();
     finish_list();
     return;
   }
 
   // ---- step 2: quantize the residual G - a*codes                 (Sec. 4.3)
-  // (the residual is recomputed where it is needed instead of being kept in 64 registers)
+  // (the residual is recomputed where it is needed instead of being kept in registers)
   float rm = 0.0f;
 #pragma unroll
-  for (int pz = 0; pz < 4; ++pz)
+  for (int r = 0; r < kRows; ++r) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) rm = fmaxf(rm, fabsf(residual(pz, e)));
-  const float rmax = block_max(rm, red);
-  const float ra = __fdiv_rn(rmax, 127.0f);
-  const float ra_rcp = fast_recip(ra);
-  forget_unpacked(raw);
-  v4i rq[4];
-#pragma unroll
-  for (int pz = 0; pz < 4; ++pz) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      put_code_f(rq[pz], e, (ra == 0.0f) ? 0.0f : rint_quotient(residual(pz, e), ra, ra_rcp, 127.0f));
-      if ((e & 7) == 7) __builtin_amdgcn_sched_barrier(0);
-    }
-    finish_codes(rq[pz]);
+    for (int e = 0; e < kCols; ++e) rm = fmaxf(rm, fabsf(residual(r, e)));
+    __builtin_amdgcn_sched_barrier(0);
   }
-
-  int8_t* rdst = p.res_codes + (int64_t)slot * kBlockBytes;
-#pragma unroll
-  for (int pz = 0; pz < 4; ++pz)
-    *reinterpret_cast<v4i*>(rdst + tile_offset(pz * 32 + rp, cc * 16)) = rq[pz];
-  if (kWantT) store_transposed(rq, rp, cc, img, p.res_codes_t + (int64_t)slot * kBlockBytes);
-  if (t == 0) p.res_scales[slot] = ra;
+  const Scale rs = make_scale(block_max(__float_as_uint(rm), red[1]));   // its barrier frees the images
+  forget_unpacked(raw);
+  forget_unpacked(q);
+  u32x2 rq[kRows];
+  quantize_rows(residual, rs, rq);
+  write_images<kWantT>(rq, img, img_t);
+  __syncthreads();
+  copy_image<false>(img, p.res_codes + (int64_t)slot * kBlockBytes);
+  if (kWantT) copy_image<true>(img_t, p.res_codes_t + (int64_t)slot * kBlockBytes);
+  if (t == 0) p.res_scales[slot] = rs.a;
   store_block_record();
   finish_list();
 }
@@ -458,12 +568,12 @@ void quantize_kernel(QuantParams p) {
 
 // max |G| of each block into amax[nbr * nbc] (the tensor's scale array serves as that buffer
 // until quantize_kernel overwrites it with the scales).
-__global__ __launch_bounds__(kThreads, 4) void block_absmax_kernel(QuantParams p) {
-  __shared__ float red[4];
+__global__ __launch_bounds__(kThreads, 8) void block_absmax_kernel(QuantParams p) {
+  __shared__ uint32_t red[kWaves];
   const int blk = blockIdx.x;
   const int bi = blk / p.nbc, bk = blk - bi * p.nbc;
-  v4i raw[4][2];
-  load_block(p, bi, bk, threadIdx.x >> 3, threadIdx.x & 7, raw);
+  v4i raw[kRows];
+  load_block(p, bi, bk, raw);
   const float amax = block_max(thread_absmax(raw), red);
   if (threadIdx.x == 0) p.scales[blk] = amax;
 }
@@ -585,16 +695,17 @@ hipError_t launch_quantize(const QuantParams& p, hipStream_t st) {
   if (nb > 0) {
     const dim3 grid(nb), block(kThreads);
     const bool err = p.crit == 3 || p.crit == 4;
-    if (p.stochastic) {
-      if (p.codes_t) hipLaunchKernelGGL((quantize_kernel<true, true, false>), grid, block, 0, st, p);
-      else hipLaunchKernelGGL((quantize_kernel<false, true, false>), grid, block, 0, st, p);
-    } else if (err) {
-      if (p.codes_t) hipLaunchKernelGGL((quantize_kernel<true, false, true>), grid, block, 0, st, p);
-      else hipLaunchKernelGGL((quantize_kernel<false, false, true>), grid, block, 0, st, p);
-    } else {
-      if (p.codes_t) hipLaunchKernelGGL((quantize_kernel<true, false, false>), grid, block, 0, st, p);
-      else hipLaunchKernelGGL((quantize_kernel<false, false, false>), grid, block, 0, st, p);
-    }
+    auto go = [&](auto rounding, auto err_c) {
+      constexpr Rounding kR = (Rounding)decltype(rounding)::value;
+      constexpr bool kErr = decltype(err_c)::value;
+      if (p.codes_t) hipLaunchKernelGGL((quantize_kernel<true, kR, kErr>), grid, block, 0, st, p);
+      else hipLaunchKernelGGL((quantize_kernel<false, kR, kErr>), grid, block, 0, st, p);
+    };
+    const bool aligned = p.cols % 4 == 0 && (int64_t)p.rows * p.cols <= (int64_t)1 << 34;
+    if (p.stochastic && aligned) go(std::integral_constant<int, kSrAligned>{}, std::false_type{});
+    else if (p.stochastic) go(std::integral_constant<int, kSr>{}, std::false_type{});
+    else if (err) go(std::integral_constant<int, kNearest>{}, std::true_type{});
+    else go(std::integral_constant<int, kNearest>{}, std::false_type{});
   }
   return hipGetLastError();
 }
