@@ -137,10 +137,36 @@ def _check(status, where):
         raise FqError(status, where)
 
 
+# A call below is two or three microseconds of Python in front of about 3.6 of launch, and a small layer
+# is a handful of such calls: pointers go to ctypes as plain integers, a QTensor keeps the reference to
+# its struct, and the current stream's handle is asked for without making a torch.cuda.Stream
+# (0.1 instead of 2.9 us per call).
+_torch = None
+
+
+def _t():
+    """The torch module, imported on first use (the library itself does not need it)."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _stream_ptr(stream):
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    c = _t()._C
+    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+
+
+def _bf16_matrix(x):
+    """(rows, cols, pitch) of a 2-D torch.bfloat16 CUDA tensor with unit column stride."""
+    assert x.dtype == _t().bfloat16 and x.dim() == 2 and x.is_cuda
+    rows, cols = x.shape
+    ld, sc = x.stride()
+    assert sc == 1 or cols <= 1
+    return rows, cols, ld if rows > 1 else max(cols, 1)
 
 
 def fq_qtensor_bytes(rows, cols, capacity, want_transposed=False, block=FQ_BLOCK) -> int:
@@ -169,6 +195,7 @@ class QTensor:
         self.storage = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
         self._base = (self.storage.data_ptr() + 255) & ~255
         self.c = fq_qtensor()
+        self._ref = C.byref(self.c)
         _check(lib().fq_qtensor_bind(C.c_void_p(self._base), self.rows, self.cols, self.block,
                                      self.capacity, int(self.want_transposed), C.byref(self.c)),
                "fq_qtensor_bind")
@@ -205,45 +232,32 @@ class QTensor:
 def fq_quantize(x, crit, theta, out: QTensor = None, capacity=None, want_transposed=False,
                 stream=None, block=FQ_BLOCK) -> QTensor:
     """x: 2-D torch.bfloat16 CUDA tensor with unit column stride."""
-    import torch
-    assert x.dtype == torch.bfloat16 and x.dim() == 2 and x.is_cuda
-    assert x.stride(1) == 1 or x.shape[1] <= 1
-    rows, cols = x.shape
-    ld = x.stride(0) if rows > 1 else max(cols, 1)
+    rows, cols, ld = _bf16_matrix(x)
     if out is None:
         out = QTensor(rows, cols, capacity, want_transposed, x.device, block=block)
-    _check(lib().fq_quantize(C.c_void_p(x.data_ptr()), rows, cols, ld, out.block, int(crit),
-                             C.c_float(theta), C.byref(out.c), _stream_ptr(stream)), "fq_quantize")
+    _check((_lib or lib()).fq_quantize(x.data_ptr(), rows, cols, ld, out.block, int(crit), float(theta), out._ref,
+                                       _stream_ptr(stream)), "fq_quantize")
     return out
 
 
 def fq_quantize_sr(x, seed, out: QTensor = None, want_transposed=False, stream=None) -> QTensor:
     """Block INT8 with stochastic rounding (no fallback); x as for fq_quantize."""
-    import torch
-    assert x.dtype == torch.bfloat16 and x.dim() == 2 and x.is_cuda
-    assert x.stride(1) == 1 or x.shape[1] <= 1
-    rows, cols = x.shape
-    ld = x.stride(0) if rows > 1 else max(cols, 1)
+    rows, cols, ld = _bf16_matrix(x)
     if out is None:
         out = QTensor(rows, cols, 0, want_transposed, x.device)
-    _check(lib().fq_quantize_sr(C.c_void_p(x.data_ptr()), rows, cols, ld, FQ_BLOCK,
-                                C.c_uint64(seed), C.byref(out.c), _stream_ptr(stream)),
-           "fq_quantize_sr")
+    _check((_lib or lib()).fq_quantize_sr(x.data_ptr(), rows, cols, ld, FQ_BLOCK, C.c_uint64(seed), out._ref,
+                                          _stream_ptr(stream)), "fq_quantize_sr")
     return out
 
 
 def fq_quantize_topk(x, k, out: QTensor = None, capacity=None, want_transposed=False,
                      stream=None) -> QTensor:
     """As fq_quantize, with the k blocks of largest abs-max falling back (Sec. 4.4)."""
-    import torch
-    assert x.dtype == torch.bfloat16 and x.dim() == 2 and x.is_cuda
-    assert x.stride(1) == 1 or x.shape[1] <= 1
-    rows, cols = x.shape
-    ld = x.stride(0) if rows > 1 else max(cols, 1)
+    rows, cols, ld = _bf16_matrix(x)
     if out is None:
         out = QTensor(rows, cols, capacity, want_transposed, x.device)
-    _check(lib().fq_quantize_topk(C.c_void_p(x.data_ptr()), rows, cols, ld, FQ_BLOCK, int(k),
-                                  C.byref(out.c), _stream_ptr(stream)), "fq_quantize_topk")
+    _check((_lib or lib()).fq_quantize_topk(x.data_ptr(), rows, cols, ld, FQ_BLOCK, int(k), out._ref,
+                                            _stream_ptr(stream)), "fq_quantize_topk")
     return out
 
 
@@ -275,34 +289,36 @@ def fq_gemm_biased(op, A: QTensor, B: QTensor, out=None, out_dtype=None, stream=
 
 def fq_gemm(op, A: QTensor, B: QTensor, out=None, out_dtype=None, stream=None, _entry="fq_gemm"):
     """C = A (op) B per Alg. 1; out is a 2-D float32 or bfloat16 CUDA tensor."""
-    import torch
+    torch = _t()
     Mo, No = gemm_out_shape(op, A, B)
     if out is None:
         out = torch.empty((Mo, No), dtype=out_dtype or torch.float32, device=A.storage.device)
-    assert out.shape == (Mo, No) and (out.stride(1) == 1 or No <= 1)
+        ldc = max(No, 1)
+    else:
+        assert out.shape == (Mo, No) and (out.stride(1) == 1 or No <= 1)
+        ldc = out.stride(0) if Mo > 1 else max(No, 1)
     cdt = {torch.float32: FQ_OUT_F32, torch.bfloat16: FQ_OUT_BF16}[out.dtype]
-    ldc = out.stride(0) if Mo > 1 else max(No, 1)
-    _check(getattr(lib(), _entry)(int(op), C.byref(A.c), C.byref(B.c), C.c_void_p(out.data_ptr()),
-                                  cdt, ldc, _stream_ptr(stream)), _entry)
+    _check(getattr(_lib or lib(), _entry)(int(op), A._ref, B._ref, out.data_ptr(), cdt, ldc, _stream_ptr(stream)),
+           _entry)
     return out
 
 
 def fq_gemm_debug_partials(op, A: QTensor, B: QTensor, k_block, residual_term, stream=None):
-    import torch
+    torch = _t()
     Mo, No = gemm_out_shape(op, A, B)
     out = torch.zeros((Mo, No), dtype=torch.int32, device=A.storage.device)
-    _check(lib().fq_gemm_debug_partials(int(op), C.byref(A.c), C.byref(B.c), int(k_block),
-                                        int(bool(residual_term)), C.c_void_p(out.data_ptr()),
+    _check(lib().fq_gemm_debug_partials(int(op), A._ref, B._ref, int(k_block),
+                                        int(bool(residual_term)), out.data_ptr(),
                                         _stream_ptr(stream)), "fq_gemm_debug_partials")
     return out
 
 
 def fq_codes_to_rowmajor(tiled, rows, cols, stream=None):
     """tiled: int8 CUDA tensor in tile order (a QTensor 'codes' view)."""
-    import torch
+    torch = _t()
     dense = torch.empty((rows, cols), dtype=torch.int8, device=tiled.device)
-    _check(lib().fq_codes_to_rowmajor(C.c_void_p(tiled.data_ptr()), rows, cols,
-                                      C.c_void_p(dense.data_ptr()), _stream_ptr(stream)),
+    _check(lib().fq_codes_to_rowmajor(tiled.data_ptr(), rows, cols,
+                                      dense.data_ptr(), _stream_ptr(stream)),
            "fq_codes_to_rowmajor")
     return dense
 
@@ -310,7 +326,7 @@ def fq_codes_to_rowmajor(tiled, rows, cols, stream=None):
 def fq_qtensor_check(t: QTensor, stream=None) -> int:
     """Synchronizes; returns the number of flagged blocks, raises on capacity overflow."""
     n = C.c_int32(0)
-    _check(lib().fq_qtensor_check(C.byref(t.c), C.byref(n), _stream_ptr(stream)), "fq_qtensor_check")
+    _check(lib().fq_qtensor_check(t._ref, C.byref(n), _stream_ptr(stream)), "fq_qtensor_check")
     return int(n.value)
 
 
@@ -325,27 +341,24 @@ def fq_ctx_scales_bytes(rows, cols) -> int:
 def fq_ctx_quantize(x, packed=None, scales=None, stream=None):
     """1 x 128 group INT10 compression of a 2-D bf16 CUDA tensor (Sec. 5.2 of the paper).
     Returns (packed uint8 [rows, ng, 160], scales float32 [rows, ng])."""
-    import torch
-    assert x.dtype == torch.bfloat16 and x.dim() == 2 and x.is_cuda
-    assert x.stride(1) == 1 or x.shape[1] <= 1
-    rows, cols = x.shape
+    torch = _t()
+    rows, cols, ld = _bf16_matrix(x)
     ng = -(-cols // FQ_CTX_GROUP)
-    ld = x.stride(0) if rows > 1 else max(cols, 1)
     if packed is None:
         packed = torch.empty((rows, ng, FQ_CTX_GROUP_BYTES), dtype=torch.uint8, device=x.device)
     if scales is None:
         scales = torch.empty((rows, ng), dtype=torch.float32, device=x.device)
     assert packed.is_contiguous() and packed.numel() == fq_ctx_packed_bytes(rows, cols)
     assert scales.is_contiguous() and scales.numel() * 4 == fq_ctx_scales_bytes(rows, cols)
-    _check(lib().fq_ctx_quantize(C.c_void_p(x.data_ptr()), rows, cols, ld,
-                                 C.c_void_p(packed.data_ptr()), C.c_void_p(scales.data_ptr()),
+    _check(lib().fq_ctx_quantize(x.data_ptr(), rows, cols, ld,
+                                 packed.data_ptr(), scales.data_ptr(),
                                  _stream_ptr(stream)), "fq_ctx_quantize")
     return packed, scales
 
 
 def fq_ctx_dequantize(packed, scales, rows, cols, out=None, stream=None):
     """Inverse of fq_ctx_quantize: a bf16 [rows, cols] CUDA tensor."""
-    import torch
+    torch = _t()
     if out is None:
         out = torch.empty((rows, cols), dtype=torch.bfloat16, device=packed.device)
     assert out.dtype == torch.bfloat16 and out.shape == (rows, cols)
@@ -353,8 +366,8 @@ def fq_ctx_dequantize(packed, scales, rows, cols, out=None, stream=None):
     assert packed.is_contiguous() and packed.numel() == fq_ctx_packed_bytes(rows, cols)
     assert scales.is_contiguous() and scales.numel() * 4 == fq_ctx_scales_bytes(rows, cols)
     ldo = out.stride(0) if rows > 1 else max(cols, 1)
-    _check(lib().fq_ctx_dequantize(C.c_void_p(packed.data_ptr()), C.c_void_p(scales.data_ptr()),
-                                   rows, cols, C.c_void_p(out.data_ptr()), ldo,
+    _check(lib().fq_ctx_dequantize(packed.data_ptr(), scales.data_ptr(),
+                                   rows, cols, out.data_ptr(), ldo,
                                    _stream_ptr(stream)), "fq_ctx_dequantize")
     return out
 
@@ -376,7 +389,7 @@ def _pitch(t):
 def fq_glu_forward(x1, x2, stream=None):
     """y = silu(x1) * x2 with the INT10 contexts of x1 and x2 written in the same pass.
     Returns (y bf16, (packed1, scales1), (packed2, scales2))."""
-    import torch
+    torch = _t()
     assert x1.dtype == x2.dtype == torch.bfloat16 and x1.shape == x2.shape and x1.dim() == 2
     assert _pitch(x1) == _pitch(x2)
     rows, cols = x1.shape
@@ -384,25 +397,25 @@ def fq_glu_forward(x1, x2, stream=None):
     y = torch.empty((rows, cols), dtype=torch.bfloat16, device=x1.device)
     ctx = [(torch.empty((rows, ng, FQ_CTX_GROUP_BYTES), dtype=torch.uint8, device=x1.device),
             torch.empty((rows, ng), dtype=torch.float32, device=x1.device)) for _ in range(2)]
-    _check(lib().fq_glu_forward(C.c_void_p(x1.data_ptr()), C.c_void_p(x2.data_ptr()), rows, cols,
-                                _pitch(x1), C.c_void_p(y.data_ptr()), _pitch(y),
-                                C.c_void_p(ctx[0][0].data_ptr()), C.c_void_p(ctx[0][1].data_ptr()),
-                                C.c_void_p(ctx[1][0].data_ptr()), C.c_void_p(ctx[1][1].data_ptr()),
+    _check(lib().fq_glu_forward(x1.data_ptr(), x2.data_ptr(), rows, cols,
+                                _pitch(x1), y.data_ptr(), _pitch(y),
+                                ctx[0][0].data_ptr(), ctx[0][1].data_ptr(),
+                                ctx[1][0].data_ptr(), ctx[1][1].data_ptr(),
                                 _stream_ptr(stream)), "fq_glu_forward")
     return y, ctx[0], ctx[1]
 
 
 def fq_glu_backward(dy, ctx1, ctx2, stream=None):
     """(dx1, dx2) bf16 from dy and the two contexts of fq_glu_forward."""
-    import torch
+    torch = _t()
     assert dy.dtype == torch.bfloat16 and dy.dim() == 2
     rows, cols = dy.shape
     dx1 = torch.empty((rows, cols), dtype=torch.bfloat16, device=dy.device)
     dx2 = torch.empty_like(dx1)
-    _check(lib().fq_glu_backward(C.c_void_p(dy.data_ptr()), _pitch(dy),
-                                 C.c_void_p(ctx1[0].data_ptr()), C.c_void_p(ctx1[1].data_ptr()),
-                                 C.c_void_p(ctx2[0].data_ptr()), C.c_void_p(ctx2[1].data_ptr()),
-                                 rows, cols, C.c_void_p(dx1.data_ptr()), C.c_void_p(dx2.data_ptr()),
+    _check(lib().fq_glu_backward(dy.data_ptr(), _pitch(dy),
+                                 ctx1[0].data_ptr(), ctx1[1].data_ptr(),
+                                 ctx2[0].data_ptr(), ctx2[1].data_ptr(),
+                                 rows, cols, dx1.data_ptr(), dx2.data_ptr(),
                                  _pitch(dx1), _stream_ptr(stream)), "fq_glu_backward")
     return dx1, dx2
 
@@ -410,7 +423,7 @@ def fq_glu_backward(dy, ctx1, ctx2, stream=None):
 def fq_rmsnorm_forward(x, w, eps, stream=None):
     """y = x * rstd * w per row with the INT10 context of x and rstd written in the same pass.
     Returns (y bf16, rstd float32 [rows], (packed, scales))."""
-    import torch
+    torch = _t()
     assert x.dtype == w.dtype == torch.bfloat16 and x.dim() == 2 and w.shape == (x.shape[1],)
     assert w.is_contiguous()
     rows, cols = x.shape
@@ -419,10 +432,10 @@ def fq_rmsnorm_forward(x, w, eps, stream=None):
     rstd = torch.empty((rows,), dtype=torch.float32, device=x.device)
     packed = torch.empty((rows, ng, FQ_CTX_GROUP_BYTES), dtype=torch.uint8, device=x.device)
     scales = torch.empty((rows, ng), dtype=torch.float32, device=x.device)
-    _check(lib().fq_rmsnorm_forward(C.c_void_p(x.data_ptr()), C.c_void_p(w.data_ptr()), rows, cols,
-                                    _pitch(x), C.c_float(eps), C.c_void_p(y.data_ptr()), _pitch(y),
-                                    C.c_void_p(packed.data_ptr()), C.c_void_p(scales.data_ptr()),
-                                    C.c_void_p(rstd.data_ptr()), _stream_ptr(stream)),
+    _check(lib().fq_rmsnorm_forward(x.data_ptr(), w.data_ptr(), rows, cols,
+                                    _pitch(x), float(eps), y.data_ptr(), _pitch(y),
+                                    packed.data_ptr(), scales.data_ptr(),
+                                    rstd.data_ptr(), _stream_ptr(stream)),
            "fq_rmsnorm_forward")
     return y, rstd, (packed, scales)
 
@@ -431,27 +444,27 @@ def fq_rmsnorm_backward_static(dy, ctx, rstd, w, dx, dw, n_parts=64, stream=None
     """fq_rmsnorm_backward into caller-provided dx (bf16 [rows, cols]) and dw (float32 [cols])
     with the library's built-in scratch buffer: the call allocates nothing."""
     rows, cols = dy.shape
-    _check(lib().fq_rmsnorm_backward_static(C.c_void_p(dy.data_ptr()), _pitch(dy),
-                                            C.c_void_p(ctx[0].data_ptr()), C.c_void_p(ctx[1].data_ptr()),
-                                            C.c_void_p(rstd.data_ptr()), C.c_void_p(w.data_ptr()),
-                                            rows, cols, C.c_void_p(dx.data_ptr()), _pitch(dx),
-                                            C.c_void_p(dw.data_ptr()), int(n_parts), _stream_ptr(stream)),
+    _check(lib().fq_rmsnorm_backward_static(dy.data_ptr(), _pitch(dy),
+                                            ctx[0].data_ptr(), ctx[1].data_ptr(),
+                                            rstd.data_ptr(), w.data_ptr(),
+                                            rows, cols, dx.data_ptr(), _pitch(dx),
+                                            dw.data_ptr(), int(n_parts), _stream_ptr(stream)),
            "fq_rmsnorm_backward_static")
     return dx, dw
 
 
 def fq_rmsnorm_backward(dy, ctx, rstd, w, n_parts=256, stream=None):
     """(dx bf16, dw float32 [cols]) from dy, the context and rstd of fq_rmsnorm_forward, and w."""
-    import torch
+    torch = _t()
     assert dy.dtype == w.dtype == torch.bfloat16 and dy.dim() == 2 and w.is_contiguous()
     rows, cols = dy.shape
     dx = torch.empty((rows, cols), dtype=torch.bfloat16, device=dy.device)
     dw = torch.empty((cols,), dtype=torch.float32, device=dy.device)
     parts = torch.empty((n_parts * cols + rows,), dtype=torch.float32, device=dy.device)
-    _check(lib().fq_rmsnorm_backward(C.c_void_p(dy.data_ptr()), _pitch(dy),
-                                     C.c_void_p(ctx[0].data_ptr()), C.c_void_p(ctx[1].data_ptr()),
-                                     C.c_void_p(rstd.data_ptr()), C.c_void_p(w.data_ptr()), rows, cols,
-                                     C.c_void_p(dx.data_ptr()), _pitch(dx), C.c_void_p(dw.data_ptr()),
-                                     C.c_void_p(parts.data_ptr()), int(n_parts), _stream_ptr(stream)),
+    _check(lib().fq_rmsnorm_backward(dy.data_ptr(), _pitch(dy),
+                                     ctx[0].data_ptr(), ctx[1].data_ptr(),
+                                     rstd.data_ptr(), w.data_ptr(), rows, cols,
+                                     dx.data_ptr(), _pitch(dx), dw.data_ptr(),
+                                     parts.data_ptr(), int(n_parts), _stream_ptr(stream)),
            "fq_rmsnorm_backward")
     return dx, dw
