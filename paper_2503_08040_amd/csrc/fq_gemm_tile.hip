@@ -20,7 +20,7 @@
 // 550 cycles per step).  Smaller tiles win while the chip is not full, larger ones from then on;
 // plan_small in fq_gemm.hip has the rule.
 // Measured (GEMM alone, bf16 output, 5 % of the blocks flagged, gemm_kernel -> the form chosen):
-// 33 x 4096 x 11008 70.6 -> 12.4 us, 256 x 11008 x 4096 182 -> 28.7 us, 777 x 1544 x 2200
+// 33 x 4096 x 11008 70.6 -> 12.2 us, 256 x 11008 x 4096 182 -> 28.1 us, 777 x 1544 x 2200
 // 34.6 -> 10.9 us, 2048^3 42.5 -> 17.7 us, 2048 x 4096 x 4096 76 -> 48 us.
 //
 // The MFMA operands are swapped (D = B A^T): a lane then holds consecutive columns of one row of C
@@ -151,9 +151,59 @@ __device__ __forceinline__ float lane_float(float v, int k) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k & 63));
 }
 
+// Empty volatile asm: pins the source order of pure instructions without emitting code.
+__device__ __forceinline__ void pin(v4i& x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void pin(float& a, float& b) { asm volatile("" : "+v"(a), "+v"(b)); }
+
+// One unit: a 32 x 32 sub-tile of one k-block.  kPar: parity of the unit in the wavefront's sequence of
+// units.  Multiplies a with b into P[kPar] and folds the finished tile P[kPar ^ 1] of the unit before
+// it into `acc` with the scale f of that unit: per slot one MFMA, the two FMAs of the elements
+// converted in the slot before, two converts.  extra(n) adds slot n's loads.
+template <int kPar, class Extra>
+__device__ __forceinline__ void unit(v4i (&P)[2][4], const v4i (&b)[2][2], float (&acc)[16], const v4i (&a)[2][2],
+                                     float f, const Extra& extra) {
+  float T[2] = {0.0f, 0.0f};
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+    const int ks = n >> 2, q = n & 3, ch = q >> 1, rh = q & 1;
+    const v4i z = {0, 0, 0, 0};
+    P[kPar][q] = mfma16(b[ch][ks], a[rh][ks], ks ? P[kPar][q] : z);
+    extra(n);
+    pin(P[kPar][q]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (n > 0) {
+      acc[2 * n - 2] = __builtin_fmaf(T[0], f, acc[2 * n - 2]);
+      acc[2 * n - 1] = __builtin_fmaf(T[1], f, acc[2 * n - 1]);
+      pin(acc[2 * n - 2], acc[2 * n - 1]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    T[0] = (float)P[kPar ^ 1][n >> 1][2 * (n & 1)];
+    T[1] = (float)P[kPar ^ 1][n >> 1][2 * (n & 1) + 1];
+    pin(T[0], T[1]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  acc[14] = __builtin_fmaf(T[0], f, acc[14]);
+  acc[15] = __builtin_fmaf(T[1], f, acc[15]);
+  pin(acc[14], acc[15]);
+}
+
+// step(k + d, d, reload) for d in [kFrom, kTo) as long as k + d < end
+template <int kFrom, int kTo, class F>
+__device__ __forceinline__ void steps(int k, int end, F& step, bool reload) {
+  if constexpr (kFrom < kTo) {
+    if (k + kFrom < end) {
+      step(k + kFrom, std::integral_constant<int, kFrom>{}, reload);
+      steps<kFrom + 1, kTo>(k, end, step, reload);
+    }
+  }
+}
+
 // ---- one wavefront per 32 x 32 output tile, operands straight from global memory.  kD k-blocks are in
 // flight (32 registers each); the steps of a trip are straight-line code, so that the compiler's wait
-// for a k-block leaves the younger ones in flight.
+// for a k-block leaves the younger ones in flight.  A k-block's tile is folded under the next one's
+// MFMAs, which matters where a wavefront has its SIMD to itself: 33 x 11008 x 4096 23.3 -> 21.4 us, 64 x
+// 2048 x 2048 6.5 -> 6.1, 128 x 4096 x 4096 11.3 -> 10.7.  33 x 4096 x 11008 (12.2 us) reads its 45 MB of
+// weights at 4.6 TB/s.
 template <int kD>
 __global__ __launch_bounds__(64, 2) void gemm_wave_kernel(GemmParams p) {
   const int lane = threadIdx.x;
@@ -198,47 +248,48 @@ __global__ __launch_bounds__(64, 2) void gemm_wave_kernel(GemmParams p) {
       for (int ks = 0; ks < 2; ++ks)
         R[i][ks] = load16(as, ao, i * 256 + ks * 2048);
   };
-  auto fold = [&](const v4i (&a)[2][2], const v4i (&b)[2][2], float s) {
-    v4i P[4];
-    const v4i z = {0, 0, 0, 0};
+  v4i P[2][4];
+  auto fold = [&](const v4i (&t)[4], float f) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) P[q] = mfma16(b[q >> 1][0], a[q & 1][0], z);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) P[q] = mfma16(b[q >> 1][1], a[q & 1][1], P[q]);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[4 * q + r] = __builtin_fmaf((float)P[q][r], s, acc[4 * q + r]);
+    for (int e = 0; e < 16; ++e) acc[e] = __builtin_fmaf((float)t[e >> 2][e & 3], f, acc[e]);
   };
 
   if (nkb > 0) {
 #pragma unroll
     for (int d = 0; d < kD; ++d) load_main(d, A[d], B[d]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) P[1][q] = v4i{0, 0, 0, 0};
+    float sp = 0.0f;      // scale of the unit whose tile is still to be folded
     for (int k0 = 0; k0 < nkb; k0 += 64) {
       const KLane kl = load_klane(p, ib, jb, k0, lane);
       bad |= __ballot(kl.slot == -2) != 0;
       const int n = min(64, nkb - k0);
       int slot = lane_int(kl.slot, 0);
       if (slot >= 0) load_res(slot);
-      auto step = [&](int k, int d, bool reload) {
-        fold(A[d], B[d], lane_float(kl.s, k));
-        if (slot >= 0) fold(R, B[d], lane_float(kl.t, k));
+      auto step = [&](int k, auto d_c, bool reload) {
+        constexpr int d = decltype(d_c)::value, par = d & 1;
+        unit<par>(P, B[d], acc, A[d], sp, [](int) {});
+        sp = lane_float(kl.s, k);
+        if (slot >= 0) {
+          // the residual's tile takes the main one's place: fold that now
+          fold(P[par], sp);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) P[par][q] = mfma16(B[d][q >> 1][0], R[q & 1][0], v4i{0, 0, 0, 0});
+#pragma unroll
+          for (int q = 0; q < 4; ++q) P[par][q] = mfma16(B[d][q >> 1][1], R[q & 1][1], P[par][q]);
+          sp = lane_float(kl.t, k);
+        }
         if (reload) load_main(k0 + k + kD, A[d], B[d]);
         slot = k + 1 < n ? lane_int(kl.slot, k + 1) : -1;
         if (slot >= 0) load_res(slot);
       };
       int k = 0;
-      for (; k + kD <= n; k += kD) {
-#pragma unroll
-        for (int d = 0; d < kD; ++d) step(k + d, d, true);
-      }
+      for (; k + kD <= n; k += kD) steps<0, kD>(k, k + kD, step, true);
       // what is left is the end of the contraction (64 is a multiple of kD)
-#pragma unroll
-      for (int d = 0; d < kD - 1; ++d) {
-        if (k + d >= n) break;
-        step(k + d, d, false);
-      }
+      steps<0, kD - 1>(k, n, step, false);
     }
+    if (nkb & 1) fold(P[0], sp);
+    else fold(P[1], sp);
   }
   store_unit(p, acc, rg * 32, cg * 32, lane, bad);
 }
@@ -246,44 +297,13 @@ __global__ __launch_bounds__(64, 2) void gemm_wave_kernel(GemmParams p) {
 // ---- one workgroup of four wavefronts per output tile of 128 rows x 32 kWU columns, every wavefront 32
 // rows x kWU column groups ("units"), kWU = 2 or 4
 
-// Empty volatile asm: pins the source order of pure instructions without emitting code.
-__device__ __forceinline__ void pin(v4i& x) { asm volatile("" : "+v"(x)); }
-__device__ __forceinline__ void pin(float& a, float& b) { asm volatile("" : "+v"(a), "+v"(b)); }
-
-// One unit: the 32 x 32 sub-tile of one column group.  kPar: parity of the unit in the wavefront's
-// sequence of units.  Multiplies a with bq[kPar] into P[kPar], fetches the next unit's B operands
-// from b_next into bq[kPar ^ 1] and folds the finished tile P[kPar ^ 1] of the unit before it into
-// `acc` with the scale f of that unit: per slot one MFMA, the two FMAs of the elements converted in the
-// slot before, two converts.
+// A unit whose successor's B operands are fetched from LDS (b_next) into bq[kPar ^ 1].
 template <int kPar>
 __device__ __forceinline__ void tile_unit(v4i (&P)[2][4], v4i (&bq)[2][2][2], float (&acc)[16], const v4i (&a)[2][2],
                                           const int8_t* b_next, const int (&boff)[2], float f) {
-  float T[2] = {0.0f, 0.0f};
-#pragma unroll
-  for (int n = 0; n < 8; ++n) {
-    const int ks = n >> 2, q = n & 3, ch = q >> 1, rh = q & 1;
-    const v4i z = {0, 0, 0, 0};
-    P[kPar][q] = mfma16(bq[kPar][ch][ks], a[rh][ks], ks ? P[kPar][q] : z);
-    if (n < 4) {
-      const int ich = n >> 1, iks = n & 1;
-      bq[kPar ^ 1][ich][iks] = *reinterpret_cast<const v4i*>(b_next + boff[ich] + iks * 2048);
-    }
-    pin(P[kPar][q]);
-    __builtin_amdgcn_sched_barrier(0);
-    if (n > 0) {
-      acc[2 * n - 2] = __builtin_fmaf(T[0], f, acc[2 * n - 2]);
-      acc[2 * n - 1] = __builtin_fmaf(T[1], f, acc[2 * n - 1]);
-      pin(acc[2 * n - 2], acc[2 * n - 1]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    T[0] = (float)P[kPar ^ 1][n >> 1][2 * (n & 1)];
-    T[1] = (float)P[kPar ^ 1][n >> 1][2 * (n & 1) + 1];
-    pin(T[0], T[1]);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  acc[14] = __builtin_fmaf(T[0], f, acc[14]);
-  acc[15] = __builtin_fmaf(T[1], f, acc[15]);
-  pin(acc[14], acc[15]);
+  unit<kPar>(P, bq[kPar], acc, a, f, [&](int n) {
+    if (n < 4) bq[kPar ^ 1][n >> 1][n & 1] = *reinterpret_cast<const v4i*>(b_next + boff[n >> 1] + (n & 1) * 2048);
+  });
 }
 
 // Units [kFrom, kTo) of a wavefront with kWU units per k-block, every one with its
