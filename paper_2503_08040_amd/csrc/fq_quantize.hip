@@ -153,7 +153,7 @@ __device__ __forceinline__ void quantize_rows(const F& val, const Scale& s, u32x
     }
     codes[r][0] = pack_byte2(y[0], y[1], y[2], y[3]) ^ 0x80808080u;
     codes[r][1] = pack_byte2(y[4], y[5], y[6], y[7]) ^ 0x80808080u;
-    if (near[0] < 4) {
+    if (__builtin_expect(near[0] < 4, 0)) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         uint32_t w = 0;
@@ -217,26 +217,43 @@ __device__ __forceinline__ void copy_image(const int8_t* img, int8_t* dst) {
 }
 
 // Loads the thread's 4 x 8 values of block (bi, bk), zero outside the matrix.  p.vec_ok: rows are
-// 16-byte aligned.
+// 16-byte aligned.  Ragged and unaligned blocks load 16 bytes at 2-byte addresses, which the hardware
+// takes, from the nearest place where all 8 values exist, and shift; like that all four loads are in
+// flight together (with a branch per row each row's load was waited for before the next: four
+// round trips to memory).
 __device__ __forceinline__ void load_block(const QuantParams& p, int bi, int bk, v4i (&raw)[kRows]) {
   const int row = bi * kBlock + kRows * (threadIdx.x >> 4), col = bk * kBlock + kCols * (threadIdx.x & 15);
-  const uint16_t* src = p.x + (int64_t)row * p.ld + col;
   if ((bi + 1) * kBlock <= p.rows && (bk + 1) * kBlock <= p.cols && p.vec_ok) {
+    const uint16_t* src = p.x + (int64_t)row * p.ld + col;
 #pragma unroll
     for (int r = 0; r < kRows; ++r) raw[r] = *reinterpret_cast<const v4i*>(src + r * p.ld);
+  } else if (p.cols >= kCols) {
+    const int from = min(col, p.cols - kCols), gone = 16 * (col - from);     // bits shifted out
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+      __builtin_memcpy(&raw[r], p.x + (int64_t)min(row + r, p.rows - 1) * p.ld + from, 16);
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      uint64_t v[2];
+      __builtin_memcpy(v, &raw[r], 16);
+      if (gone >= 64) {
+        v[0] = gone < 128 ? v[1] >> (gone & 63) : 0;
+        v[1] = 0;
+      } else if (gone > 0) {
+        v[0] = (v[0] >> gone) | (v[1] << (64 - gone));
+        v[1] >>= gone;
+      }
+      if (row + r >= p.rows) v[0] = v[1] = 0;
+      __builtin_memcpy(&raw[r], v, 16);
+    }
   } else {
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {
       raw[r] = v4i{0, 0, 0, 0};
-      if (row + r >= p.rows) continue;
-      if (col + kCols <= p.cols) {
-        // rows of any alignment: the hardware takes 16-byte loads at 2-byte addresses
-        __builtin_memcpy(&raw[r], src + r * p.ld, 16);
-      } else {
 #pragma unroll
-        for (int e = 0; e < kCols; ++e)
-          if (col + e < p.cols) raw[r][e >> 1] |= (int)((uint32_t)src[r * p.ld + e] << (16 * (e & 1)));
-      }
+      for (int e = 0; e < kCols; ++e)
+        if (row + r < p.rows && col + e < p.cols)
+          raw[r][e >> 1] |= (int)((uint32_t)p.x[(int64_t)(row + r) * p.ld + col + e] << (16 * (e & 1)));
     }
   }
 }
@@ -399,6 +416,7 @@ void quantize_kernel(QuantParams p) {
   __shared__ uint32_t red[2][kWaves];
   __shared__ double redd[kErr ? 2 * kWaves : 1];
   __shared__ int slot_sh, last_sh, scan_base_sh;
+  __shared__ uint32_t flags_sh;
   __shared__ int scan_sh[kWaves];
   __shared__ __attribute__((aligned(16))) int8_t img[kBlockBytes];
   __shared__ __attribute__((aligned(16))) int8_t img_t[kWantT ? kBlockBytes : 16];
@@ -498,9 +516,17 @@ void quantize_kernel(QuantParams p) {
       const int groups = (nb + 31) >> 5;
       if (decided == full) last = groups == 1 || atomicAdd(p.fb_groups_done, 1) == groups - 1;
       last_sh = last;
+      flags_sh = (uint32_t)(group_before >> 32) | (u ? 1u << (blk & 31) : 0u);
     }
     __syncthreads();
-    if (last_sh) {      // uniform over the workgroup
+    if (!last_sh) return;          // uniform over the workgroup
+    if (gridDim.x <= 32) {
+      // one group: its flags came back with the OR that completed it
+      const uint32_t f = flags_sh;
+      const int pos = __popc(f & ((1u << (t & 31)) - 1u));
+      if (t < 32 && (f >> t & 1u) && pos < p.capacity) p.fb_list[pos] = t;
+      if (t == 0) __hip_atomic_store(p.fb_words, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
       write_fb_list(p.fb_words, (int)gridDim.x, p.capacity, p.fb_list, scan_sh, &scan_base_sh);
       if (t == 0) *p.fb_groups_done = 0;    // ready for the next call
     }
