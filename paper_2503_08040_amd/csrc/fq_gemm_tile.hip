@@ -132,18 +132,33 @@ __device__ __forceinline__ int xcd_run(int b, int total) {
 
 }  // namespace
 
-// Scales and residual slots of 64 consecutive k-blocks, one per lane: the main and the residual scale
-// product and the slot of block (ib, k0 + lane).  Read back with v_readlane, they cost the k-loop no
-// scalar loads, whose unordered counter would wait for the youngest of them at every use.
-struct KLane { float s, t; int slot; };
+// Scales and residual slots of 64 consecutive k-blocks, one per lane: main scale product, scale of B,
+// residual scale and slot of block (ib, k0 + lane).  Read back with v_readlane, they cost the k-loop no
+// scalar loads, whose unordered counter would wait for the youngest of them at every use.  Loaded in
+// two steps because the residual scales depend on the slots.
+struct KFirst {
+  float sa, sb;
+  int slot;
+};
+struct KLane {
+  float s, sb, rs;
+  int slot;
+};
 
-__device__ __forceinline__ KLane load_klane(const GemmParams& p, int ib, int jb, int k0, int lane) {
+__device__ __forceinline__ KFirst load_first(const GemmParams& p, int ib, int jb, int k0, int lane) {
   const int k = min(k0 + lane, p.nkb - 1);
-  KLane r;
+  KFirst r;
   r.slot = p.a_slot ? p.a_slot[ib * p.a_si + k * p.a_sk] : -1;
-  const float sb = p.b_scales[jb * p.b_sj + k * p.b_sk];
-  r.s = p.a_scales[ib * p.a_si + k * p.a_sk] * sb;
-  r.t = p.a_slot ? p.a_res_scales[max(r.slot, 0)] * sb : 0.0f;
+  r.sb = p.b_scales[jb * p.b_sj + k * p.b_sk];
+  r.sa = p.a_scales[ib * p.a_si + k * p.a_sk];
+  return r;
+}
+__device__ __forceinline__ KLane finish(const GemmParams& p, const KFirst& f) {
+  KLane r;
+  r.rs = p.a_slot ? p.a_res_scales[max(f.slot, 0)] : 0.0f;
+  r.s = f.sa * f.sb;
+  r.sb = f.sb;
+  r.slot = f.slot;
   return r;
 }
 __device__ __forceinline__ int lane_int(int v, int k) { return __builtin_amdgcn_readlane(v, k & 63); }
@@ -255,13 +270,16 @@ __global__ __launch_bounds__(64, 2) void gemm_wave_kernel(GemmParams p) {
   };
 
   if (nkb > 0) {
+    // the first k-blocks' scales are requested in front of the operands: loads return in order, and
+    // the residual scales take a second trip
+    const KFirst first = load_first(p, ib, jb, 0, lane);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int d = 0; d < kD; ++d) load_main(d, A[d], B[d]);
 #pragma unroll
     for (int q = 0; q < 4; ++q) P[1][q] = v4i{0, 0, 0, 0};
     float sp = 0.0f;      // scale of the unit whose tile is still to be folded
-    for (int k0 = 0; k0 < nkb; k0 += 64) {
-      const KLane kl = load_klane(p, ib, jb, k0, lane);
+    auto chunk = [&](const KLane& kl, int k0) {
       bad |= __ballot(kl.slot == -2) != 0;
       const int n = min(64, nkb - k0);
       int slot = lane_int(kl.slot, 0);
@@ -277,7 +295,7 @@ __global__ __launch_bounds__(64, 2) void gemm_wave_kernel(GemmParams p) {
           for (int q = 0; q < 4; ++q) P[par][q] = mfma16(B[d][q >> 1][0], R[q & 1][0], v4i{0, 0, 0, 0});
 #pragma unroll
           for (int q = 0; q < 4; ++q) P[par][q] = mfma16(B[d][q >> 1][1], R[q & 1][1], P[par][q]);
-          sp = lane_float(kl.t, k);
+          sp = lane_float(kl.rs, k) * lane_float(kl.sb, k);
         }
         if (reload) load_main(k0 + k + kD, A[d], B[d]);
         slot = k + 1 < n ? lane_int(kl.slot, k + 1) : -1;
@@ -287,7 +305,9 @@ __global__ __launch_bounds__(64, 2) void gemm_wave_kernel(GemmParams p) {
       for (; k + kD <= n; k += kD) steps<0, kD>(k, k + kD, step, true);
       // what is left is the end of the contraction (64 is a multiple of kD)
       steps<0, kD - 1>(k, n, step, false);
-    }
+    };
+    chunk(finish(p, first), 0);
+    for (int k0 = 64; k0 < nkb; k0 += 64) chunk(finish(p, load_first(p, ib, jb, k0, lane)), k0);
     if (nkb & 1) fold(P[0], sp);
     else fold(P[1], sp);
   }
@@ -393,7 +413,8 @@ __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(GemmParams p
     for (int q = 0; q < 4; ++q) P[1][q] = v4i{0, 0, 0, 0};
     float sp = 0.0f;      // scale of the unit whose tile is still to be folded
     for (int k0 = 0; k0 < nkb; k0 += 64) {
-      const KLane kl = load_klane(p, ib, jb, k0, lane);
+      const KLane kl = finish(p, load_first(p, ib, jb, k0, lane));
+      const float residual_scales = kl.rs * kl.sb;
       bad |= __ballot(kl.slot == -2) != 0;
       const int kend = min(k0 + 64, nkb);
       // k-block k of parity j: its A operands are in A[j], its B blocks in LDS stage j
@@ -404,7 +425,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(GemmParams p
         load_a(abase + (int64_t)min(k + 1, nkb - 1) * kBlockBytes, A[j ^ 1]);
         if (slot >= 0) load_a(rbase + (int64_t)slot * kBlockBytes, R);
         float s = lane_float(kl.s, k);
-        const float t = lane_float(kl.t, k);
+        const float t = lane_float(residual_scales, k);
         const int8_t* const bs = lds + j * kStageBytes;
         tile_units<kWU, 0, kWU - 1>(P, bq, acc, a, bs, boff, s, sp);
         if (slot >= 0) {
