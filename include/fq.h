@@ -395,7 +395,9 @@ fq_status fq_gemm_plain(fq_op op, const fq_qtensor *A, const fq_qtensor *B, void
  * to a positive number (fq_gemm reads the same variable; meant for tuning and tests).  The
  * plan never changes results: every output element is accumulated in Alg. 1's order.
  * Outputs of less than about a chip's worth of these tiles are computed on smaller tiles instead
- * (32 x 32, 128 x 64 or 128 x 128, chosen by fq_gemm from the shape), with the same results.
+ * (32 x 32, 128 x 64 or 128 x 128, chosen by fq_gemm from the shape), with the same results, and
+ * where 128 x 384 tiles over the last block rows end earlier than over the last block columns,
+ * fq_gemm takes those instead of this plan.
  */
 fq_status fq_gemm_tile_plan(int32_t rows_out, int32_t cols_out, int32_t compute_units,
                             int32_t plan[3]);

@@ -813,17 +813,17 @@ __device__ __forceinline__ void tile_of(int b, int tiles_i, int tiles_j, int& ti
 
 }  // namespace
 
-// Grid: p.n_main workgroups compute 2 x 2-block tiles covering block columns [0, 2*main_tj),
-// the rest 1 x 3-block tiles covering block columns [2*main_tj, njb).
+// Grid: p.n_main workgroups compute 2 x 2-block tiles covering block rows [0, 2*main_ti) and columns
+// [0, 2*main_tj), the rest 1 x 3-block tiles covering the columns or the rows that are left.
 __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmParams p) {
   extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
   int ti, tj;
   if ((int)blockIdx.x < p.n_main) {
-    tile_of(blockIdx.x, (p.nib + 1) >> 1, p.main_tj, ti, tj);
+    tile_of(blockIdx.x, p.main_ti, p.main_tj, ti, tj);
     tile_body<Geo<2, 2>, false>(p, 2 * ti, 2 * tj, lds);
   } else {
-    tile_of(blockIdx.x - p.n_main, p.nib, p.tail_tj, ti, tj);
-    tile_body<Geo<1, 3>, false>(p, ti, 2 * p.main_tj + 3 * tj, lds);
+    tile_of(blockIdx.x - p.n_main, p.tail_ni, p.tail_tj, ti, tj);
+    tile_body<Geo<1, 3>, false>(p, p.tail_i0 + ti, p.tail_j0 + 3 * tj, lds);
   }
 }
 
@@ -839,11 +839,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_biased_kernel(GemmParams p) 
   extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
   int ti, tj;
   if ((int)blockIdx.x < p.n_main) {
-    tile_of(blockIdx.x, (p.nib + 1) >> 1, p.main_tj, ti, tj);
+    tile_of(blockIdx.x, p.main_ti, p.main_tj, ti, tj);
     tile_body<Geo<2, 2>, true>(p, 2 * ti, 2 * tj, lds);
   } else {
-    tile_of(blockIdx.x - p.n_main, p.nib, p.tail_tj, ti, tj);
-    tile_body<Geo<1, 3>, true>(p, ti, 2 * p.main_tj + 3 * tj, lds);
+    tile_of(blockIdx.x - p.n_main, p.tail_ni, p.tail_tj, ti, tj);
+    tile_body<Geo<1, 3>, true>(p, p.tail_i0 + ti, p.tail_j0 + 3 * tj, lds);
   }
 }
 
@@ -886,9 +886,10 @@ __global__ __launch_bounds__(256) void partials_kernel(GemmParams p) {
 namespace {
 
 struct TilePlan {
-  int n_main;    // workgroups computing 2 x 2-block tiles
-  int main_tj;   // tile columns they cover (block columns [0, 2*main_tj))
-  int tail_tj;   // 1 x 3-block tile columns covering the remaining block columns
+  int n_main;    // workgroups computing 2 x 2-block tiles: main_ti x main_tj of them, over the block
+  int main_ti, main_tj;      // rows [0, 2*main_ti) and columns [0, 2*main_tj)
+  int tail_i0, tail_ni, tail_j0, tail_tj;    // 1 x 3-block tiles: tail_ni rows from block row tail_i0,
+                                             // tail_tj tile columns from block column tail_j0
   double cost;   // rounds of the chip, in units of one 2 x 2 tile per compute unit
 };
 
@@ -896,11 +897,11 @@ struct TilePlan {
 // chip mostly idle: then the last block columns are cut into 1 x 3-block tiles (3/4 of the work
 // of a 2 x 2 tile each) so that the final round is shorter.  Costs are in units of one 2 x 2
 // tile per compute unit.
-TilePlan plan_tiles(int nib, int njb, int cus) {
+TilePlan plan_columns(int nib, int njb, int cus) {
   const int tiles_i = (nib + 1) / 2, tiles_j = (njb + 1) / 2;
   const int total = tiles_i * tiles_j;
   const double cost_all = cus > 0 ? (total + cus - 1) / cus : 1;
-  const TilePlan all{total, tiles_j, 0, cost_all};
+  const TilePlan all{total, tiles_i, tiles_j, 0, nib, njb, 0, cost_all};
   if (cus <= 0 || total <= cus || total % cus == 0) return all;
   const int rounds = total / cus;
   const int cm = std::min(tiles_j, rounds * cus / tiles_i);
@@ -909,8 +910,26 @@ TilePlan plan_tiles(int nib, int njb, int cus) {
   const int tail_tj = (tail_cols + 2) / 3;
   const int n_tail = nib * tail_tj;
   const double cost_split = (cm * tiles_i + cus - 1) / cus + 0.75 * ((n_tail + cus - 1) / cus);
-  if (cost_split + 0.05 < cost_all) return TilePlan{cm * tiles_i, cm, tail_tj, cost_split};
+  if (cost_split + 0.05 < cost_all) return TilePlan{cm * tiles_i, tiles_i, cm, 0, nib, 2 * cm, tail_tj, cost_split};
   return all;
+}
+
+// The same with the last block rows instead of the last block columns where that ends earlier: what
+// columns leave over is a multiple of the (many) tile rows of a tall output, such as the weight
+// gradient of an up projection.  11008 x 4096: 688 tiles are three rounds, and ten of 32 block
+// columns of 86 rows are 344 1 x 3 tiles, two more rounds; 22 block rows of 32 columns are 242, one.
+// dW = 11008 x 4096 from K = 4096, binary32: ROWFIG.
+TilePlan plan_tiles(int nib, int njb, int cus) {
+  const TilePlan cols = plan_columns(nib, njb, cus);
+  const int tiles_i = (nib + 1) / 2, tiles_j = (njb + 1) / 2, total = tiles_i * tiles_j;
+  if (cus <= 0 || total <= cus || total % cus == 0) return cols;
+  const int rm = std::min(tiles_i, total / cus * cus / tiles_j);
+  const int tail_rows = nib - 2 * rm;
+  if (rm <= 0 || tail_rows <= 0) return cols;
+  const int tail_tj = (njb + 2) / 3;
+  const double cost = (rm * tiles_j + cus - 1) / cus + 0.75 * ((tail_rows * tail_tj + cus - 1) / cus);
+  if (cost + 0.05 < cols.cost) return TilePlan{rm * tiles_j, rm, tiles_j, 2 * rm, tail_rows, 0, tail_tj, cost};
+  return cols;
 }
 
 // Tile of fq_gemm_tile.hip for this output, or kNone: the tiles above.  Estimated nanoseconds per
@@ -970,7 +989,7 @@ int planning_cus() {
 }  // namespace
 
 void gemm_tile_plan(int nib, int njb, int cus, int out[3]) {
-  const TilePlan plan = plan_tiles(nib, njb, cus > 0 ? cus : planning_cus());
+  const TilePlan plan = plan_columns(nib, njb, cus > 0 ? cus : planning_cus());
   out[0] = plan.n_main;
   out[1] = plan.main_tj;
   out[2] = plan.tail_tj;
@@ -989,9 +1008,13 @@ hipError_t launch_gemm(const GemmParams& p_in, bool debug, hipStream_t st) {
   if (const SmallTile tile = plan_small(p.M, p.N, plan, cus); tile != SmallTile::kNone)
     return launch_gemm_small(p, tile, st);
   p.n_main = plan.n_main;
+  p.main_ti = plan.main_ti;
   p.main_tj = plan.main_tj;
+  p.tail_i0 = plan.tail_i0;
+  p.tail_ni = plan.tail_ni;
+  p.tail_j0 = plan.tail_j0;
   p.tail_tj = plan.tail_tj;
-  const int grid = plan.n_main + p.nib * plan.tail_tj;
+  const int grid = plan.n_main + plan.tail_ni * plan.tail_tj;
   // the kernel needs more dynamic LDS than the default limit: raise it once per device
   static std::atomic<bool> attr_set[kMaxDevices];
   int dev = 0;

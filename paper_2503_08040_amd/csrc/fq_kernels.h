@@ -55,7 +55,9 @@ struct GemmParams {
   int nib, njb, nkb;
   int out_bf16;
   int vec_ok;                 // C base and row pitch allow 16-byte stores
-  int n_main, main_tj, tail_tj;   // tile plan, filled in by launch_gemm
+  // tile plan, filled in by launch_gemm: main tiles, their rows and columns; block rows of the tail, its
+  // first block row and block column, its tile columns
+  int n_main, main_ti, main_tj, tail_ni, tail_i0, tail_j0, tail_tj;
   int group;                  // quantization group edge (128, 64, 32)
   int a_ni, a_nk, b_nj;       // extents of the scale grids along i, k (A) and j (B), in groups
   int biased;                 // tolerance variant: biased INT32 accumulation (gemm_biased_kernel)
