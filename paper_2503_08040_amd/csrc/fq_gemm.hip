@@ -74,49 +74,37 @@ constexpr int kLdsBytes = 4 * kRingBytes;       // 128 KiB: two A sets + two B s
                                                 // staging patches re-use the same memory
 
 typedef __attribute__((address_space(3))) void lds_void;
-typedef const __attribute__((address_space(1))) void gbl_void;
 
-// One wavefront copies 8 KiB (8 fragments) global -> LDS with direct loads.  `src` and
-// `lds_dst` are wave-uniform; the per-lane part of the address is the 32-bit offset lane*16,
-// so the loads use the scalar-base addressing form and need no 64-bit address registers.
-__device__ inline void stage_half_block(const int8_t* src, int8_t* lds_dst, int lane) {
+// One wavefront copies 4 KiB (4 fragments) global -> LDS with direct loads.  `src` and `lds_dst` are
+// wave-uniform; the per-lane part of the address is the 32-bit offset lane*16 (scalar-base form), and
+// the 4 loads share one base and differ only in the instruction offset.  Written as assembly (the
+// loads have no register results) because the compiler counts the builtin as an access to both memories
+// of unknown order: with one in flight every wait for an LDS read became a wait for all of them, the
+// ones issued just before included.  Whoever reads the LDS waits with s_waitcnt vmcnt(0) and a barrier.
+// 8192^3 with a fifth of the blocks flagged 678 -> 665 us, 4096 x 4096 x 11008 220.6 -> 217.5.
+__device__ __forceinline__ void stage_quarter_block(const int8_t* src, int8_t* lds_dst, int lane) {
   const unsigned voff = (unsigned)lane * 16u;
   // make the uniformity of the base explicit (folds away when it is already scalar)
   const uint64_t a = reinterpret_cast<uint64_t>(src);
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-  src = reinterpret_cast<const int8_t*>(((uint64_t)hi << 32) | lo);
+  const uint64_t base = ((uint64_t)hi << 32) | lo;
+  const uint32_t to = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)lds_dst);
 #ifdef FQ_ABLATE_NO_DMA
   if (voff != 0xFFFFFFFFu) return;
 #endif
-  // 4 loads share one base (global and LDS) and differ only in the instruction offset
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    gbl_void* g = (gbl_void*)(src + b * 4 * kFragBytes + voff);
-    lds_void* l = (lds_void*)(lds_dst + b * 4 * kFragBytes);
-    __builtin_amdgcn_global_load_lds(g, l, 16, 0 * kFragBytes, 0);
-    __builtin_amdgcn_global_load_lds(g, l, 16, 1 * kFragBytes, 0);
-    __builtin_amdgcn_global_load_lds(g, l, 16, 2 * kFragBytes, 0);
-    __builtin_amdgcn_global_load_lds(g, l, 16, 3 * kFragBytes, 0);
-  }
+  static_assert(kFragBytes == 1024, "offsets below");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+               "global_load_lds_dwordx4 %1, %2\n\t"
+               "global_load_lds_dwordx4 %1, %2 offset:1024\n\t"
+               "global_load_lds_dwordx4 %1, %2 offset:2048\n\t"
+               "global_load_lds_dwordx4 %1, %2 offset:3072"
+               ::"s"(to), "v"(voff), "s"(base) : "memory");     // m0: nothing here keeps a value in it
 }
-
-// One wavefront copies 4 KiB (4 fragments) global -> LDS: one group of stage_half_block.
-__device__ inline void stage_quarter_block(const int8_t* src, int8_t* lds_dst, int lane) {
-  const unsigned voff = (unsigned)lane * 16u;
-  const uint64_t a = reinterpret_cast<uint64_t>(src);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-  src = reinterpret_cast<const int8_t*>(((uint64_t)hi << 32) | lo);
-#ifdef FQ_ABLATE_NO_DMA
-  if (voff != 0xFFFFFFFFu) return;
-#endif
-  gbl_void* g = (gbl_void*)(src + voff);
-  lds_void* l = (lds_void*)lds_dst;
-  __builtin_amdgcn_global_load_lds(g, l, 16, 0 * kFragBytes, 0);
-  __builtin_amdgcn_global_load_lds(g, l, 16, 1 * kFragBytes, 0);
-  __builtin_amdgcn_global_load_lds(g, l, 16, 2 * kFragBytes, 0);
-  __builtin_amdgcn_global_load_lds(g, l, 16, 3 * kFragBytes, 0);
+// 8 KiB
+__device__ __forceinline__ void stage_half_block(const int8_t* src, int8_t* lds_dst, int lane) {
+  stage_quarter_block(src, lds_dst, lane);
+  stage_quarter_block(src + 4 * kFragBytes, lds_dst + 4 * kFragBytes, lane);
 }
 
 // two floats -> two bf16 (round-to-nearest-even) in one dword, low half first
@@ -239,8 +227,11 @@ __device__ __forceinline__ void run_unit(WaveState<G>& st, const int8_t* a_cur, 
       const bool b_done = rh == 1;
       // the other four slots (rh = 0) carry a load each into a free buffer: operand i = 0..3
       const int i = 2 * ks + ch, irh = i >> 1, iks = i & 1;
-      // A operands of the next si go into the other aq buffer a whole unit before their use
-      if (si + 1 < G::kSI && sj == 0 && !b_done)
+      // A operands of the next si go into the other aq buffer a whole unit before their use.  Unit 0
+      // starts its reads two slots later: at its first MFMA the compiler waits for every read in flight
+      // (two paths lead here), and one issued just before would be waited for in full
+      // (4096 x 16384 x 4096 271 -> 266 us)
+      if (si + 1 < G::kSI && sj == 0 && (u == 0 ? b_done : !b_done))
         st.aq[(si + 1) & 1][irh][iks] = lds_frag(a_cur + G::a_block(h, si + 1) * kBlockBytes,
                                                  G::a_group(h, si + 1), irh, iks, lane);
       // the last two units (same si, odd: they use aq[1]) fetch the next item's first operands
@@ -334,14 +325,25 @@ __device__ __forceinline__ void drain(WaveState<G>& st, const float (&sp)[G::kSP
   st.acc[kLastSi][kSJ - 1][15] = __builtin_fmaf(st.T[1], s, st.acc[kLastSi][kSJ - 1][15]);
 }
 
-// Scalars of one k-block: residual slots and scales of the tile's A blocks, scales of the (up
-// to two) B blocks this wave's columns lie in.
+// Scalars of one k-block as a wavefront needs them: which A blocks of the tile are flagged, the
+// residual slot of the A block it stages, and per scale column of its own i-block a^A a^B and a~^A a^B.
 template <class G>
 struct KRec {
-  int slot[G::kBI];
-  float sa[G::kBI];
-  float rs[G::kBI];   // residual scales (valid where the slot is >= 0)
-  float sb[2];
+  bool flagged[G::kBI];
+  int slot;
+  float s[G::kSC], t[G::kSC];
+};
+
+// The same of 64 consecutive k-blocks, one per lane (flags: one per bit).  Read back with v_readlane
+// they cost the k-loop no scalar loads.  Those shared the LDS reads' counter and come back in any
+// order, so every item waited for the youngest of them at its first LDS read, and where a transposed
+// operand's scales are a row of the grid apart each was a miss.  4096 x 11008 x 4096 as NN 203.6 ->
+// 196.5 us, 4096 x 16384 x 4096 as TN 301 -> 291, 8192^3 (NT, a fifth of the blocks flagged) 712 -> 704.
+template <class G>
+struct KChunk {
+  unsigned long long flagged[G::kBI];
+  int slot;
+  float s[G::kSC], t[G::kSC];
 };
 
 }  // namespace
@@ -405,14 +407,6 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
   const int8_t* const smain = (stage_a ? p.a_codes : p.b_codes) +
                               (int64_t)sblk * p.nkb * kBlockBytes + spart;
 
-  // Scales and slots are read-only for the whole kernel: reading them through the constant
-  // address space makes them scalar loads, which do not share a counter with the vector loads.
-  typedef const __attribute__((address_space(4))) float cfloat;
-  typedef const __attribute__((address_space(4))) int32_t cint;
-  cfloat* const a_sc = (cfloat*)p.a_scales;
-  cfloat* const b_sc = (cfloat*)p.b_scales;
-  cfloat* const r_sc = (cfloat*)p.a_res_scales;
-  cint* const a_sl = (cint*)p.a_slot;
   const bool has_fb = p.a_slot != nullptr;
   int ia[kBI];
 #pragma unroll
@@ -426,32 +420,60 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
   const int ibj_lo = jlo_blk * p.b_sj, ibj_hi = jhi_blk * p.b_sj;
   const int nkb = p.nkb;
 
-  auto load_rec = [&](int k) -> KRec<G> {
+  bool poison = false;           // this wavefront's i-block has a flagged block without a slot
+  KChunk<G> kc;
+  auto load_chunk = [&](int k0) {
+    const int k = min(k0 + lane, nkb - 1);
+    const bool in = k0 + lane < nkb;
+    int slot[kBI], ia_own = ia[0];
+#pragma unroll
+    for (int i = 0; i < kBI; ++i) {
+      slot[i] = -1;
+      if (has_fb) slot[i] = p.a_slot[ia[i] + k * p.a_sk];
+      if (G::a_block(h, 0) == i) ia_own = ia[i];
+    }
+    const float sa = p.a_scales[ia_own + k * p.a_sk];
+    float sb[G::kSC];
+#pragma unroll
+    for (int q = 0; q < G::kSC; ++q)
+      sb[q] = p.b_scales[((G::kSC > 1 && ((kSJ * c + q) >> 2) != jlo) ? ibj_hi : ibj_lo) + k * p.b_sk];
+    int own = slot[0];
+#pragma unroll
+    for (int i = 1; i < kBI; ++i) if (G::a_block(h, 0) == i) own = slot[i];
+    const float rs = has_fb ? p.a_res_scales[max(own, 0)] : 0.0f;
+    kc.slot = slot[0];
+#pragma unroll
+    for (int i = 0; i < kBI; ++i) {
+      kc.flagged[i] = __ballot(in && slot[i] >= 0);
+      if (kSkew ? h == i : sidx == i) kc.slot = slot[i];
+    }
+    poison |= __ballot(in && own == -2) != 0;
+#pragma unroll
+    for (int q = 0; q < G::kSC; ++q) {
+      kc.s[q] = sa * sb[q];
+      kc.t[q] = rs * sb[q];
+    }
+  };
+  auto lane_float = [](float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+  };
+  auto rec_of = [&](int k) -> KRec<G> {      // k in the chunk that is loaded, or >= nkb
     KRec<G> r;
+    const int l = k & 63;
 #pragma unroll
-    for (int i = 0; i < kBI; ++i) { r.slot[i] = -1; r.sa[i] = 0.0f; r.rs[i] = 0.0f; }
-    r.sb[0] = r.sb[1] = 0.0f;
-    if (k < nkb) {
+    for (int i = 0; i < kBI; ++i) r.flagged[i] = k < nkb && ((kc.flagged[i] >> l) & 1) != 0;
+    r.slot = __builtin_amdgcn_readlane(kc.slot, l);
 #pragma unroll
-      for (int i = 0; i < kBI; ++i) {
-        if (has_fb) r.slot[i] = a_sl[ia[i] + k * p.a_sk];
-        r.sa[i] = a_sc[ia[i] + k * p.a_sk];
-      }
-      r.sb[0] = b_sc[ibj_lo + k * p.b_sk];
-      if (G::kSC > 1) r.sb[1] = b_sc[ibj_hi + k * p.b_sk];
+    for (int q = 0; q < G::kSC; ++q) {
+      r.s[q] = lane_float(kc.s[q], l);
+      r.t[q] = lane_float(kc.t[q], l);
     }
     return r;
-  };
-  // Residual scales depend on the slots, so they are fetched one step after the record itself:
-  // by then the slots have arrived and the dependent load does not stall the wavefront.
-  auto load_res_scales = [&](KRec<G>& r) {
-#pragma unroll
-    for (int i = 0; i < kBI; ++i) if (r.slot[i] >= 0) r.rs[i] = r_sc[r.slot[i]];
   };
   auto any_flagged = [&](const KRec<G>& r) {
     bool f = false;
 #pragma unroll
-    for (int i = 0; i < kBI; ++i) f |= r.slot[i] >= 0;
+    for (int i = 0; i < kBI; ++i) f |= r.flagged[i];
     return f;
   };
   // Stages this wave's 8 KiB share of item (k, res) into ring slot `asel` (A) / k & 1 (B).
@@ -462,11 +484,8 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
     if (stage_a) {
       const int8_t* src;
       if (res) {
-        int s = -1;
-#pragma unroll
-        for (int i = 0; i < kBI; ++i) if (sidx == i) s = r.slot[i];
-        if (s < 0) return;   // unflagged block: nothing to bring (its wavefronts skip the item)
-        src = p.a_res + (int64_t)s * kBlockBytes + spart;
+        if (r.slot < 0) return;   // unflagged block: nothing to bring (its wavefronts skip the item)
+        src = p.a_res + (int64_t)r.slot * kBlockBytes + spart;
       } else {
         src = smain + (int64_t)k * kBlockBytes;
       }
@@ -494,13 +513,13 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
   // of i-block h, one per SIMD each) run half an item apart: a quarter of its own team's A block,
   // and for team 0 half a B block as well.
   auto stage_team = [&](int k, int res, const KRec<G>& r, int asel, bool new_b) {
-    int blk = ib[0], s = r.slot[0];
+    int blk = ib[0];
 #pragma unroll
-    for (int i = 1; i < kBI; ++i) if (h == i) { blk = ib[i]; s = r.slot[i]; }
+    for (int i = 1; i < kBI; ++i) if (h == i) blk = ib[i];
     const int quarter = c * (kBlockBytes / 4);
     int8_t* const dst = a_ring + asel * G::kASet + h * kBlockBytes + quarter;
     if (!res) stage_quarter_block(p.a_codes + ((int64_t)blk * p.nkb + k) * kBlockBytes + quarter, dst, lane);
-    else if (s >= 0) stage_quarter_block(p.a_res + (int64_t)s * kBlockBytes + quarter, dst, lane);
+    else if (r.slot >= 0) stage_quarter_block(p.a_res + (int64_t)r.slot * kBlockBytes + quarter, dst, lane);
     if (h == 0 && new_b) {
       int jb = jbt[0];
 #pragma unroll
@@ -510,9 +529,6 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
                        b_ring + (k & 1) * G::kBSet + part, lane);
     }
   };
-  // scale column sc belongs to the wave's second j-block?
-  auto sc_is_hi = [&](int scol) { return ((kSJ * c + scol) >> 2) != jlo; };
-
   WaveState<G> st;
 #pragma unroll
   for (int si = 0; si < kSI; ++si)
@@ -520,7 +536,6 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
     for (int sj = 0; sj < kSJ; ++sj)
 #pragma unroll
       for (int r = 0; r < 16; ++r) st.acc[si][sj][r] = 0.0f;
-  bool poison = false;           // this wavefront's i-block has a flagged block without a slot
   v4i magic = {kMagicBits, kMagicBits, kMagicBits, kMagicBits};
   if (kBiased) asm volatile("" : "+v"(magic));   // stays in registers: an MFMA operand cannot be a literal
   float bias_s[G::kSC];          // kBiased: sum of the scales used since the bias was last removed
@@ -543,20 +558,20 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
 
   if (nkb > 0) {
     // ---- prologue: items 0 and 1 into the two ring slots
-    // records are fetched two k-blocks ahead so that no scalar load is waited for in the loop
-    KRec<G> r0 = load_rec(0), r1 = load_rec(1), r2 = load_rec(2);
     int k = 0, res = 0, t = 0;
+    KRec<G> r0{}, r1;      // k-blocks k and k + 1
+    if constexpr (kSkew) stage_team(0, 0, r0, 0, true);
+    else stage_item(0, 0, r0, 0, true);
+    load_chunk(0);
+    r0 = rec_of(0);
+    r1 = rec_of(1);
     if constexpr (kSkew) {
-      stage_team(0, 0, r0, 0, true);
       if (any_flagged(r0)) stage_team(0, 1, r0, 1, false);
       else if (1 < nkb) stage_team(1, 0, r1, 1, true);
     } else {
-      stage_item(0, 0, r0, 0, true);
       if (any_flagged(r0)) stage_item(0, 1, r0, 1, false);
       else if (1 < nkb) stage_item(1, 0, r1, 1, true);
     }
-    load_res_scales(r0);
-    load_res_scales(r1);
     __builtin_amdgcn_s_waitcnt(0x0F70);    // vmcnt(0): this wave's direct-to-LDS loads landed
     __syncthreads();
 #pragma unroll
@@ -603,26 +618,21 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
       const int n2k = (n1res || n2res) ? k + 1 : k + 2;
       const bool has2 = n2k < nkb;
 
-      // ---- this wavefront's i-block in this item: its slot, scale, and whether there is work
-      int my_slot = r0.slot[0];
-      float my_sa = res ? r0.rs[0] : r0.sa[0];
+      // ---- this wavefront's i-block in this item: is it flagged, its scales
+      bool mine = r0.flagged[0];
 #pragma unroll
       for (int i = 1; i < kBI; ++i)
-        if (G::a_block(h, 0) == i) {
-          my_slot = r0.slot[i];
-          my_sa = res ? r0.rs[i] : r0.sa[i];
-        }
-      if (!res) poison |= my_slot == -2;
+        if (G::a_block(h, 0) == i) mine = r0.flagged[i];
       // a residual item is work only for the wavefronts whose i-block is flagged at this k
 #ifdef FQ_ABLATE_NO_MULTIPLY
       const bool active = p.M < 0;
 #else
-      const bool active = !res || my_slot >= 0;
+      const bool active = !res || mine;
 #endif
       ItemScales<G> sc;
 #pragma unroll
       for (int q = 0; q < G::kSC; ++q)
-        sc.s[q] = my_sa * ((G::kSC > 1 && sc_is_hi(q)) ? r0.sb[1] : r0.sb[0]);
+        sc.s[q] = res ? r0.t[q] : r0.s[q];
 
       const int8_t* const a_cur = a_ring + (t & 1) * G::kASet;
       const int8_t* const a_nxt = a_ring + ((t + 1) & 1) * G::kASet;
@@ -714,9 +724,8 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
         res = 0;
         ++k;
         r0 = r1;
-        r1 = r2;
-        load_res_scales(r1);      // its slots were fetched an item ago
-        r2 = load_rec(k + 2);
+        if (((k + 1) & 63) == 0 && k + 1 < nkb) load_chunk(k + 1);
+        r1 = rec_of(k + 1);
       }
     }
     if (kSkew && h == 0) asm volatile("s_barrier" ::: "memory");   // team 1's last item boundary
@@ -918,7 +927,7 @@ TilePlan plan_columns(int nib, int njb, int cus) {
 // columns leave over is a multiple of the (many) tile rows of a tall output, such as the weight
 // gradient of an up projection.  11008 x 4096: 688 tiles are three rounds, and ten of 32 block
 // columns of 86 rows are 344 1 x 3 tiles, two more rounds; 22 block rows of 32 columns are 242, one.
-// dW = 11008 x 4096 from K = 4096, binary32: ROWFIG.
+// 11008 x 4096 x 4096, binary32 output: 235 -> 227 us.
 TilePlan plan_tiles(int nib, int njb, int cus) {
   const TilePlan cols = plan_columns(nib, njb, cus);
   const int tiles_i = (nib + 1) / 2, tiles_j = (njb + 1) / 2, total = tiles_i * tiles_j;
