@@ -13,8 +13,8 @@
 //     accumulators per lane in architectural VGPRs (the vector ALU cannot read
 //     accumulation registers, so the accumulators it updates must not live
 //     there).  A second geometry, 1 x 3 blocks (128 x 384, 2 x 3 sub-tiles per
-//     wavefront), covers the last block columns when the 2 x 2 tiles would
-//     leave the final round of the chip mostly idle;
+//     wavefront), covers the last block columns or rows when the 2 x 2 tiles
+//     would leave the final round of the chip mostly idle;
 //   - the k-loop runs over "items": the main product of k-block k and, when
 //     one of the tile's A blocks is flagged at k, a residual item right
 //     after it.  A and B operands sit in two independent double-buffered LDS
