@@ -270,6 +270,26 @@ __device__ __forceinline__ uint32_t thread_absmax(const v4i (&raw)[kRows]) {
   return (uint32_t)(m[0] > m[1] ? m[0] : m[1]) << 16;
 }
 
+// max |G| of the block.  NaNs, which are larger than everything as integers, do not count: where there
+// are any (uniform over the workgroup) the maximum of the others is taken.  red, red2: kWaves words each.
+__device__ __forceinline__ float block_absmax(const v4i (&raw)[kRows], uint32_t* red, uint32_t* red2) {
+  float m = block_max(thread_absmax(raw), red);
+  if (__builtin_expect(__float_as_uint(m) > 0x7F800000u, 0)) {
+    uint32_t v = 0;
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+#pragma unroll
+      for (int e = 0; e < kCols; ++e) {
+        const uint32_t b = __float_as_uint(x_at(raw, r, e)) & 0x7FFFFFFFu;
+        v = max(v, b > 0x7F800000u ? 0u : b);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    m = block_max(v, red2);
+  }
+  return m;
+}
+
 // The bits block b contributes to its group's word: "decided" and, if u, "flagged".
 __device__ inline unsigned long long my_bits(int b, bool u) {
   return (1ull << (b & 31)) | ((u ? 1ull : 0ull) << (32 + (b & 31)));
@@ -430,7 +450,7 @@ void quantize_kernel(QuantParams p) {
   load_block(p, bi, bk, raw);
 
   // ---- step 1: a = max|G| / 127, codes = round(G / a)           (Sec. 3.1)
-  const float amax = block_max(thread_absmax(raw), red[0]);
+  const float amax = block_absmax(raw, red[0], red[1]);
   const Scale sc = make_scale(amax);
   const float a = sc.a;
   forget_unpacked(raw);
@@ -595,12 +615,12 @@ void quantize_kernel(QuantParams p) {
 // max |G| of each block into amax[nbr * nbc] (the tensor's scale array serves as that buffer
 // until quantize_kernel overwrites it with the scales).
 __global__ __launch_bounds__(kThreads, 8) void block_absmax_kernel(QuantParams p) {
-  __shared__ uint32_t red[kWaves];
+  __shared__ uint32_t red[2][kWaves];
   const int blk = blockIdx.x;
   const int bi = blk / p.nbc, bk = blk - bi * p.nbc;
   v4i raw[kRows];
   load_block(p, bi, bk, raw);
-  const float amax = block_max(thread_absmax(raw), red);
+  const float amax = block_absmax(raw, red[0], red[1]);
   if (threadIdx.x == 0) p.scales[blk] = amax;
 }
 
