@@ -159,7 +159,9 @@ __device__ __forceinline__ void quantize_rows(const F& val, const Scale& s, u32x
         uint32_t w = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float k = fminf(fmaxf(rintf(__fdiv_rn(val(r, 4 * h + e), s.a)), -127.0f), 127.0f);
+          // a NaN in a block whose scale is 0 comes here too: its neighbours keep code 0
+          const float t = s.a == 0.0f ? 0.0f : __fdiv_rn(val(r, 4 * h + e), s.a);
+          const float k = fminf(fmaxf(rintf(t), -127.0f), 127.0f);
           w |= ((uint32_t)(int)k & 0xFFu) << (8 * e);
           __builtin_amdgcn_sched_barrier(0);
         }

@@ -32,3 +32,33 @@ def test_nan_does_not_enter_the_scale(rows, cols):
     assert np.array_equal(s.view("scales").cpu().numpy(), o.scales)
     t = fq.fq_quantize_topk(gu.to_device_bf16(bits), 2)
     assert np.array_equal(t.view("mask").cpu().numpy(), g.view("mask").cpu().numpy())
+
+
+def test_codes_beside_a_nan():
+    """A NaN leaves the codes of every other value of its block as they are without it, also where the
+    block's scale, or the scale of its residual, is zero (codes 0: nothing is divided)."""
+    rng = np.random.default_rng(8)
+    rows, cols = 256, 380
+    x = rng.standard_normal((rows, cols)).astype(np.float32)
+    x[:128, :128] = 0.0                                              # scale 0
+    x[:128, 128:256] = rng.integers(-127, 128, size=(128, 128))      # scale 1, residual scale 0
+    x[0, 128] = 127.0
+    x[128:, 256:] = 0.0                                              # scale 0 in a ragged block
+    bits = synth.to_bf16_bits(x)
+    for r, c in ((3, 5), (77, 127), (9, 130), (100, 255), (40, 300), (41, 379), (130, 17), (200, 379), (255, 256)):
+        bits[r, c] = 0x7FC0 if c & 1 else 0xFF81
+    fine = (bits & 0x7FFF) <= 0x7F80
+    o = fqo.quantize(bits, 128, fqo.CRIT_ALL, 0.0)
+    assert o.scales[0, 0] == 0 and o.scales[1, 2] == 0 and o.scales[0, 1] == 1 and o.res_scales[0, 1] == 0
+    gu.announce("codes beside a NaN")
+    g = fq.fq_quantize(gu.to_device_bf16(bits), fq.FQ_CRIT_ALL, 0.0, want_transposed=True)
+    assert np.array_equal(g.view("scales").cpu().numpy(), o.scales)
+    assert np.array_equal(gu.untile(g.view("codes").cpu().numpy(), rows, cols)[0][fine], o.codes[fine])
+    assert np.array_equal(gu.untile(g.view("codes_t").cpu().numpy(), cols, rows)[0].T[fine], o.codes[fine])
+    slot, rsc = g.view("fb_slot").cpu().numpy(), g.view("res_scales").cpu().numpy()
+    assert np.array_equal(rsc[slot], o.res_scales)
+    res = gu.untile(g.view("res_codes").cpu().numpy()[slot.ravel()], rows, cols)[0]
+    assert np.array_equal(res[fine], o.res_codes[fine])
+    s = fq.fq_quantize_sr(gu.to_device_bf16(bits), 11)
+    so = fqo.quantize_sr(bits, 128, 11)
+    assert np.array_equal(gu.untile(s.view("codes").cpu().numpy(), rows, cols)[0][fine], so.codes[fine])
