@@ -132,14 +132,33 @@ __device__ inline Scale make_scale(float amax) {
   return s;
 }
 
+// Exact quotient RN(x / a) without a division: r = RN(1 / a), and two residual corrections (the second
+// starts from a faithful quotient, which makes the result the correctly rounded one).  For a in
+// [2^-100, 2^100] and quotients of 2^-1 and more, which is what rounding to nearest needs.  A product of
+// quotient and scale below about 2^-103 leaves a residual that underflows, so at a = 2^-90, where the
+// stochastic rounding stops taking it, quotients below 2^-13 can be off by their last bit: over all pairs
+// of a bf16 value and a bf16 maximum this happens to 2 in 1000, and to none does it change which 24-bit
+// random numbers round up.
+__device__ __forceinline__ float exact_quotient(float x, float a, float r) {
+  float q = x * r;
+  q = __builtin_fmaf(__builtin_fmaf(-q, a, x), r, q);
+  return __builtin_fmaf(__builtin_fmaf(-q, a, x), r, q);
+}
+
 // codes[r] = rint(RN(x / a)) of the thread's values x = val(r, e), packed bytes, two's complement.
 // One fused multiply-add puts x / a + 128.5 into fixed point with 16 fraction bits (y): byte 2 is
 // the rounded quotient + 128, the low half says how far the quotient is from a half-integer.  In
 // units of 2^-16: the reciprocal is off by at most 0.5, the sum by 0.5, the binary32 rounding of the
-// true quotient by 0.25, so with 2 added to y a low half of 4 or more leaves no doubt.  Otherwise
-// (6 of 10^5 values, or r16 = NaN) the row is done again with the exact quotient, clamped: a
-// subnormal scale can be far from max/127.  4.75 vector instructions per value and no branch
-// but one per 8 values, where testing and branching per value took more than twice that.
+// true quotient by 0.25, so with 2 added to y a low half of 4 or more leaves no doubt.  Otherwise (or
+// with r16 = NaN) the row of 8 is done again with the exact quotient: 4.75 vector instructions per value
+// and no branch but one per 8 values, where testing and branching per value took more than twice that.
+// A doubt is no rare thing: quotients of bf16 values and a bf16 maximum lie on a coarse grid.  Of N(0, 1)
+// values 6 in 1000 are that near a half-integer, and half of a wavefront's rows hold one; where
+// the block's maximum is a power of two all do.  So the second time divides no more than it has to: a
+// scale that has a reciprocal takes two residual corrections per value (no rounded code depends on which of
+// the two it was, over all pairs of a bf16 value and a bf16 maximum), the others divide and clamp (a
+// subnormal scale can be far from max/127).  With 8 divisions 4096 x 4096 of N(0, 1) without fallback took
+// 14.4 instead of 11.8 us, 8192 x 8192 with every block flagged 83 instead of 74.5.
 template <class F>
 __device__ __forceinline__ void quantize_rows(const F& val, const Scale& s, u32x2 (&codes)[kRows]) {
 #pragma unroll
@@ -154,19 +173,23 @@ __device__ __forceinline__ void quantize_rows(const F& val, const Scale& s, u32x
     codes[r][0] = pack_byte2(y[0], y[1], y[2], y[3]) ^ 0x80808080u;
     codes[r][1] = pack_byte2(y[4], y[5], y[6], y[7]) ^ 0x80808080u;
     if (__builtin_expect(near[0] < 4, 0)) {
+      auto again = [&](const auto& quotient) {
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        uint32_t w = 0;
+        for (int h = 0; h < 2; ++h) {
+          uint32_t w = 0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          // a NaN in a block whose scale is 0 comes here too: its neighbours keep code 0
-          const float t = s.a == 0.0f ? 0.0f : __fdiv_rn(val(r, 4 * h + e), s.a);
-          const float k = fminf(fmaxf(rintf(t), -127.0f), 127.0f);
-          w |= ((uint32_t)(int)k & 0xFFu) << (8 * e);
-          __builtin_amdgcn_sched_barrier(0);
+          for (int e = 0; e < 4; ++e) {
+            const float k = fminf(fmaxf(rintf(quotient(val(r, 4 * h + e))), -127.0f), 127.0f);
+            w = __builtin_amdgcn_cvt_pk_u8_f32(k + 128.0f, e, w);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          codes[r][h] = w ^ 0x80808080u;
         }
-        codes[r][h] = w;
-      }
+      };
+      const float rcp = s.r16 * 0x1p-16f;     // RN(1 / a) again
+      if (s.r16 > 0.0f) again([&](float x) { return exact_quotient(x, s.a, rcp); });
+      // a scale of 0: a NaN comes here, its neighbours keep code 0
+      else again([&](float x) { return s.a == 0.0f ? 0.0f : __fdiv_rn(x, s.a); });
     }
     __builtin_amdgcn_sched_barrier(0);     // one row's temporaries at a time
   }
@@ -344,16 +367,6 @@ __device__ inline void write_fb_list(unsigned long long* words, int nb, int capa
   }
 }
 
-
-// Exact quotient RN(x / a) for the stochastic rounding: r = RN(1 / a), and two residual corrections
-// (the second starts from a faithful quotient, which makes the result the correctly rounded one).
-// For a in [2^-90, 2^90]; a residual that underflows belongs to a quotient below 2^-25, whose
-// last bits the comparison with a 24-bit random number does not see.
-__device__ __forceinline__ float exact_quotient(float x, float a, float r) {
-  float q = x * r;
-  q = __builtin_fmaf(__builtin_fmaf(-q, a, x), r, q);
-  return __builtin_fmaf(__builtin_fmaf(-q, a, x), r, q);
-}
 
 // floor(t) + [top 24 bits of w < fraction of t], clamped, + 128 as a float
 __device__ __forceinline__ float round_stochastic(float t, uint32_t w) {

@@ -171,3 +171,23 @@ def test_untile_matches_documented_layout():
     dense = fq.fq_codes_to_rowmajor(gq.view("codes"), 200, 300).cpu().numpy()
     want, _ = gu.untile(gq.view("codes").cpu().numpy(), 200, 300)
     assert np.array_equal(dense, want)
+
+
+def test_values_near_half_integers_and_the_scales_that_have_a_reciprocal():
+    """bf16 values over a bf16 maximum are often half-integers but for the rounding of the scale, so the
+    quotient has to be exact: blocks whose maximum has few mantissa bits, at scales on both sides of the
+    bounds 2^-100 and 2^100 of the reciprocal (127 * 2^k is the scale 2^k), and a ragged one."""
+    rng = np.random.default_rng(71)
+    tops = [1.0, 1.5, 1.25, 1.875, 127 / 64, 254 / 128, 1.0078125]
+    exps = [-102, -101, -100, -99, -94, -93, 0, 99, 100, 101, 105, 106, 107]
+    x = np.zeros((len(tops) * 128 - 40, len(exps) * 128 - 9), F32)
+    for i, m in enumerate(tops):
+        for j, k in enumerate(exps):
+            blk = x[i * 128:(i + 1) * 128, j * 128:(j + 1) * 128]
+            v = np.clip(rng.standard_normal(blk.shape) * 0.6, -m, m)
+            v[0, 0] = -m
+            # (n + 1/2) / 127 of the maximum
+            v[1] = np.resize((np.arange(-126, 127) + 0.5) / 127 * m, blk.shape[1])
+            blk[:] = v * 2.0 ** k
+    _, oq = _run(synth.to_bf16_bits(x), fq.FQ_CRIT_ALL, 0.0, label="near ties")
+    assert (oq.scales == F32(2.0 ** -100)).any() and (oq.scales == F32(2.0 ** 100)).any()
