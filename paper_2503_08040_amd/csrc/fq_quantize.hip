@@ -145,6 +145,14 @@ __device__ __forceinline__ float exact_quotient(float x, float a, float r) {
   return __builtin_fmaf(__builtin_fmaf(-q, a, x), r, q);
 }
 
+// The whole part of v, for 0 <= v < 2^32; 0 for a NaN.  The instruction is named because a C++
+// conversion leaves a NaN's result open, and quantize_rows finds its NaNs by that 0.
+__device__ __forceinline__ uint32_t whole_part(float v) {
+  uint32_t u;
+  asm("v_cvt_u32_f32 %0, %1" : "=v"(u) : "v"(v));
+  return u;
+}
+
 // codes[r] = rint(RN(x / a)) of the thread's values x = val(r, e), packed bytes, two's complement.
 // One fused multiply-add puts x / a + 128.5 into fixed point with 16 fraction bits (y): byte 2 is
 // the rounded quotient + 128, the low half says how far the quotient is from a half-integer.  In
@@ -167,7 +175,7 @@ __device__ __forceinline__ void quantize_rows(const F& val, const Scale& s, u32x
     u16x2 near = {0xFFFF, 0xFFFF};
 #pragma unroll
     for (int e = 0; e < kCols; ++e) {
-      y[e] = (uint32_t)__builtin_fmaf(val(r, e), s.r16, 128.5f * 65536.0f + 2.0f);
+      y[e] = whole_part(__builtin_fmaf(val(r, e), s.r16, 128.5f * 65536.0f + 2.0f));
       near = __builtin_elementwise_min(near, __builtin_bit_cast(u16x2, y[e]));
     }
     codes[r][0] = pack_byte2(y[0], y[1], y[2], y[3]) ^ 0x80808080u;
