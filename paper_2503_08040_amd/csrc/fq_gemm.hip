@@ -88,18 +88,24 @@ __device__ __forceinline__ void stage_quarter_block(const int8_t* src, int8_t* l
   const uint64_t a = reinterpret_cast<uint64_t>(src);
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-  const uint64_t base = ((uint64_t)hi << 32) | lo;
+  uint64_t base = ((uint64_t)hi << 32) | lo;
   const uint32_t to = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)lds_dst);
 #ifdef FQ_ABLATE_NO_DMA
   if (voff != 0xFFFFFFFFu) return;
 #endif
   static_assert(kFragBytes == 1024, "offsets below");
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-               "global_load_lds_dwordx4 %1, %2\n\t"
-               "global_load_lds_dwordx4 %1, %2 offset:1024\n\t"
-               "global_load_lds_dwordx4 %1, %2 offset:2048\n\t"
-               "global_load_lds_dwordx4 %1, %2 offset:3072"
-               ::"s"(to), "v"(voff), "s"(base) : "memory");     // m0: nothing here keeps a value in it
+  // The block keeps the wait states its loads need by itself, as the compiler does not look inside: the
+  // second move is the one between a write to m0 and its use, and leaves the base written by the scalar
+  // unit, whatever wrote it before (a vector instruction would have to be five wait states away).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"     // that m0 is a register nobody keeps values in is known
+  asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %0\n\t"
+               "global_load_lds_dwordx4 %2, %0\n\t"
+               "global_load_lds_dwordx4 %2, %0 offset:1024\n\t"
+               "global_load_lds_dwordx4 %2, %0 offset:2048\n\t"
+               "global_load_lds_dwordx4 %2, %0 offset:3072"
+               : "+s"(base) : "s"(to), "v"(voff) : "memory", "m0");
+#pragma clang diagnostic pop
 }
 // 8 KiB
 __device__ __forceinline__ void stage_half_block(const int8_t* src, int8_t* lds_dst, int lane) {
