@@ -366,8 +366,8 @@ fq_status fq_gemm(fq_op op, const fq_qtensor *A, const fq_qtensor *B, void *C,
  * every 4 items of the k-loop.  The FP32 additions therefore round at the magnitude of the biased
  * partial sums: the result differs from fq_gemm's by up to about 2e-4 of max |C| (measured; the
  * bound does not grow with K), inside the 1e-3 this library's outputs are held to, but it is not
- * the oracle's result bit for bit.  (Outputs that fq_gemm computes on smaller tiles are computed by
- * the same exact kernels here.)  fq_gemm stays the reference path.  Arguments and errors as fq_gemm.
+ * the oracle's result bit for bit.  (Small outputs, where fq_gemm's kernels for smaller tiles are
+ * faster than this one, are computed by those, bit for bit.)  fq_gemm stays the reference path.  Arguments and errors as fq_gemm.
  */
 fq_status fq_gemm_biased(fq_op op, const fq_qtensor *A, const fq_qtensor *B, void *C,
                          fq_out_dtype cdt, int64_t ldc, void *hip_stream);

@@ -102,6 +102,21 @@ def test_scale_range():
     _check(fq.FQ_OP_NT, ga, gb, oa, ob, "scale range")
 
 
+@pytest.mark.parametrize("shape,cus,own", [((256, 384), 2, True), ((500, 256), 3, True), ((256, 384), 256, False)])
+def test_smaller_tiles_only_where_they_beat_the_biased_kernel(shape, cus, own, monkeypatch):
+    """fq_gemm takes smaller tiles for all of these.  They are exact, so whether the variant ran its own
+    kernel shows in the bits: two large tiles on two compute units, two on three, two on the chip."""
+    monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
+    rng = np.random.default_rng(11)
+    a = rng.standard_normal((shape[0], 1300)).astype(F32)
+    b = rng.standard_normal((shape[1], 1300)).astype(F32)
+    ga, gb, oa, ob = _quant_pair(synth.to_bf16_bits(a), synth.to_bf16_bits(b), fq.FQ_CRIT_NONE, 0.0)
+    _check(fq.FQ_OP_NT, ga, gb, oa, ob, f"{shape} on {cus} compute units")
+    exact = fq.fq_gemm(fq.FQ_OP_NT, ga, gb)
+    assert np.array_equal(exact.cpu().numpy(), fqo.gemm(fqo.OP_NT, oa, ob))
+    assert torch.equal(fq.fq_gemm_biased(fq.FQ_OP_NT, ga, gb), exact) != own
+
+
 def test_rejects_small_groups_and_empty_cases():
     x = torch.randn((256, 256), device="cuda").to(torch.bfloat16)
     q64 = fq.fq_quantize(x, fq.FQ_CRIT_NONE, 0.0, capacity=0, block=64)
