@@ -366,8 +366,9 @@ fq_status fq_gemm(fq_op op, const fq_qtensor *A, const fq_qtensor *B, void *C,
  * every 4 items of the k-loop.  The FP32 additions therefore round at the magnitude of the biased
  * partial sums: the result differs from fq_gemm's by up to about 2e-4 of max |C| (measured; the
  * bound does not grow with K), inside the 1e-3 this library's outputs are held to, but it is not
- * the oracle's result bit for bit.  (Small outputs, where fq_gemm's kernels for smaller tiles are
- * faster than this one, are computed by those, bit for bit.)  fq_gemm stays the reference path.  Arguments and errors as fq_gemm.
+ * the oracle's result bit for bit.  (Outputs for which smaller tiles are faster, see fq_gemm_path, are
+ * computed by fq_gemm's exact kernels here too.)  fq_gemm stays the reference path.  Arguments
+ * and errors as fq_gemm.
  */
 fq_status fq_gemm_biased(fq_op op, const fq_qtensor *A, const fq_qtensor *B, void *C,
                          fq_out_dtype cdt, int64_t ldc, void *hip_stream);
@@ -385,22 +386,30 @@ fq_status fq_gemm_plain(fq_op op, const fq_qtensor *A, const fq_qtensor *B, void
                         fq_out_dtype cdt, int64_t ldc, void *hip_stream);
 
 /*
- * How fq_gemm cuts an rows_out x cols_out output into workgroup tiles (host-only inspection;
- * App. C: the GEMM tile need not equal the quantization block).  The output is covered by
- * 256 x 256 tiles (2 x 2 quantization blocks); when their number would leave the last round of
- * the GPU's compute units mostly idle, the last block columns are covered by 128 x 384 tiles
- * (1 x 3 blocks) instead.  plan[0] = workgroups with 256 x 256 tiles, plan[1] = tile columns
- * they cover, plan[2] = columns of 128 x 384 tiles (0: none).  compute_units <= 0 means the
- * current device's count, or the value of the environment variable FQ_GEMM_CUS if that is set
- * to a positive number (fq_gemm reads the same variable; meant for tuning and tests).  The
- * plan never changes results: every output element is accumulated in Alg. 1's order.
- * Outputs of less than about a chip's worth of these tiles are computed on smaller tiles instead
- * (32 x 32, 128 x 64 or 128 x 128, chosen by fq_gemm from the shape), with the same results, and
- * where 128 x 384 tiles over the last block rows end earlier than over the last block columns,
- * fq_gemm takes those instead of this plan.
+ * The covering of a rows_out x cols_out output with the large tiles (host-only inspection; App. C: the
+ * GEMM tile need not equal the quantization block): 256 x 256 tiles (2 x 2 quantization blocks)
+ * and, when their number would leave the last round of the GPU's compute units mostly idle,
+ * 128 x 384 tiles (1 x 3 blocks) over the last block columns instead.  plan[0] = workgroups
+ * with 256 x 256 tiles, plan[1] = tile columns they cover, plan[2] = columns of 128 x 384 tiles
+ * (0: none).  compute_units <= 0 means the current device's count, or the value of the
+ * environment variable FQ_GEMM_CUS if that is set to a positive number (fq_gemm reads the same
+ * variable; meant for tuning and tests).  fq_gemm may take smaller tiles, or cut block rows
+ * instead of block columns: fq_gemm_path says what it does.
  */
 fq_status fq_gemm_tile_plan(int32_t rows_out, int32_t cols_out, int32_t compute_units,
                             int32_t plan[3]);
+
+/*
+ * The tiles that fq_gemm (biased = 0) or fq_gemm_biased (1) computes a rows_out x cols_out output
+ * with (host-only inspection, compute_units as above).  path[0] = 1: 32 x 32, 2: 128 x 64, 3:
+ * 128 x 128 tiles, path[1] = their number; these are chosen where the output is less than about a
+ * chip's worth of large tiles.  path[0] = 0: the large ones, path[1] = the number of 256 x 256
+ * tiles, path[2] and path[3] = the number of 128 x 384 tiles over the last block columns or,
+ * where that ends earlier, the last block rows.  All zero for an empty output.  fq_gemm's results do not
+ * depend on the tiles: every output element is accumulated in Alg. 1's order.
+ */
+fq_status fq_gemm_path(int32_t rows_out, int32_t cols_out, int32_t compute_units, int biased,
+                       int32_t path[4]);
 
 /* (With blocks of 64 or 32, k_block counts blocks of that size.)
  * The INT32 block product of k-block `k_block` alone (Alg. 1's INT x INT

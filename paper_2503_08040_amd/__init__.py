@@ -20,6 +20,7 @@ FQ_CRIT_NONE, FQ_CRIT_ABSMAX_GT, FQ_CRIT_ALL, FQ_CRIT_L1_GT, FQ_CRIT_L1REL_GT, F
     0, 1, 2, 3, 4, 5
 FQ_OP_NT, FQ_OP_NN, FQ_OP_TN = 0, 1, 2
 FQ_OUT_F32, FQ_OUT_BF16 = 0, 1
+FQ_TILES_256x256, FQ_TILES_32x32, FQ_TILES_128x64, FQ_TILES_128x128 = 0, 1, 2, 3
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # FQ_LIBRARY: another build of the same library to load instead (the benchmark's ablation builds)
@@ -29,7 +30,8 @@ EXPORTS = ["fq_qtensor_bytes", "fq_qtensor_bind", "fq_quantize", "fq_quantize_sr
            "fq_threshold_update", "fq_gemm", "fq_gemm_plain", "fq_gemm_biased",
            "fq_gemm_debug_partials", "fq_codes_to_rowmajor", "fq_qtensor_check",
            "fq_status_string", "fq_ctx_packed_bytes", "fq_ctx_scales_bytes", "fq_ctx_quantize",
-           "fq_ctx_dequantize", "fq_gemm_tile_plan", "fq_glu_forward", "fq_glu_backward", "fq_rmsnorm_forward",
+           "fq_ctx_dequantize", "fq_gemm_tile_plan", "fq_gemm_path",
+           "fq_glu_forward", "fq_glu_backward", "fq_rmsnorm_forward",
            "fq_rmsnorm_backward", "fq_rmsnorm_backward_static"]
 
 
@@ -124,6 +126,8 @@ def lib():
                                                  C.c_void_p, C.c_int32, C.c_void_p]
         L.fq_gemm_tile_plan.restype = C.c_int
         L.fq_gemm_tile_plan.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
+        L.fq_gemm_path.restype = C.c_int
+        L.fq_gemm_path.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int, C.POINTER(C.c_int32)]
         _lib = L
     return _lib
 
@@ -378,6 +382,15 @@ def fq_gemm_tile_plan(rows_out, cols_out, compute_units=0):
     _check(lib().fq_gemm_tile_plan(int(rows_out), int(cols_out), int(compute_units), out),
            "fq_gemm_tile_plan")
     return int(out[0]), int(out[1]), int(out[2])
+
+
+def fq_gemm_path(rows_out, cols_out, compute_units=0, biased=False):
+    """(FQ_TILES_*, their number, 128x384 tiles over the last block columns, over the last block rows) of
+    fq_gemm or fq_gemm_biased."""
+    out = (C.c_int32 * 4)()
+    _check(lib().fq_gemm_path(int(rows_out), int(cols_out), int(compute_units), int(bool(biased)), out),
+           "fq_gemm_path")
+    return tuple(int(v) for v in out)
 
 
 def _pitch(t):

@@ -486,6 +486,16 @@ fq_status fq_gemm_tile_plan(int32_t rows_out, int32_t cols_out, int32_t compute_
   return FQ_OK;
 }
 
+fq_status fq_gemm_path(int32_t rows_out, int32_t cols_out, int32_t compute_units, int biased,
+                       int32_t path[4]) {
+  if (!path) return FQ_ERR_NULL;
+  if (rows_out < 0 || cols_out < 0) return FQ_ERR_SHAPE;
+  int out[4];
+  fq::gemm_path(rows_out, cols_out, compute_units, biased != 0, out);
+  for (int i = 0; i < 4; ++i) path[i] = out[i];
+  return FQ_OK;
+}
+
 fq_status fq_gemm_debug_partials(fq_op op, const fq_qtensor* A, const fq_qtensor* B,
                                  int32_t k_block, int residual_term, int32_t* p_out,
                                  void* hip_stream) {

@@ -1013,6 +1013,23 @@ void gemm_tile_plan(int nib, int njb, int cus, int out[3]) {
   out[2] = plan.tail_tj;
 }
 
+void gemm_path(int M, int N, int cus, bool biased, int out[4]) {
+  auto blocks = [](int n) { return (int)(((int64_t)n + kBlock - 1) / kBlock); };
+  const int nib = blocks(M), njb = blocks(N);
+  out[0] = out[1] = out[2] = out[3] = 0;
+  if (nib == 0 || njb == 0) return;
+  if (cus <= 0) cus = planning_cus();
+  const TilePlan plan = plan_tiles(nib, njb, cus);
+  const SmallTile tile = plan_small(M, N, plan, cus, biased);
+  out[0] = (int)tile;
+  if (tile != SmallTile::kNone) {
+    out[1] = small_tiles(M, N, tile);
+  } else {
+    out[1] = plan.n_main;
+    out[plan.tail_i0 > 0 ? 3 : 2] = plan.tail_ni * plan.tail_tj;
+  }
+}
+
 hipError_t launch_gemm(const GemmParams& p_in, bool debug, hipStream_t st) {
   if (debug) {
     if (p_in.nib * p_in.njb == 0) return hipSuccess;

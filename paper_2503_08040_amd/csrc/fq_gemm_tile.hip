@@ -458,21 +458,22 @@ __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(GemmParams p
     store_unit(p, acc[u], rg * 32, (cg0 + u) * 32, lane, bad);
 }
 
-template <int kWU>
-static void launch_tiles(const GemmParams& p, hipStream_t st) {
-  const int tj = (p.N + 32 * kWU - 1) / (32 * kWU);
-  hipLaunchKernelGGL(gemm_tile_kernel<kWU>, dim3(p.nib * tj), dim3(kTileThreads), 0, st, p, p.nib, tj);
+int small_tiles(int M, int N, SmallTile tile) {
+  const int r = tile == SmallTile::k32x32 ? 32 : 128;
+  const int c = tile == SmallTile::k32x32 ? 32 : tile == SmallTile::k128x64 ? 64 : 128;
+  return ((M + r - 1) / r) * ((N + c - 1) / c);
 }
 
 hipError_t launch_gemm_small(const GemmParams& p, SmallTile tile, hipStream_t st) {
+  const dim3 grid(small_tiles(p.M, p.N, tile));
   switch (tile) {
-    case SmallTile::k32x32: {
-      const int units = ((p.M + 31) / 32) * ((p.N + 31) / 32);
-      hipLaunchKernelGGL(gemm_wave_kernel<4>, dim3(units), dim3(64), 0, st, p);
+    case SmallTile::k32x32: hipLaunchKernelGGL(gemm_wave_kernel<4>, grid, dim3(64), 0, st, p); break;
+    case SmallTile::k128x64:
+      hipLaunchKernelGGL(gemm_tile_kernel<2>, grid, dim3(kTileThreads), 0, st, p, p.nib, (p.N + 63) / 64);
       break;
-    }
-    case SmallTile::k128x64: launch_tiles<2>(p, st); break;
-    case SmallTile::k128x128: launch_tiles<4>(p, st); break;
+    case SmallTile::k128x128:
+      hipLaunchKernelGGL(gemm_tile_kernel<4>, grid, dim3(kTileThreads), 0, st, p, p.nib, p.njb);
+      break;
     case SmallTile::kNone: break;
   }
   return hipGetLastError();

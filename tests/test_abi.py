@@ -151,3 +151,44 @@ def test_tile_plan_covers_the_output_and_never_costs_more():
     p = (C.c_int32 * 3)()
     assert fq.lib().fq_gemm_tile_plan(-1, 5, 4, p) == fq.FQ_ERR_SHAPE
     assert fq.lib().fq_gemm_tile_plan(5, 5, 4, None) == fq.FQ_ERR_NULL
+
+
+def test_gemm_path_says_what_covers_the_output():
+    """fq_gemm_path (host-only): the tiles it names are as many as cover the output, 128x384 tiles appear
+    over columns or over rows and only with 256x256 tiles, and the kinds of the documented shapes."""
+    import random
+    rng = random.Random(1)
+    seen = set()
+    for _ in range(600):
+        rows, cols = (int(round(2 ** rng.uniform(0, 13.5))) for _ in range(2))
+        cus, biased = rng.choice([1, 2, 3, 8, 64, 256, 304]), rng.random() < 0.5
+        kind, n, over_cols, over_rows = fq.fq_gemm_path(rows, cols, cus, biased)
+        ceil = lambda a, b: -(-a // b)
+        if kind != fq.FQ_TILES_256x256:
+            r, c = {fq.FQ_TILES_32x32: (32, 32), fq.FQ_TILES_128x64: (128, 64), fq.FQ_TILES_128x128: (128, 128)}[kind]
+            assert (n, over_cols, over_rows) == (ceil(rows, r) * ceil(cols, c), 0, 0)
+            seen.add(kind)
+            continue
+        nib, njb = ceil(rows, 128), ceil(cols, 128)
+        ti, tj = ceil(nib, 2), ceil(njb, 2)
+        assert n > 0 and not (over_cols and over_rows)
+        seen.add((kind, over_cols > 0, over_rows > 0))
+        if over_rows:
+            assert n % tj == 0 and over_rows == (nib - 2 * (n // tj)) * ceil(njb, 3)
+        elif over_cols:
+            assert n % ti == 0 and over_cols == nib * ceil(njb - 2 * (n // ti), 3)
+            assert fq.fq_gemm_tile_plan(rows, cols, cus) == (n, n // ti, over_cols // nib)
+        else:
+            assert n == ti * tj
+    assert len(seen) == 6
+    large = fq.FQ_TILES_256x256
+    assert fq.fq_gemm_path(4096, 11008, 256) == (large, 512, 256, 0)
+    assert fq.fq_gemm_path(11008, 4096, 256) == (large, 512, 0, 242)
+    assert fq.fq_gemm_path(33, 11008, 256) == (fq.FQ_TILES_32x32, 688, 0, 0)
+    assert fq.fq_gemm_path(512, 4096, 256) == (fq.FQ_TILES_128x64, 256, 0, 0)
+    assert fq.fq_gemm_path(2048, 11008, 256) == (fq.FQ_TILES_128x128, 1376, 0, 0)
+    assert fq.fq_gemm_path(2048, 11008, 256, biased=True) == (large, 256, 128, 0)
+    assert fq.fq_gemm_path(0, 5, 256) == fq.fq_gemm_path(5, 0, 256) == (0, 0, 0, 0)
+    p = (C.c_int32 * 4)()
+    assert fq.lib().fq_gemm_path(-1, 5, 4, 0, p) == fq.FQ_ERR_SHAPE
+    assert fq.lib().fq_gemm_path(5, 5, 4, 0, None) == fq.FQ_ERR_NULL

@@ -108,17 +108,28 @@ def test_ragged_and_multi_tile_shapes(op, sa, sb):
     _check_gemm(op, ga, gb, oa, ob, f"ragged op={op} {sa}x{sb}", partials=(sa[0] <= 300))
 
 
-@pytest.mark.parametrize("op,sa,sb,cus", [
-    (fq.FQ_OP_NT, (700, 300), (1100, 300), 6),     # 128x384 tiles with one valid block column
-    (fq.FQ_OP_NT, (700, 300), (1100, 300), 10),    # three valid block columns
-    (fq.FQ_OP_NT, (300, 260), (1300, 260), 7),     # two columns of 128x384 tiles, the last ragged
-    (fq.FQ_OP_NN, (300, 200), (200, 1300), 7),
-    (fq.FQ_OP_TN, (200, 700), (200, 1100), 10),
-    (fq.FQ_OP_NT, (129, 128), (1281, 128), 5),     # one k-block, ragged rows and columns
+LARGE, T128x64, T128x128 = fq.FQ_TILES_256x256, fq.FQ_TILES_128x64, fq.FQ_TILES_128x128
+
+
+@pytest.mark.parametrize("op,sa,sb,cus,kind", [
+    (fq.FQ_OP_NT, (250, 300), (1661, 300), 2, LARGE),      # 128x384 tiles with one valid block column
+    (fq.FQ_OP_NT, (250, 300), (1833, 300), 3, LARGE),      # three valid block columns
+    (fq.FQ_OP_NT, (129, 260), (1589, 260), 4, LARGE),      # two columns of 128x384 tiles, the last ragged
+    (fq.FQ_OP_NN, (250, 200), (200, 1661), 4, LARGE),
+    (fq.FQ_OP_TN, (200, 450), (200, 1225), 4, LARGE),
+    (fq.FQ_OP_NT, (129, 128), (1600, 128), 2, LARGE),      # one k-block, ragged rows and columns
+    # the same kinds of edges where smaller tiles are the faster ones
+    (fq.FQ_OP_NT, (700, 300), (1100, 300), 6, T128x128),
+    (fq.FQ_OP_NT, (700, 300), (1100, 300), 10, T128x128),
+    (fq.FQ_OP_NT, (300, 260), (1300, 260), 7, T128x64),
+    (fq.FQ_OP_NN, (300, 200), (200, 1300), 7, T128x64),
+    (fq.FQ_OP_TN, (200, 700), (200, 1100), 10, T128x128),
+    (fq.FQ_OP_NT, (129, 128), (1281, 128), 5, T128x64),
 ])
-def test_mixed_tile_geometries(op, sa, sb, cus, monkeypatch):
-    """The planner's second geometry (128 x 384 tiles for the last block columns), forced on
-    small problems by telling the planner the GPU has only a few compute units."""
+def test_mixed_tile_geometries(op, sa, sb, cus, kind, monkeypatch):
+    """The large tiles' second geometry (128 x 384 tiles for the last block columns), and the smaller
+    tiles that take its place, forced on small problems by telling the planner the GPU has only a few
+    compute units."""
     monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
     rng = np.random.default_rng(sa[0] + 3 * sb[1] + op + cus)
     a = rng.standard_normal(sa).astype(F32)
@@ -128,26 +139,30 @@ def test_mixed_tile_geometries(op, sa, sb, cus, monkeypatch):
     ga, gb, oa, ob = _quant_pair(synth.to_bf16_bits(a), synth.to_bf16_bits(b),
                                  fq.FQ_CRIT_ABSMAX_GT, 8.0)
     Mo, No = fqo.out_shape(op, oa, ob)
-    plan = fq.fq_gemm_tile_plan(Mo, No)
-    assert plan[2] > 0 and plan[0] > 0, f"plan {plan} does not use both geometries"
+    path = fq.fq_gemm_path(Mo, No)
+    assert path[0] == kind, f"path {path}"
+    assert kind != LARGE or (path[1] > 0 and path[2] > 0), f"path {path} does not use both geometries"
     assert int(oa.fb_count[0]) > 0
-    c = _check_gemm(op, ga, gb, oa, ob, f"mixed op={op} {sa}x{sb} cus={cus} plan={plan}", partials=False)
-    # the plan does not change a single bit of the result
+    c = _check_gemm(op, ga, gb, oa, ob, f"mixed op={op} {sa}x{sb} cus={cus} path={path}", partials=False)
+    # the tiles do not change a single bit of the result
     monkeypatch.setenv("FQ_GEMM_CUS", "1000000")
-    assert fq.fq_gemm_tile_plan(Mo, No)[2] == 0
+    assert fq.fq_gemm_path(Mo, No)[0] == fq.FQ_TILES_32x32
     assert np.array_equal(fq.fq_gemm(op, ga, gb).cpu().numpy(), c)
 
 
-def test_scale_products_in_the_subnormal_range():
+@pytest.mark.parametrize("cols,cus,kind", [(384, 256, fq.FQ_TILES_32x32), (512, 1, LARGE), (384, 3, T128x128)])
+def test_scale_products_in_the_subnormal_range(cols, cus, kind, monkeypatch):
     """A and B blocks so small that a^A * a^B is subnormal or underflows to zero: the product of
     the scales, the FMA with it and the accumulator must behave as IEEE binary32 without
     flush-to-zero on both sides."""
+    monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
+    assert fq.fq_gemm_path(256, cols)[0] == kind
     rng = np.random.default_rng(44)
     a = rng.standard_normal((256, 512))
     for bk, k in enumerate((-126, -118, -110, -104)):
         a[:, bk * 128:(bk + 1) * 128] *= 2.0 ** k
     a[5, 3] = 50.0 * 2.0 ** -126                      # an outlier among tiny values
-    b = rng.standard_normal((384, 512)) * 2.0 ** -24
+    b = rng.standard_normal((cols, 512)) * 2.0 ** -24
     b[:128] *= 2.0 ** -20
     with np.errstate(under="ignore"):
         ab, bb = synth.to_bf16_bits(a.astype(F32)), synth.to_bf16_bits(b.astype(F32))
@@ -174,13 +189,16 @@ def test_strided_output_and_reuse():
     assert torch.equal(c1, c2)
 
 
-def test_empty_contraction_and_empty_output():
+@pytest.mark.parametrize("cus,kind", [(256, fq.FQ_TILES_32x32), (3, T128x64), (2, T128x128), (1, LARGE)])
+def test_empty_contraction_and_empty_output(cus, kind, monkeypatch):
+    monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
+    assert fq.fq_gemm_path(256, 256)[0] == kind
     a = fq.fq_quantize(torch.empty((256, 0), dtype=torch.bfloat16, device="cuda"),
                        fq.FQ_CRIT_NONE, 0.0, capacity=0)
-    b = fq.fq_quantize(torch.empty((128, 0), dtype=torch.bfloat16, device="cuda"),
+    b = fq.fq_quantize(torch.empty((256, 0), dtype=torch.bfloat16, device="cuda"),
                        fq.FQ_CRIT_NONE, 0.0, capacity=0)
     gu.announce("gemm with K = 0")
-    c = fq.fq_gemm(fq.FQ_OP_NT, a, b, out=torch.full((256, 128), 3.0, device="cuda"))
+    c = fq.fq_gemm(fq.FQ_OP_NT, a, b, out=torch.full((256, 256), 3.0, device="cuda"))
     assert torch.count_nonzero(c).item() == 0
     a0 = fq.fq_quantize(torch.empty((0, 256), dtype=torch.bfloat16, device="cuda"),
                         fq.FQ_CRIT_NONE, 0.0, capacity=0)
@@ -200,11 +218,13 @@ def test_capacity_overflow_poisons_output():
     assert torch.isnan(c).any().item()      # never a silently wrong product
 
 
-@pytest.mark.parametrize("shape_a,shape_b,cus", [
-    ((600, 384), (300, 384), 0),      # 256x256 tiles only
-    ((700, 300), (1100, 300), 6),     # 128x384 tiles beside them
+@pytest.mark.parametrize("shape_a,shape_b,cus,kind,tail", [
+    ((500, 384), (1281, 384), 4, LARGE, False),         # 256x256 tiles only
+    ((450, 300), (1225, 300), 4, LARGE, True),          # 128x384 tiles beside them
+    ((600, 384), (300, 384), 0, fq.FQ_TILES_32x32, False),
+    ((700, 300), (1100, 300), 6, T128x128, False),
 ])
-def test_capacity_overflow_poisons_exactly_the_affected_block_rows(shape_a, shape_b, cus, monkeypatch):
+def test_capacity_overflow_poisons_exactly_the_affected_block_rows(shape_a, shape_b, cus, kind, tail, monkeypatch):
     """Every block is flagged but only some get a residual slot: the rows of an i-block that has
     a flagged block without a slot are NaN, all other rows are the complete result."""
     if cus:
@@ -221,7 +241,9 @@ def test_capacity_overflow_poisons_exactly_the_affected_block_rows(shape_a, shap
     assert (slot == -2).sum() == nbr * nbc - (nbr * nbc) // 2
     bad = (slot == -2).any(axis=1)
     assert bad.any()
-    gu.announce(f"gemm with overflowed residual slots, plan {fq.fq_gemm_tile_plan(shape_a[0], shape_b[0])}")
+    path = fq.fq_gemm_path(shape_a[0], shape_b[0])
+    assert path[0] == kind and (path[2] > 0) == tail
+    gu.announce(f"gemm with overflowed residual slots, path {path}")
     c = fq.fq_gemm(fq.FQ_OP_NT, ga, gb).cpu().numpy()
     ref = fqo.gemm(fqo.OP_NT, fqo.quantize(a_bits, 128, fqo.CRIT_ALL, 0.0),
                    fqo.quantize(b_bits, 128, fqo.CRIT_NONE, 0.0))
@@ -296,16 +318,20 @@ def test_full_size(cfg, monkeypatch):
         del ref, refb
     assert worst <= TOL
     # properties that hold at any size: finite everywhere, bf16 output is the rounding of fp32,
-    # and the result does not depend on the tile plan (config 2 on 256 compute units uses both
-    # tile geometries; forcing a single geometry must give the same bits)
+    # and the result does not depend on the tiles (config 2 on 256 compute units uses both
+    # large tile geometries; 256 x 256 tiles alone and 32 x 32 tiles must give the same bits)
     assert torch.isfinite(c32).all().item()
     assert torch.equal(c, c32.to(torch.bfloat16))
-    plan = fq.fq_gemm_tile_plan(wl.M, wl.N)
-    print(f"{cfg}: tile plan {plan}", flush=True)
-    monkeypatch.setenv("FQ_GEMM_CUS", "1000000")
-    assert fq.fq_gemm_tile_plan(wl.M, wl.N)[2] == 0
-    gu.announce(f"{cfg}: gemm with a single tile geometry")
-    assert torch.equal(fq.fq_gemm(fq.FQ_OP_NT, ga, gb), c32)
+    path = fq.fq_gemm_path(wl.M, wl.N)
+    print(f"{cfg}: tiles {path}", flush=True)
+    assert path[0] == LARGE and (path[2] > 0) == (cfg == "cfg2")
+    single = -(-wl.M // 256) * -(-wl.N // 256)
+    for cus, want in ((single, (LARGE, single, 0, 0)),
+                      (1000000, (fq.FQ_TILES_32x32, -(-wl.M // 32) * -(-wl.N // 32), 0, 0))):
+        monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
+        assert fq.fq_gemm_path(wl.M, wl.N) == want
+        gu.announce(f"{cfg}: gemm with a single tile geometry {want}")
+        assert torch.equal(fq.fq_gemm(fq.FQ_OP_NT, ga, gb), c32)
 
 
 @pytest.mark.parametrize("variant", ["stochastic", "fallback"])

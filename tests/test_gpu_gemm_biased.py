@@ -44,8 +44,18 @@ def _check(op, ga, gb, oa, ob, label):
     return err
 
 
-def test_config1():
+def _own(rows, cols, tails=False):
+    """Asserts that a rows x cols output runs the biased kernel itself, with both of its geometries."""
+    path = fq.fq_gemm_path(rows, cols, biased=True)
+    assert path[0] == fq.FQ_TILES_256x256 and (path[2] > 0) == tails, path
+
+
+@pytest.mark.parametrize("cus", [256, 1])
+def test_config1(cus, monkeypatch):
+    monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
     wl = synth.config1()
+    if cus == 1:
+        _own(wl.M, wl.N)
     ga, gb, oa, ob = _quant_pair(wl.X, wl.W, fq.FQ_CRIT_ABSMAX_GT, wl.theta)
     _check(fq.FQ_OP_NT, ga, gb, oa, ob, "cfg1")
     # every block flagged: a residual item behind every main item
@@ -62,6 +72,23 @@ def test_config1():
     (fq.FQ_OP_NT, (640, 128), (768, 128)),        # one k-block: a window that never fills
 ])
 def test_ragged_and_multi_tile_shapes(op, sa, sb):
+    _ragged(op, sa, sb)
+
+
+@pytest.mark.parametrize("op,sa,sb", [
+    (fq.FQ_OP_NT, (250, 200), (253, 200)),
+    (fq.FQ_OP_NT, (500, 1300), (450, 1300)),      # 11 k-blocks: bias windows of 4, 4 and 3 items
+    (fq.FQ_OP_NN, (497, 384), (384, 500)),
+    (fq.FQ_OP_TN, (384, 497), (384, 500)),
+    (fq.FQ_OP_NT, (512, 128), (768, 128)),        # one k-block: a window that never fills
+])
+def test_ragged_and_multi_tile_shapes_on_the_biased_kernel(op, sa, sb, monkeypatch):
+    monkeypatch.setenv("FQ_GEMM_CUS", "1")
+    _own(sa[1] if op == fq.FQ_OP_TN else sa[0], sb[0] if op == fq.FQ_OP_NT else sb[1])
+    _ragged(op, sa, sb)
+
+
+def _ragged(op, sa, sb):
     rng = np.random.default_rng(sa[0] + 7 * sb[1] + op)
     a = rng.standard_normal(sa).astype(F32)
     for _ in range(6):
@@ -74,7 +101,8 @@ def test_ragged_and_multi_tile_shapes(op, sa, sb):
 
 @pytest.mark.parametrize("op,sa,sb,cus", [
     (fq.FQ_OP_NT, (700, 300), (1100, 300), 10),
-    (fq.FQ_OP_NN, (300, 200), (200, 1300), 7),
+    (fq.FQ_OP_NT, (129, 600), (1040, 600), 2),    # 128x384 tiles with one valid block column
+    (fq.FQ_OP_NN, (250, 200), (200, 1467), 4),    # two columns of them
 ])
 def test_mixed_tile_geometries(op, sa, sb, cus, monkeypatch):
     monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
@@ -86,13 +114,16 @@ def test_mixed_tile_geometries(op, sa, sb, cus, monkeypatch):
     ga, gb, oa, ob = _quant_pair(synth.to_bf16_bits(a), synth.to_bf16_bits(b),
                                  fq.FQ_CRIT_ABSMAX_GT, 8.0)
     Mo, No = fqo.out_shape(op, oa, ob)
-    plan = fq.fq_gemm_tile_plan(Mo, No)
-    assert plan[2] > 0 and plan[0] > 0
+    _own(Mo, No, tails=True)
     _check(op, ga, gb, oa, ob, f"mixed op={op} {sa}x{sb} cus={cus}")
 
 
-def test_scale_range():
+@pytest.mark.parametrize("cus", [256, 1])
+def test_scale_range(cus, monkeypatch):
     """The bias is proportional to the scales: tiny and huge scale products in one contraction."""
+    monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
+    if cus == 1:
+        _own(256, 256)
     rng = np.random.default_rng(5)
     a = rng.standard_normal((256, 1024)).astype(F32)
     a[:, :128] *= F32(1e-12)
@@ -107,6 +138,8 @@ def test_smaller_tiles_only_where_they_beat_the_biased_kernel(shape, cus, own, m
     """fq_gemm takes smaller tiles for all of these.  They are exact, so whether the variant ran its own
     kernel shows in the bits: two large tiles on two compute units, two on three, two on the chip."""
     monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
+    assert fq.fq_gemm_path(*shape)[0] != fq.FQ_TILES_256x256
+    assert (fq.fq_gemm_path(*shape, biased=True)[0] == fq.FQ_TILES_256x256) == own
     rng = np.random.default_rng(11)
     a = rng.standard_normal((shape[0], 1300)).astype(F32)
     b = rng.standard_normal((shape[1], 1300)).astype(F32)
@@ -117,18 +150,21 @@ def test_smaller_tiles_only_where_they_beat_the_biased_kernel(shape, cus, own, m
     assert torch.equal(fq.fq_gemm_biased(fq.FQ_OP_NT, ga, gb), exact) != own
 
 
-def test_rejects_small_groups_and_empty_cases():
+def test_rejects_small_groups_and_empty_cases(monkeypatch):
     x = torch.randn((256, 256), device="cuda").to(torch.bfloat16)
     q64 = fq.fq_quantize(x, fq.FQ_CRIT_NONE, 0.0, capacity=0, block=64)
     with pytest.raises(fq.FqError) as e:
         fq.fq_gemm_biased(fq.FQ_OP_NT, q64, q64)
     assert e.value.status == fq.FQ_ERR_BLOCK
     a = fq.QTensor(256, 0)
-    b = fq.QTensor(128, 0, capacity=0)
+    b = fq.QTensor(256, 0, capacity=0)
     fq.fq_quantize(torch.empty((256, 0), dtype=torch.bfloat16, device="cuda"), fq.FQ_CRIT_NONE, 0.0, out=a)
-    fq.fq_quantize(torch.empty((128, 0), dtype=torch.bfloat16, device="cuda"), fq.FQ_CRIT_NONE, 0.0, out=b)
-    c = fq.fq_gemm_biased(fq.FQ_OP_NT, a, b, out=torch.full((256, 128), 3.0, device="cuda"))
-    assert (c == 0).all().item()
+    fq.fq_quantize(torch.empty((256, 0), dtype=torch.bfloat16, device="cuda"), fq.FQ_CRIT_NONE, 0.0, out=b)
+    for cus in (256, 1):                          # the exact 32x32 tiles, the biased kernel
+        monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
+        assert (fq.fq_gemm_path(256, 256, biased=True)[0] == fq.FQ_TILES_256x256) == (cus == 1)
+        c = fq.fq_gemm_biased(fq.FQ_OP_NT, a, b, out=torch.full((256, 256), 3.0, device="cuda"))
+        assert (c == 0).all().item()
 
 
 @pytest.mark.parametrize("cfg", ["cfg2", "cfg3"])
@@ -141,6 +177,7 @@ def test_full_size(cfg):
     gb = fq.fq_quantize(gu.to_device_bf16(wl.W), fq.FQ_CRIT_NONE, 0.0, capacity=0)
     oa = fqo.quantize(wl.X, 128, fqo.CRIT_ABSMAX_GT, wl.theta)
     ob = fqo.quantize(wl.W, 128, fqo.CRIT_NONE, 0.0)
+    _own(wl.M, wl.N, tails=cfg == "cfg2")
     gu.announce(f"{cfg}: biased gemm")
     c32 = fq.fq_gemm_biased(fq.FQ_OP_NT, ga, gb)
     exact = fq.fq_gemm(fq.FQ_OP_NT, ga, gb)

@@ -38,7 +38,8 @@ def _compare(op, Mo, No, K, spikes, tag):
 
 @pytest.mark.parametrize("op,K", [(NT, 128), (NT, 8192), (NT, 8300), (NN, 8191), (TN, 8400), (TN, 16500)])
 def test_scales_of_64_k_blocks_at_a_time(op, K, monkeypatch):
-    monkeypatch.setenv("FQ_GEMM_CUS", "1")       # one 256 x 256 tile
+    monkeypatch.setenv("FQ_GEMM_CUS", "1")
+    assert fq.fq_gemm_path(250, 256) == (fq.FQ_TILES_256x256, 1, 0, 0) == fq.fq_gemm_path(250, 256, biased=True)
     _compare(op, 250, 256, K, 20, "one tile")
 
 
@@ -47,11 +48,13 @@ def test_tail_along_the_last_block_rows(op, K, monkeypatch):
     # 10 x 2 blocks on two compute units: five 256 x 256 tiles would be three rounds; four of them and
     # two 128 x 384 tiles over the last two block rows are 2.75
     monkeypatch.setenv("FQ_GEMM_CUS", "2")
+    assert fq.fq_gemm_path(1275, 253) == (fq.FQ_TILES_256x256, 4, 0, 2) == fq.fq_gemm_path(1275, 253, biased=True)
     _compare(op, 1275, 253, K, 30, "row tail")
 
 
 def test_block_without_a_slot_behind_the_64th(monkeypatch):
     monkeypatch.setenv("FQ_GEMM_CUS", "1")
+    assert fq.fq_gemm_path(256, 200)[0] == fq.FQ_TILES_256x256
     a, b = _operands(NT, 256, 200, 66 * 128, 1, 0)
     a[200, 65 * 128 + 3] = a[10, 65 * 128 + 3] = 0x4300          # both block rows flagged at k = 65
     ga = fq.fq_quantize(gu.to_device_bf16(a), fq.FQ_CRIT_ABSMAX_GT, 12.0, capacity=1)

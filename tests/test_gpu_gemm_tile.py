@@ -19,6 +19,13 @@ NT, NN, TN = fq.FQ_OP_NT, fq.FQ_OP_NN, fq.FQ_OP_TN
 # (rows, columns of the output, compute units assumed) and the tile they lead to
 TILES = {"32x32": (65, 33, 256), "32x32 one row": (1, 300, 256), "128x64": (300, 260, 8),
          "128x64 odd": (129, 301, 5), "128x128": (300, 370, 5), "256x256 and 128x384": (700, 1400, 7)}
+KIND = {"32x32": fq.FQ_TILES_32x32, "128x64": fq.FQ_TILES_128x64, "128x128": fq.FQ_TILES_128x128,
+        "256x256": fq.FQ_TILES_256x256}
+
+
+def _assert_path(tile):
+    path = fq.fq_gemm_path(*TILES[tile][:2])
+    assert path[0] == KIND[tile.split()[0]] and (path[2] + path[3] > 0) == ("128x384" in tile), path
 
 
 def _operands(op, Mo, No, K, seed, spikes):
@@ -40,6 +47,7 @@ def test_tiles_match_the_oracle(tile, op, K, spikes, monkeypatch):
     if K > 1000 and Mo * No > 200 * 400:
         K = 1300                    # the oracle's time; eleven k-blocks are enough where the others have had 66
     monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
+    _assert_path(tile)
     a, b = _operands(op, Mo, No, K, K + Mo + op, spikes)
     ga, gb, oa, ob = _quant_pair(a, b, fq.FQ_CRIT_ABSMAX_GT, 12.0)
     gu.announce(f"tile {tile} op={op} {Mo}x{No} K={K} flagged {int(oa.fb_count[0])}")
@@ -58,6 +66,7 @@ def test_tiles_match_the_oracle(tile, op, K, spikes, monkeypatch):
 def test_blocks_without_a_slot_poison_their_rows(tile, monkeypatch):
     Mo, No, cus = TILES[tile]
     monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
+    _assert_path(tile)
     a, b = _operands(NT, Mo, No, 512, 3, 0)
     nbr = -(-Mo // 128)
     ga = fq.fq_quantize(gu.to_device_bf16(a), fq.FQ_CRIT_ALL, 0.0, capacity=nbr * 4 - 1)
