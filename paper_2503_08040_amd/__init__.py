@@ -157,11 +157,26 @@ def _t():
     return _torch
 
 
+_current_stream = None
+
+
+def _stream_lookup():
+    """A function that returns the current stream's handle.  torch.cuda.current_stream() builds an object
+    for it (2.9 us); the two names that go without are not documented, so a torch may lack them."""
+    global _current_stream
+    torch = _t()
+    device, raw = (getattr(torch._C, n, None) for n in ("_cuda_getDevice", "_cuda_getCurrentRawStream"))
+    if device and raw:
+        _current_stream = lambda: raw(device())
+    else:
+        _current_stream = lambda: torch.cuda.current_stream().cuda_stream
+    return _current_stream
+
+
 def _stream_ptr(stream):
     if stream is not None:
         return stream.cuda_stream
-    c = _t()._C
-    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    return (_current_stream or _stream_lookup())()
 
 
 def _bf16_matrix(x):
@@ -239,8 +254,8 @@ def fq_quantize(x, crit, theta, out: QTensor = None, capacity=None, want_transpo
     rows, cols, ld = _bf16_matrix(x)
     if out is None:
         out = QTensor(rows, cols, capacity, want_transposed, x.device, block=block)
-    _check((_lib or lib()).fq_quantize(x.data_ptr(), rows, cols, ld, out.block, int(crit), float(theta), out._ref,
-                                       _stream_ptr(stream)), "fq_quantize")
+    _check((_lib or lib()).fq_quantize(x.data_ptr(), rows, cols, ld, out.block, int(crit), C.c_float(theta),
+                                       out._ref, _stream_ptr(stream)), "fq_quantize")
     return out
 
 
@@ -446,7 +461,7 @@ def fq_rmsnorm_forward(x, w, eps, stream=None):
     packed = torch.empty((rows, ng, FQ_CTX_GROUP_BYTES), dtype=torch.uint8, device=x.device)
     scales = torch.empty((rows, ng), dtype=torch.float32, device=x.device)
     _check(lib().fq_rmsnorm_forward(x.data_ptr(), w.data_ptr(), rows, cols,
-                                    _pitch(x), float(eps), y.data_ptr(), _pitch(y),
+                                    _pitch(x), C.c_float(eps), y.data_ptr(), _pitch(y),
                                     packed.data_ptr(), scales.data_ptr(),
                                     rstd.data_ptr(), _stream_ptr(stream)),
            "fq_rmsnorm_forward")
