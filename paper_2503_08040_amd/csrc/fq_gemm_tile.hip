@@ -218,7 +218,8 @@ __device__ __forceinline__ void steps(int k, int end, F& step, bool reload) {
 // for a k-block leaves the younger ones in flight.  A k-block's tile is folded under the next one's
 // MFMAs, which matters where a wavefront has its SIMD to itself: 33 x 11008 x 4096 23.3 -> 21.4 us, 64 x
 // 2048 x 2048 6.5 -> 6.1, 128 x 4096 x 4096 11.3 -> 10.7.  33 x 4096 x 11008 (12.2 us) reads its 45 MB of
-// weights at 4.6 TB/s.
+// weights at 3.7 TB/s: its 688 wavefronts have 5.6 MB of them in flight, since the two row groups of a column
+// ask for the same ones.
 template <int kD>
 __global__ __launch_bounds__(64, 2) void gemm_wave_kernel(GemmParams p) {
   const int lane = threadIdx.x;
