@@ -959,14 +959,14 @@ TilePlan plan_tiles(int nib, int njb, int cus) {
 //   128 x 64    520, or 390                                     (512 x 4096 x 4096; 3072^3)
 //   128 x 128   850 alone on its compute unit, 1360 a pair (two are resident)
 //   256 x 256   2400 (2250 on an idle chip), one is resident    (4096^3);
-//               gemm_biased_kernel 2050                         (2048 x 11008 x 4096)
+//               gemm_biased_kernel 2050                         (2048 x 4096 x 11008)
 // So 2048 x 4096 x 4096 takes 128 x 128 tiles (48 us against 52 with 128 x 64 and 76 with 256 x 256),
 // 3072^3 128 x 64 (46.5, 51 with 128 x 128, 61 with 256 x 256) and 4096^3 256 x 256 (81 us, 89 with
 // 128 x 128); 512 x 4096 x 4096 takes 128 x 64 (19.5 us, 23.5 with 32 x 32) and 256 x 11008 x 4096
 // 32 x 32 (28.7 us, 44 with 128 x 64).  64 x 64 tiles were never better than the nearer of their
 // neighbours by more than 3 %.  The smaller tiles have no biased form, so fq_gemm_biased takes them where
-// they beat its own kernel: 2048 x 4096 x 4096 (49 us against 68), but not 2048 x 11008 x 4096
-// (129 against 117) or 3072 x 4096 x 11008 (170 against 151), which fq_gemm computes on 128 x 128.
+// they beat its own kernel: 2048 x 4096 x 4096 (49 us against 68), but not 2048 x 4096 x 11008
+// (129 against 117) or 3072 x 11008 x 4096 (170 against 151), which fq_gemm computes on 128 x 128.
 SmallTile plan_small(int M, int N, const TilePlan& big, int cus, bool biased) {
   const double c = cus > 0 ? cus : 256;
   auto tiles = [&](int r, int s) { return (double)((M + r - 1) / r) * ((N + s - 1) / s) / c; };

@@ -12,12 +12,15 @@
 //   gemm_tile_kernel<2>   128 x 64 tiles, 4 wavefronts of 32 x 64
 //   gemm_tile_kernel<4>   128 x 128 tiles, 4 wavefronts of 32 x 128
 // A wavefront owns 32 whole rows, so its A operands go from global memory into registers and only
-// the B operands, which the wavefronts of a column share, pass through LDS.  What bounds them is the
-// 64 bytes a compute unit's vector cache delivers per cycle: a 32 x 32 x 128 step costs 8, 3 and 2 KiB
-// of operands in the three forms (1 KiB in gemm_kernel), and with the loads taken out of the loop
-// 4096^3 runs at 1773 and 2008 TOP/s on the first two instead of 486 and 1525; with a single wavefront on
-// a SIMD it is the issue of its own loads, matrix and vector instructions one after the other (500 to
-// 550 cycles per step).  Smaller tiles win while the chip is not full, larger ones from then on;
+// the B operands, which the wavefronts of a column share, pass through LDS.  A 32 x 32 x 128 step
+// asks the compute unit's vector cache for 8, 3 and 2 KiB of operands in the three forms (1 KiB in
+// gemm_kernel), and on a full chip that is what they lose to the larger tiles by: with the loads taken out
+// of the loop 4096^3 runs at 1773 and 2008 TOP/s on the first two instead of 486 and 1525.  Where they are
+// chosen it is latency: the cache serves a quarter to a half of its access per cycle, and with one or two
+// wavefronts on a SIMD a third of a wavefront's time is waiting for loads (or the barrier) and a third the issue
+// of its own matrix and vector instructions, one after the other; the matrix cores are busy 12 % of the cycles
+// (33 x 4096 x 11008), 25 % (2048^3) and 37 % (2048 x 4096 x 4096).
+// Smaller tiles win while the chip is not full, larger ones from then on;
 // plan_small in fq_gemm.hip has the rule.
 // Measured (GEMM alone, bf16 output, 5 % of the blocks flagged, gemm_kernel -> the form chosen):
 // 33 x 4096 x 11008 70.6 -> 12.2 us, 256 x 11008 x 4096 182 -> 28.1 us, 777 x 1544 x 2200

@@ -443,14 +443,15 @@ __device__ __forceinline__ void stochastic_row(const v4i (&raw)[kRows], int r, u
 
 }  // namespace
 
-// What bounds it: HBM for large tensors (4.6 TB/s of the 5 a large copy reaches on 8192 x 8192), on a
-// thousand blocks and fewer the chain load - maximum - quantize - store of a block that no other round
-// of workgroups overlaps.  Four rows x 8 columns per thread in 64 registers let four workgroups of
-// eight wavefronts share a compute unit (twice the wavefronts of a 4 x 16 split by 256 threads) and
-// halve a thread's part of that chain.  Measured against that split, re-quantizing into the same
-// tensor, 5 % of the blocks flagged: 2048 x 4096 14.2 -> 11.4 us, 4096 x 4096 19.2 -> 16.3 us (with
-// transposed copies 25.6 -> 17.8, stochastic with them 25.6 -> 19.8), 8192 x 8192 46.1 -> 43.9 us
-// (66.0 -> 59.1, 78.8 -> 68.3), 33 x 4096 13.1 -> 8.6 us.
+// What bounds it: memory for large tensors (8192 x 8192: 5.5 TB/s, a part of it from the last-level cache; a
+// large copy reaches 5.2), on a thousand blocks and fewer the chain load - maximum - quantize - store of a
+// block that no other round of workgroups overlaps.  Four rows x 8 columns per thread in 64 registers let
+// four workgroups of eight wavefronts share a compute unit (twice the wavefronts of a 4 x 16 split by 256
+// threads) and halve a thread's part of that chain.  Measured against that split (and its rounding, which
+// tested every value), re-quantizing into the same tensor, 5 % of the blocks flagged: 2048 x 4096 12.7 ->
+// 10.2 us, 4096 x 4096 18.5 -> 14.7 us (with transposed copies 24.9 -> 16.8, stochastic with them 25.9 ->
+// 20.8), 8192 x 8192 40.8 -> 37.6 us (61.2 -> 48.4, 76 -> 63), 33 x 4096 13.4 -> 6.7 us; every block flagged
+// 33.5 -> 30.8 and 73.7 -> 73.4 us; the L1 criteria (88 registers), 30 % flagged, 30 -> 22 and 81 -> 57 us.
 // kErr: the fallback decision uses a block quantization-error metric (criteria 3, 4), which
 // needs the residual of every block, not only of the flagged ones.
 template <bool kWantT, Rounding kR, bool kErr>
