@@ -34,8 +34,8 @@
 //     part and leaves the dequantizing pipeline about 10 % faster.)
 // The accumulation order per output element is exactly Alg. 1's (k ascending,
 // main term then residual term) in both geometries, so results match a
-// sequential evaluation bit for bit and do not depend on the tile plan.  Outputs too small for a
-// chip's worth of these tiles are computed by the kernels of fq_gemm_tile.hip, also bit for bit.
+// sequential evaluation bit for bit and do not depend on the tile plan.  Outputs too small for a chip's
+// worth of these tiles are computed by the kernels of fq_gemm_tile.hip and fq_gemm_ring.hip, also bit for bit.
 #include <algorithm>
 #include <atomic>
 #include <cmath>
@@ -950,37 +950,47 @@ TilePlan plan_tiles(int nib, int njb, int cus) {
   return cols;
 }
 
-// Tile of fq_gemm_tile.hip for this output, or kNone: the tiles above.  Estimated nanoseconds per
-// k-block (K = 128) of the busiest compute unit, from measurements over 256 <= M, N <= 4096 and
-// 512 <= K <= 11008 (33 rows too); the launch and the ends of the kernel cost all forms about the
-// same 3 us.  A form has a latency below which a k-block does not get however few tiles there are,
-// and a throughput:
+// Smaller tile for this output, or kNone: the tiles above.  Estimated nanoseconds per k-block (K = 128) of the
+// busiest compute unit, from measurements over 256 <= M, N <= 4096 and 512 <= K <= 11008 (33 rows too); the
+// launch and the ends of the kernel cost all forms about the same 3 us.  A form has a latency below which a
+// k-block does not get however few tiles there are, and a throughput:
 //   32 x 32     240, or 80 per tile and compute unit            (33 x 11008 x 4096; 512 x 4096 x 4096)
-//   128 x 64    520, or 390                                     (512 x 4096 x 4096; 3072^3)
+//   128 x 64    1000 for up to three of them (three are resident), or 390 each         (1536 x 4096 x 4096; 3072^3)
 //   128 x 128   850 alone on its compute unit, 1360 a pair (two are resident)
 //   256 x 256   2400 (2250 on an idle chip), one is resident    (4096^3);
 //               gemm_biased_kernel 2050                         (2048 x 4096 x 11008)
-// So 2048 x 4096 x 4096 takes 128 x 128 tiles (48 us against 52 with 128 x 64 and 76 with 256 x 256),
-// 3072^3 128 x 64 (46.5, 51 with 128 x 128, 61 with 256 x 256) and 4096^3 256 x 256 (81 us, 89 with
-// 128 x 128); 512 x 4096 x 4096 takes 128 x 64 (19.5 us, 23.5 with 32 x 32) and 256 x 11008 x 4096
-// 32 x 32 (28.7 us, 44 with 128 x 64).  64 x 64 tiles were never better than the nearer of their
-// neighbours by more than 3 %.  The smaller tiles have no biased form, so fq_gemm_biased takes them where
-// they beat its own kernel: 2048 x 4096 x 4096 (49 us against 68), but not 2048 x 4096 x 11008
-// (129 against 117) or 3072 x 11008 x 4096 (170 against 151), which fq_gemm computes on 128 x 128.
+// and the forms of fq_gemm_ring.hip, for one round of the chip and no more:
+//   128 x 64    380 alone on its compute unit, 675 a pair       (512 x 8192 x 4096; 1024 x 8192 x 4096)
+//   128 x 128   600                                             (1024 x 8192 x 4096)
+//   128 x 256   1090                                            (2048 x 8192 x 4096)
+// So 2048 x 4096 x 4096 takes 128 x 256 (39 us without flagged blocks, 43.5 with 128 x 128 pairs, 76 with
+// 256 x 256), 1536 x 4096 x 4096 three 128 x 64 per compute unit (34.1; 35.1 with 128 x 256, 36.0 with 128 x 64 of
+// the ring in two rounds), 3072^3 128 x 64 too (42; 44 and 48 in two and three rounds of the ring's 128 x 64 and
+// 128 x 128, 61 with 256 x 256) and 4096^3 256 x 256 (79 us; 82 in two rounds of 128 x 256); 512 x 4096 x 4096
+// takes the ring's 128 x 64 (16.3 us; 18.9 with the other, 23.5 with 32 x 32), 256 x 4096 x 4096 32 x 32 (10.8 us,
+// 15.4 with the ring) and 256 x 11008 x 4096 too (28.6 us, 33.2).  64 x 64 tiles were never better than the nearer
+// of their neighbours by more than 3 %.  The smaller tiles have no biased form, so fq_gemm_biased takes them where
+// they beat its own kernel: 2048 x 4096 x 4096 (42 us against 68), but not 2048 x 4096 x 11008 (129 against 117)
+// or 3072 x 11008 x 4096 (170 against 151), which fq_gemm computes on 128 x 128.
 SmallTile plan_small(int M, int N, const TilePlan& big, int cus, bool biased) {
   const double c = cus > 0 ? cus : 256;
   auto tiles = [&](int r, int s) { return (double)((M + r - 1) / r) * ((N + s - 1) / s) / c; };
-  auto whole = [](double n) { return n <= 2.0 ? std::ceil(n) : n; };   // few tiles: the fullest unit counts
-  const double pairs = std::floor(tiles(128, 128) / 2.0), rest = tiles(128, 128) - 2.0 * pairs;
-  const double est[3] = {std::max(240.0, 80.0 * tiles(32, 32)), std::max(520.0, 390.0 * whole(tiles(128, 64))),
-                         1360.0 * pairs + (rest > 1.0 ? 1360.0 : rest > 0.0 ? 850.0 : 0.0)};
-  const SmallTile kind[3] = {SmallTile::k32x32, SmallTile::k128x64, SmallTile::k128x128};
+  const double n64 = tiles(128, 64), n128 = tiles(128, 128);
+  const double pairs = std::floor(n128 / 2.0), rest = n128 - 2.0 * pairs;
+  constexpr double kNever = 1e300;
+  const struct { SmallTile kind; double est; } form[] = {
+      {SmallTile::k32x32, std::max(240.0, 80.0 * tiles(32, 32))},
+      {SmallTile::k128x64, n64 <= 3.0 ? 1000.0 : 390.0 * n64},
+      {SmallTile::k128x128, 1360.0 * pairs + (rest > 1.0 ? 1360.0 : rest > 0.0 ? 850.0 : 0.0)},
+      {SmallTile::kRing128x64, n64 <= 1.0 ? 380.0 : n64 <= 2.0 ? 675.0 : kNever},
+      {SmallTile::kRing128x128, n128 <= 1.0 ? 600.0 : kNever},
+      {SmallTile::kRing128x256, tiles(128, 256) <= 1.0 ? 1090.0 : kNever}};
   double best = (biased ? 2050.0 : 2400.0) * big.cost;
   SmallTile tile = SmallTile::kNone;
-  for (int i = 0; i < 3; ++i)
-    if (est[i] < best) {
-      best = est[i];
-      tile = kind[i];
+  for (const auto& f : form)
+    if (f.est < best) {
+      best = f.est;
+      tile = f.kind;
     }
   return tile;
 }
@@ -1024,9 +1034,16 @@ void gemm_path(int M, int N, int cus, bool biased, int out[4]) {
   if (cus <= 0) cus = planning_cus();
   const TilePlan plan = plan_tiles(nib, njb, cus);
   const SmallTile tile = plan_small(M, N, plan, cus, biased);
-  out[0] = (int)tile;
-  if (tile != SmallTile::kNone) {
-    out[1] = small_tiles(M, N, tile);
+  auto small = [&](int kind, int r, int c) {
+    out[0] = kind;
+    out[1] = (int)(((int64_t)M + r - 1) / r) * (int)(((int64_t)N + c - 1) / c);
+  };
+  if (tile == SmallTile::k32x32) {
+    small(1, 32, 32);
+  } else if (tile == SmallTile::k128x64 || tile == SmallTile::kRing128x64) {
+    small(2, 128, 64);
+  } else if (tile != SmallTile::kNone) {
+    small(3, 128, 128);
   } else {
     out[1] = plan.n_main;
     out[plan.tail_i0 > 0 ? 3 : 2] = plan.tail_ni * plan.tail_tj;

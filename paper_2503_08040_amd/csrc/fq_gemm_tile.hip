@@ -15,22 +15,22 @@
 // the B operands, which the wavefronts of a column share, pass through LDS.  A 32 x 32 x 128 step
 // asks the compute unit's vector cache for 8, 3 and 2 KiB of operands in the three forms (1 KiB in
 // gemm_kernel), and on a full chip that is what they lose to the larger tiles by: with the loads taken out
-// of the loop 4096^3 runs at 1773 and 2008 TOP/s on the first two instead of 486 and 1525.  Where they are
-// chosen it is latency: the cache serves a quarter to a half of its access per cycle, and with one or two
-// wavefronts on a SIMD a third of a wavefront's time is waiting for loads (or the barrier) and a third the issue
-// of its own matrix and vector instructions, one after the other; the matrix cores are busy 12 % of the cycles
-// (33 x 4096 x 11008), 25 % (2048^3) and 37 % (2048 x 4096 x 4096).
-// Smaller tiles win while the chip is not full, larger ones from then on;
-// plan_small in fq_gemm.hip has the rule.
-// Measured (GEMM alone, bf16 output, 5 % of the blocks flagged, gemm_kernel -> the form chosen):
-// 33 x 4096 x 11008 70.6 -> 12.2 us, 256 x 11008 x 4096 182 -> 28.1 us, 777 x 1544 x 2200
-// 34.6 -> 10.9 us, 2048^3 42.5 -> 17.7 us, 2048 x 4096 x 4096 76 -> 48 us.
+// of the loop 4096^3 runs at 1773 and 2008 TOP/s on the first two instead of 486 and 1525.  With few tiles it is
+// latency: a third of a wavefront's time is waiting for loads (or the barrier) and a third the issue of its own
+// matrix and vector instructions, one after the other; 33 x 4096 x 11008 keeps the matrix cores busy 12 % of
+// the cycles.  So the 128 x 64 and 128 x 128 forms are for outputs of more than a round of the tiles of
+// fq_gemm_ring.hip and less than about a round of gemm_kernel's, where two or three workgroups on a compute unit
+// hide each other's latency and start and end at different times; plan_small in fq_gemm.hip has the rule.
+// Measured (GEMM alone, bf16 output, gemm_kernel -> the form chosen): 33 x 4096 x 11008 70.6 -> 12.2 us,
+// 256 x 11008 x 4096 182 -> 28.1 us (5 % of the blocks flagged), 1536 x 4096 x 4096 76 -> 34.1 us, 3072^3
+// 61 -> 42 us.
 //
 // The MFMA operands are swapped (D = B A^T): a lane then holds consecutive columns of one row of C
 // and stores them without a transposition through LDS.
 #include <type_traits>
 
 #include "fq_device.h"
+#include "fq_gemm_unit.h"
 #include "fq_kernels.h"
 
 namespace fq {
@@ -38,74 +38,8 @@ namespace fq {
 namespace {
 
 
-constexpr int kXcds = 8;          // accelerator complex dies, each with a private L2
 constexpr int kGroupN = 4;        // tile columns per rasterization group
 constexpr int kTileThreads = 256;
-constexpr int kFragRows = 4096;   // bytes of one 32-row group of a block (128 contraction positions)
-
-// Row (of the 32 in a group) that lane i of operand half ch = 0, 1 supplies.  The result registers
-// of lane group g = i / 4 are 4 consecutive operand rows; with this order the two halves give a lane
-// 8 consecutive columns of C, columns 8 g + 4 ch' ..., and both the first 8 and the 16 lanes of an
-// LDS read fall into distinct banks (ch' = ch or 1 - ch by g, which store_unit undoes).
-__device__ __forceinline__ int perm_col(int i, int ch) {
-  const int g = i >> 2;
-  const int sigma = (g ^ (g >> 1)) & 1;        // 0, 1, 1, 0
-  return 8 * g + 4 * (ch ^ sigma) + (i & 3);
-}
-
-// 16 columns x 16 rows x 64: lane l supplies operand row l % 16 and contraction bytes of group l / 16.
-__device__ __forceinline__ v4i mfma16(const v4i& b, const v4i& a, const v4i& c) {
-  return __builtin_amdgcn_mfma_i32_16x16x64_i8(b, a, c, 0, 0, 0);
-}
-
-// Writes a lane's 16 values of a 32 x 32 sub-tile: element 4 q + r, quadrant q = 2 ch + rh (column half
-// ch, row half rh).  bad: a flagged block of these rows found no residual slot, the rows become NaN.
-__device__ __forceinline__ void store_unit(const GemmParams& p, const float (&acc)[16], int row0, int col0,
-                                           int lane, bool bad) {
-  const int g = lane >> 4;
-  const bool swap = ((g ^ (g >> 1)) & 1) != 0;
-  const int col = col0 + 8 * g;
-#pragma unroll
-  for (int rh = 0; rh < 2; ++rh) {
-    const int row = row0 + 16 * rh + (lane & 15);
-    float v[8];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float x = acc[4 * rh + r], y = acc[8 + 4 * rh + r];   // quadrants (ch 0, rh), (ch 1, rh)
-      v[r] = bad ? __int_as_float(0x7FC00000) : (swap ? y : x);
-      v[4 + r] = bad ? __int_as_float(0x7FC00000) : (swap ? x : y);
-    }
-    if (row >= p.M || col >= p.N) continue;
-    if (p.out_bf16) {
-      uint16_t* dst = reinterpret_cast<uint16_t*>(p.c) + (int64_t)row * p.ldc + col;
-      if (p.vec_ok && col + 8 <= p.N) {
-        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-        typedef float f32x2 __attribute__((ext_vector_type(2)));
-        v4i o;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          f32x2 t = {v[2 * i], v[2 * i + 1]};
-          o[i] = __builtin_bit_cast(int, __builtin_convertvector(t, bf16x2));
-        }
-        *reinterpret_cast<v4i*>(dst) = o;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (col + e < p.N) dst[e] = (uint16_t)float_to_bf16_bits(v[e]);
-      }
-    } else {
-      float* dst = reinterpret_cast<float*>(p.c) + (int64_t)row * p.ldc + col;
-      if (p.vec_ok && col + 8 <= p.N) {
-        reinterpret_cast<float4*>(dst)[0] = make_float4(v[0], v[1], v[2], v[3]);
-        reinterpret_cast<float4*>(dst)[1] = make_float4(v[4], v[5], v[6], v[7]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (col + e < p.N) dst[e] = v[e];
-      }
-    }
-  }
-}
 
 // Keeps a wave-uniform address in scalar registers: loads then take the scalar-base form, and no
 // vector register is written as an address while loads into its neighbours are in flight.
@@ -123,14 +57,6 @@ __device__ __forceinline__ unsigned lane_offset(unsigned v) {
 }
 __device__ __forceinline__ v4i load16(gbl_i8* base, unsigned off, int imm) {
   return *(gbl_v4i*)(base + off + imm);
-}
-
-// Workgroup b of `total` -> its place in the tile order: workgroups are dealt to the XCDs round-robin,
-// so each XCD gets a contiguous run of tiles, whose B blocks then come through one L2.
-__device__ __forceinline__ int xcd_run(int b, int total) {
-  const int xcd = b % kXcds, l = b / kXcds;
-  const int q = total / kXcds, rem = total % kXcds;
-  return xcd * q + min(xcd, rem) + l;
 }
 
 }  // namespace
@@ -167,42 +93,6 @@ __device__ __forceinline__ KLane finish(const GemmParams& p, const KFirst& f) {
 __device__ __forceinline__ int lane_int(int v, int k) { return __builtin_amdgcn_readlane(v, k & 63); }
 __device__ __forceinline__ float lane_float(float v, int k) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k & 63));
-}
-
-// Empty volatile asm: pins the source order of pure instructions without emitting code.
-__device__ __forceinline__ void pin(v4i& x) { asm volatile("" : "+v"(x)); }
-__device__ __forceinline__ void pin(float& a, float& b) { asm volatile("" : "+v"(a), "+v"(b)); }
-
-// One unit: a 32 x 32 sub-tile of one k-block.  kPar: parity of the unit in the wavefront's sequence of
-// units.  Multiplies a with b into P[kPar] and folds the finished tile P[kPar ^ 1] of the unit before
-// it into `acc` with the scale f of that unit: per slot one MFMA, the two FMAs of the elements
-// converted in the slot before, two converts.  extra(n) adds slot n's loads.
-template <int kPar, class Extra>
-__device__ __forceinline__ void unit(v4i (&P)[2][4], const v4i (&b)[2][2], float (&acc)[16], const v4i (&a)[2][2],
-                                     float f, const Extra& extra) {
-  float T[2] = {0.0f, 0.0f};
-#pragma unroll
-  for (int n = 0; n < 8; ++n) {
-    const int ks = n >> 2, q = n & 3, ch = q >> 1, rh = q & 1;
-    const v4i z = {0, 0, 0, 0};
-    P[kPar][q] = mfma16(b[ch][ks], a[rh][ks], ks ? P[kPar][q] : z);
-    extra(n);
-    pin(P[kPar][q]);
-    __builtin_amdgcn_sched_barrier(0);
-    if (n > 0) {
-      acc[2 * n - 2] = __builtin_fmaf(T[0], f, acc[2 * n - 2]);
-      acc[2 * n - 1] = __builtin_fmaf(T[1], f, acc[2 * n - 1]);
-      pin(acc[2 * n - 2], acc[2 * n - 1]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    T[0] = (float)P[kPar ^ 1][n >> 1][2 * (n & 1)];
-    T[1] = (float)P[kPar ^ 1][n >> 1][2 * (n & 1) + 1];
-    pin(T[0], T[1]);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  acc[14] = __builtin_fmaf(T[0], f, acc[14]);
-  acc[15] = __builtin_fmaf(T[1], f, acc[15]);
-  pin(acc[14], acc[15]);
 }
 
 // step(k + d, d, reload) for d in [kFrom, kTo) as long as k + d < end
@@ -462,23 +352,18 @@ __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(GemmParams p
     store_unit(p, acc[u], rg * 32, (cg0 + u) * 32, lane, bad);
 }
 
-int small_tiles(int M, int N, SmallTile tile) {
-  const int r = tile == SmallTile::k32x32 ? 32 : 128;
-  const int c = tile == SmallTile::k32x32 ? 32 : tile == SmallTile::k128x64 ? 64 : 128;
-  return ((M + r - 1) / r) * ((N + c - 1) / c);
-}
-
 hipError_t launch_gemm_small(const GemmParams& p, SmallTile tile, hipStream_t st) {
-  const dim3 grid(small_tiles(p.M, p.N, tile));
+  auto tiles = [&](int r, int c) { return dim3(((p.M + r - 1) / r) * ((p.N + c - 1) / c)); };
   switch (tile) {
-    case SmallTile::k32x32: hipLaunchKernelGGL(gemm_wave_kernel<4>, grid, dim3(64), 0, st, p); break;
+    case SmallTile::k32x32: hipLaunchKernelGGL(gemm_wave_kernel<4>, tiles(32, 32), dim3(64), 0, st, p); break;
     case SmallTile::k128x64:
-      hipLaunchKernelGGL(gemm_tile_kernel<2>, grid, dim3(kTileThreads), 0, st, p, p.nib, (p.N + 63) / 64);
+      hipLaunchKernelGGL(gemm_tile_kernel<2>, tiles(128, 64), dim3(kTileThreads), 0, st, p, p.nib, (p.N + 63) / 64);
       break;
     case SmallTile::k128x128:
-      hipLaunchKernelGGL(gemm_tile_kernel<4>, grid, dim3(kTileThreads), 0, st, p, p.nib, p.njb);
+      hipLaunchKernelGGL(gemm_tile_kernel<4>, tiles(128, 128), dim3(kTileThreads), 0, st, p, p.nib, p.njb);
       break;
     case SmallTile::kNone: break;
+    default: return launch_gemm_ring(p, tile, st);
   }
   return hipGetLastError();
 }

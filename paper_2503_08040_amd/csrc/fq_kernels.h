@@ -132,18 +132,19 @@ struct RmsParams {
 hipError_t launch_quantize(const QuantParams& p, hipStream_t st);
 hipError_t launch_untile(const int8_t* tiled, int rows, int cols, int8_t* dense, hipStream_t st);
 hipError_t launch_gemm(const GemmParams& p, bool debug, hipStream_t st);
-// fq_gemm_tile.hip: the same product on smaller tiles, for outputs that do not fill the chip
-enum class SmallTile { kNone, k32x32, k128x64, k128x128 };
+// The same product on smaller tiles, for outputs that do not fill the chip: fq_gemm_tile.hip and, kRing*,
+// fq_gemm_ring.hip (kRing128x256: pairs of 128 x 128 tiles)
+enum class SmallTile { kNone, k32x32, k128x64, k128x128, kRing128x64, kRing128x128, kRing128x256 };
 hipError_t launch_gemm_small(const GemmParams& p, SmallTile tile, hipStream_t st);
-int small_tiles(int M, int N, SmallTile tile);      // workgroups of it
+hipError_t launch_gemm_ring(const GemmParams& p, SmallTile tile, hipStream_t st);
 // groups of 32 / 64 (and the plain 128 kernel): fq_group.hip
 hipError_t launch_quantize_group(const QuantParams& p, hipStream_t st);
 hipError_t launch_gemm_group(const GemmParams& p, bool debug, hipStream_t st);
 // out = {workgroups with 2x2-block tiles, tile columns they cover, 1x3-block tile columns};
 // cus <= 0: the current device's compute units (or FQ_GEMM_CUS).
 void gemm_tile_plan(int nib, int njb, int cus, int out[3]);
-// out = {SmallTile, its workgroups or those with 2x2-block tiles, 1x3-block tiles over the last block
-// columns, over the last block rows}: what launch_gemm does.
+// out = {0 and those with 2x2-block tiles, or 1, 2, 3 and the number of 32x32, 128x64, 128x128 tiles; 1x3-block
+// tiles over the last block columns, over the last block rows}: what launch_gemm does.
 void gemm_path(int M, int N, int cus, bool biased, int out[4]);
 hipError_t launch_rmsnorm(const RmsParams& p, bool backward, hipStream_t st);
 hipError_t launch_glu(const GluParams& p, bool backward, hipStream_t st);
