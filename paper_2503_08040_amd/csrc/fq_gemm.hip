@@ -40,6 +40,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstdlib>
+#include <type_traits>
 
 #include "fq_device.h"
 #include "fq_kernels.h"
@@ -82,14 +83,17 @@ typedef __attribute__((address_space(3))) void lds_void;
 // of unknown order: with one in flight every wait for an LDS read became a wait for all of them, the
 // ones issued just before included.  Whoever reads the LDS waits with s_waitcnt vmcnt(0) and a barrier.
 // 8192^3 with a fifth of the blocks flagged 678 -> 665 us, 4096 x 4096 x 11008 220.6 -> 217.5.
-__device__ __forceinline__ void stage_quarter_block(const int8_t* src, int8_t* lds_dst, int lane) {
+template <class Dst>
+__device__ __forceinline__ void stage_quarter_block(const int8_t* src, Dst lds_dst, int lane) {
   const unsigned voff = (unsigned)lane * 16u;
   // make the uniformity of the base explicit (folds away when it is already scalar)
   const uint64_t a = reinterpret_cast<uint64_t>(src);
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
   uint64_t base = ((uint64_t)hi << 32) | lo;
-  const uint32_t to = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)lds_dst);
+  uint32_t to;
+  if constexpr (std::is_pointer_v<Dst>) to = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)lds_dst);
+  else to = __builtin_amdgcn_readfirstlane(lds_dst);
 #ifdef FQ_ABLATE_NO_DMA
   if (voff != 0xFFFFFFFFu) return;
 #endif
@@ -108,7 +112,8 @@ __device__ __forceinline__ void stage_quarter_block(const int8_t* src, int8_t* l
 #pragma clang diagnostic pop
 }
 // 8 KiB
-__device__ __forceinline__ void stage_half_block(const int8_t* src, int8_t* lds_dst, int lane) {
+template <class Dst>
+__device__ __forceinline__ void stage_half_block(const int8_t* src, Dst lds_dst, int lane) {
   stage_quarter_block(src, lds_dst, lane);
   stage_quarter_block(src + 4 * kFragBytes, lds_dst + 4 * kFragBytes, lane);
 }
@@ -138,6 +143,10 @@ __device__ inline v4i lds_frag(const int8_t* blk, int rg, int rh, int ks, int la
 // freely movable pure instructions (MFMA, convert, FMA) without emitting any code.
 __device__ __forceinline__ void pin(v4i& x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void pin(float& a, float& b) { asm volatile("" : "+v"(a), "+v"(b)); }
+// acc += s * t, s uniform.
+__device__ __forceinline__ void fma_in_place(float& acc, float s, float t) {
+  asm volatile("v_fmac_f32_e32 %0, %1, %2" : "+v"(acc) : "s"(s), "v"(t));
+}
 
 // Geometry of a workgroup tile: kBI x kBJ quantization blocks, computed by 8 wavefronts laid
 // out 2 (row halves h) x 4 (column groups c).  Wavefront (h, c) owns rows [64h, 64h+64) of every
@@ -278,9 +287,8 @@ __device__ __forceinline__ void run_unit(WaveState<G>& st, const int8_t* a_cur, 
       const int fsi = prev ? kLastSi : fu / kSJ, fsj = prev ? pu % kSJ : fu % kSJ;
       const float s = prev ? sp[G::kSP == 1 ? 0 : pu - (kUnits - 2)]
                            : sc.s[G::kSC == 1 ? 0 : fsj];
-      st.acc[fsi][fsj][fe] = __builtin_fmaf(st.T[0], s, st.acc[fsi][fsj][fe]);
-      st.acc[fsi][fsj][fe + 1] = __builtin_fmaf(st.T[1], s, st.acc[fsi][fsj][fe + 1]);
-      pin(st.acc[fsi][fsj][fe], st.acc[fsi][fsj][fe + 1]);
+      fma_in_place(st.acc[fsi][fsj][fe], s, st.T[0]);
+      fma_in_place(st.acc[fsi][fsj][fe + 1], s, st.T[1]);
     }
     if constexpr (!kBiased) {
       __builtin_amdgcn_sched_barrier(0);   // FMAs before converts
@@ -368,7 +376,7 @@ constexpr int kMagicBits = 0x4B200000;          // 1.25 * 2^23 as binary32: with
                                                 // stays inside [2^23, 2^24), where one ulp is 1
 constexpr float kMagic = 10485760.0f;
 
-template <class G, bool kBiased>
+template <class G, bool kBiased, bool kFb = true>
 __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int jb_first,
                                           int8_t* lds) {
   constexpr int kBI = G::kBI, kBJ = G::kBJ, kSI = G::kSI, kSJ = G::kSJ, kUnits = G::kUnits;
@@ -379,6 +387,9 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
 #endif
   int8_t* const a_ring = lds;                    // [2][kBI blocks]
   int8_t* const b_ring = lds + 2 * G::kASet;     // [2][kBJ blocks]
+  // The rings as the loads take them.  (The biased kernel has no registers to spare: it converts the pointer
+  // each time, which costs the others 1 %.)
+  const uint32_t a_lds = (uint32_t)(uintptr_t)(lds_void*)a_ring, b_lds = a_lds + 2 * G::kASet;
 
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -413,7 +424,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
   const int8_t* const smain = (stage_a ? p.a_codes : p.b_codes) +
                               (int64_t)sblk * p.nkb * kBlockBytes + spart;
 
-  const bool has_fb = p.a_slot != nullptr;
+  const bool has_fb = kFb && p.a_slot != nullptr;
   int ia[kBI];
 #pragma unroll
   for (int i = 0; i < kBI; ++i) ia[i] = ib[i] * p.a_si;
@@ -450,10 +461,10 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
     kc.slot = slot[0];
 #pragma unroll
     for (int i = 0; i < kBI; ++i) {
-      kc.flagged[i] = __ballot(in && slot[i] >= 0);
+      kc.flagged[i] = kFb ? __ballot(in && slot[i] >= 0) : 0ull;
       if (kSkew ? h == i : sidx == i) kc.slot = slot[i];
     }
-    poison |= __ballot(in && own == -2) != 0;
+    if (kFb) poison |= __ballot(in && own == -2) != 0;
 #pragma unroll
     for (int q = 0; q < G::kSC; ++q) {
       kc.s[q] = sa * sb[q];
@@ -467,12 +478,12 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
     KRec<G> r;
     const int l = k & 63;
 #pragma unroll
-    for (int i = 0; i < kBI; ++i) r.flagged[i] = k < nkb && ((kc.flagged[i] >> l) & 1) != 0;
-    r.slot = __builtin_amdgcn_readlane(kc.slot, l);
+    for (int i = 0; i < kBI; ++i) r.flagged[i] = kFb && k < nkb && ((kc.flagged[i] >> l) & 1) != 0;
+    r.slot = kFb ? __builtin_amdgcn_readlane(kc.slot, l) : -1;
 #pragma unroll
     for (int q = 0; q < G::kSC; ++q) {
       r.s[q] = lane_float(kc.s[q], l);
-      r.t[q] = lane_float(kc.t[q], l);
+      r.t[q] = kFb ? lane_float(kc.t[q], l) : 0.0f;
     }
     return r;
   };
@@ -480,7 +491,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
     bool f = false;
 #pragma unroll
     for (int i = 0; i < kBI; ++i) f |= r.flagged[i];
-    return f;
+    return kFb && f;
   };
   // Stages this wave's 8 KiB share of item (k, res) into ring slot `asel` (A) / k & 1 (B).
   auto stage_item = [&](int k, int res, const KRec<G>& r, int asel, bool new_b) {
@@ -498,7 +509,8 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
 #ifdef FQ_ABLATE_DMA_HOT
       src = p.a_codes + (reinterpret_cast<uintptr_t>(src) & 0xFE000u);
 #endif
-      stage_half_block(src, a_ring + asel * G::kASet + soff, lane);
+      if constexpr (kBiased) stage_half_block(src, a_ring + asel * G::kASet + soff, lane);
+      else stage_half_block(src, a_lds + asel * G::kASet + soff, lane);
 #ifdef FQ_ABLATE_ONE_STAGER
       stage_half_block(src + kBlockBytes / 2, a_ring + asel * G::kASet + soff + kBlockBytes / 2, lane);
 #endif
@@ -507,7 +519,8 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
       stage_half_block(p.a_codes + (reinterpret_cast<uintptr_t>(smain + (int64_t)k * kBlockBytes) & 0xFE000u),
                        b_ring + (k & 1) * G::kBSet + soff, lane);
 #else
-      stage_half_block(smain + (int64_t)k * kBlockBytes, b_ring + (k & 1) * G::kBSet + soff, lane);
+      if constexpr (kBiased) stage_half_block(smain + (int64_t)k * kBlockBytes, b_ring + (k & 1) * G::kBSet + soff, lane);
+      else stage_half_block(smain + (int64_t)k * kBlockBytes, b_lds + (k & 1) * G::kBSet + soff, lane);
 #endif
 #ifdef FQ_ABLATE_ONE_STAGER
       stage_half_block(smain + (int64_t)k * kBlockBytes + kBlockBytes / 2,
@@ -612,7 +625,9 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
         stage_half_block(p.a_codes + (reinterpret_cast<uintptr_t>(smain + (int64_t)late_b_k * kBlockBytes) & 0xFE000u),
                          b_ring + (late_b_k & 1) * G::kBSet + soff, lane);
 #else
-        stage_half_block(smain + (int64_t)late_b_k * kBlockBytes, b_ring + (late_b_k & 1) * G::kBSet + soff, lane);
+        if constexpr (kBiased)
+          stage_half_block(smain + (int64_t)late_b_k * kBlockBytes, b_ring + (late_b_k & 1) * G::kBSet + soff, lane);
+        else stage_half_block(smain + (int64_t)late_b_k * kBlockBytes, b_lds + (late_b_k & 1) * G::kBSet + soff, lane);
 #endif
       }
       late_b_k = -1;
@@ -839,6 +854,25 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmParams p) {
   } else {
     tile_of(blockIdx.x - p.n_main, p.tail_ni, p.tail_tj, ti, tj);
     tile_body<Geo<1, 3>, false>(p, p.tail_i0 + ti, p.tail_j0 + 3 * tj, lds);
+  }
+}
+
+// gemm_kernel for an A operand that cannot fall back (gradients of the paper's recipe, activations quantized
+// without a criterion): every item is a k-block, there is no branch around the units and no path to join behind
+// them, and a third of the scalar instructions of an item are gone, all of which sat around its barrier, where no
+// wavefront has anything else to issue.  Same bits; bf16 output unless said, us, gemm_kernel before -> here:
+// 4096 x 4096 x 11008 202 -> 190, 4096 x 11008 x 4096 as NN 185 -> 174, 11008 x 4096 x 4096 as TN with binary32
+// output 215 -> 203, 8192^3 545 -> 511.  (Working out an item's addresses in the slots of an early unit, where the
+// other wavefront of the SIMD leaves issue cycles free, took the rest of the scalars from the barrier and gave nothing.)
+__global__ __launch_bounds__(kThreads, 2) void gemm_main_kernel(GemmParams p) {
+  extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
+  int ti, tj;
+  if ((int)blockIdx.x < p.n_main) {
+    tile_of(blockIdx.x, p.main_ti, p.main_tj, ti, tj);
+    tile_body<Geo<2, 2>, false, false>(p, 2 * ti, 2 * tj, lds);
+  } else {
+    tile_of(blockIdx.x - p.n_main, p.tail_ni, p.tail_tj, ti, tj);
+    tile_body<Geo<1, 3>, false, false>(p, p.tail_i0 + ti, p.tail_j0 + 3 * tj, lds);
   }
 }
 
@@ -1080,10 +1114,14 @@ hipError_t launch_gemm(const GemmParams& p_in, bool debug, hipStream_t st) {
     if (e == hipSuccess)
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_biased_kernel),
                               hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_main_kernel),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
     if (e != hipSuccess) return e;
     attr_set[dev].store(true, std::memory_order_release);
   }
   if (p.biased) hipLaunchKernelGGL(gemm_biased_kernel, dim3(grid), dim3(kThreads), kLdsBytes, st, p);
+  else if (!p.a_slot) hipLaunchKernelGGL(gemm_main_kernel, dim3(grid), dim3(kThreads), kLdsBytes, st, p);
   else hipLaunchKernelGGL(gemm_kernel, dim3(grid), dim3(kThreads), kLdsBytes, st, p);
   return hipGetLastError();
 }

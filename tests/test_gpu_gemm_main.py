@@ -1,0 +1,41 @@
+"""GPU parity of the large tiles for an A operand without fallback (the kernel that has no residual items) against the
+CPU oracle, bit for bit, in both geometries, and against the kernel with residual items on the same codes."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import paper_2503_08040_amd as fq
+from oracle import fqo
+from tests import gpu_util as gu
+from tests.test_gpu_gemm_tile import NN, NT, TN, _operands
+
+# (rows, columns, compute units assumed): one 256 x 256 tile, ragged; 128 x 384 tiles over the last block columns,
+# and over the last block rows
+TILES = {"one": (250, 256, 1), "column tail": (129, 1589, 4), "row tail": (1275, 253, 2)}
+
+
+# contraction lengths: one and two k-blocks (the prologue alone), odd, and around the 64 whose scales are held at a time
+@pytest.mark.parametrize("tile", list(TILES))
+@pytest.mark.parametrize("op,K", [(NT, 100), (NN, 256), (TN, 384), (NT, 8192), (NN, 8300), (TN, 16500)])
+def test_large_tiles_without_fallback(tile, op, K, monkeypatch):
+    Mo, No, cus = TILES[tile]
+    monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
+    path = fq.fq_gemm_path(Mo, No)
+    assert path[0] == fq.FQ_TILES_256x256 and (path[2] > 0, path[3] > 0) == ("column" in tile, "row" in tile), path
+    a, b = _operands(op, Mo, No, K, K + Mo + op, 4)
+    at, bt = op == TN, op in (NN, TN)
+    ga = fq.fq_quantize(gu.to_device_bf16(a), fq.FQ_CRIT_NONE, 0.0, capacity=0, want_transposed=at)
+    gb = fq.fq_quantize(gu.to_device_bf16(b), fq.FQ_CRIT_NONE, 0.0, capacity=0, want_transposed=bt)
+    gu.announce(f"large tiles without fallback, {tile} op={op} {Mo}x{No} K={K}")
+    ref, refb = fqo.gemm(op, fqo.quantize(a, 128, fqo.CRIT_NONE, 0.0), fqo.quantize(b, 128, fqo.CRIT_NONE, 0.0),
+                         want_bf16=True)
+    c = fq.fq_gemm(op, ga, gb)
+    assert np.array_equal(c.cpu().numpy(), ref)
+    got = fq.fq_gemm(op, ga, gb, out_dtype=torch.bfloat16).view(torch.int16).cpu().numpy().view(np.uint16)
+    assert np.array_equal(got, refb)
+    # the same codes with residual slots that nobody uses: the other kernel
+    gf = fq.fq_quantize(gu.to_device_bf16(a), fq.FQ_CRIT_ABSMAX_GT, float("inf"), want_transposed=at)
+    assert torch.equal(fq.fq_gemm(op, gf, gb), c)
