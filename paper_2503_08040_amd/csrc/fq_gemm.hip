@@ -17,16 +17,17 @@
 //     would leave the final round of the chip mostly idle;
 //   - the k-loop runs over "items": the main product of k-block k and, when
 //     one of the tile's A blocks is flagged at k, a residual item right
-//     after it.  A and B operands sit in two independent double-buffered LDS
-//     rings (64 KiB each for 2 x 2): an item always brings a new A set (codes or
-//     residual codes), a new B set only when k advances, so the residual
+//     after it.  A and B operands sit in two double-buffered LDS rings (64 KiB
+//     each for 2 x 2) that advance with k; the residual
 //     product re-uses the B blocks already on chip exactly as Alg. 1 says.
+//     The residual A blocks have 32 KiB of their own.
 //     A residual item is work only for the wavefronts whose i-block is flagged
-//     at that k: the others skip its multiplications (they still take part in
-//     staging and in the barrier), so with one of the two blocks flagged the
-//     item runs on one wavefront per SIMD and costs about 60 % of a full item;
+//     at that k: the others wait at the barrier behind it, so with one of
+//     the two blocks flagged the item runs on one wavefront per SIMD and costs
+//     half of a full item;
 //   - operands reach LDS by direct global->LDS 16-byte loads (blocks are stored
-//     in operand order, see fq.h), one barrier per item;
+//     in operand order, see fq.h), one barrier per k-block and one more where
+//     there are residual blocks;
 //   - per 32 x 32 sub-tile: 8 v_mfma_i32_16x16x64_i8 (four 16 x 16 quadrants x
 //     two halves of K = 128) into an INT32 tile, then one convert + one FMA per
 //     element folds it into the FP32 accumulators with the scalar scale of that
@@ -71,10 +72,13 @@ constexpr int kMaxDevices = 64;   // per-device host-side caches
 constexpr int kXcds = 8;      // accelerator complex dies, each with a private L2
 constexpr int kGroupN = 4;    // tile columns per rasterization group
 constexpr int kRingBytes = 2 * kBlockBytes;     // one A pair or one B pair
-constexpr int kLdsBytes = 4 * kRingBytes;       // 128 KiB: two A sets + two B sets; the epilogue
-                                                // staging patches re-use the same memory
+constexpr int kLdsBytes = 5 * kRingBytes;       // all 160 KiB: two A sets, two B sets, the residual blocks of an
+                                                // A set; the epilogue staging patches re-use the same memory
 
 typedef __attribute__((address_space(3))) void lds_void;
+
+// Address of a __shared__ object as the LDS instructions take it.
+__device__ __forceinline__ uint32_t lds_address(int8_t* q) { return (uint32_t)(uintptr_t)(lds_void*)q; }
 
 // One wavefront copies 4 KiB (4 fragments) global -> LDS with direct loads.  `src` and `lds_dst` are
 // wave-uniform; the per-lane part of the address is the 32-bit offset lane*16 (scalar-base form), and
@@ -83,17 +87,14 @@ typedef __attribute__((address_space(3))) void lds_void;
 // of unknown order: with one in flight every wait for an LDS read became a wait for all of them, the
 // ones issued just before included.  Whoever reads the LDS waits with s_waitcnt vmcnt(0) and a barrier.
 // 8192^3 with a fifth of the blocks flagged 678 -> 665 us, 4096 x 4096 x 11008 220.6 -> 217.5.
-template <class Dst>
-__device__ __forceinline__ void stage_quarter_block(const int8_t* src, Dst lds_dst, int lane) {
+__device__ __forceinline__ void stage_quarter_block(const int8_t* src, uint32_t lds_dst, int lane) {
   const unsigned voff = (unsigned)lane * 16u;
   // make the uniformity of the base explicit (folds away when it is already scalar)
   const uint64_t a = reinterpret_cast<uint64_t>(src);
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
   uint64_t base = ((uint64_t)hi << 32) | lo;
-  uint32_t to;
-  if constexpr (std::is_pointer_v<Dst>) to = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)lds_dst);
-  else to = __builtin_amdgcn_readfirstlane(lds_dst);
+  const uint32_t to = __builtin_amdgcn_readfirstlane(lds_dst);
 #ifdef FQ_ABLATE_NO_DMA
   if (voff != 0xFFFFFFFFu) return;
 #endif
@@ -112,8 +113,7 @@ __device__ __forceinline__ void stage_quarter_block(const int8_t* src, Dst lds_d
 #pragma clang diagnostic pop
 }
 // 8 KiB
-template <class Dst>
-__device__ __forceinline__ void stage_half_block(const int8_t* src, Dst lds_dst, int lane) {
+__device__ __forceinline__ void stage_half_block(const int8_t* src, uint32_t lds_dst, int lane) {
   stage_quarter_block(src, lds_dst, lane);
   stage_quarter_block(src + 4 * kFragBytes, lds_dst + 4 * kFragBytes, lane);
 }
@@ -175,7 +175,7 @@ struct Geo {
   // wavefront's 32-row groups: its i-block and its row group inside that block.
   __device__ static constexpr int a_block(int h, int /*si*/) { return kBI == 2 ? h : 0; }
   __device__ static constexpr int a_group(int h, int si) { return kBI == 2 ? si : 2 * h + si; }
-  static_assert(2 * (kASet + kBSet) <= kLdsBytes, "operand rings must fit");
+  static_assert(3 * kASet + 2 * kBSet <= kLdsBytes, "operand rings and residual blocks must fit");
   static_assert(8 * kStageBytesPerWave <= kLdsBytes, "epilogue staging must fit");
   static_assert(kBI + kBJ == 4, "8 wavefronts stage 8 half-blocks per item");
 };
@@ -339,13 +339,14 @@ __device__ __forceinline__ void drain(WaveState<G>& st, const float (&sp)[G::kSP
   st.acc[kLastSi][kSJ - 1][15] = __builtin_fmaf(st.T[1], s, st.acc[kLastSi][kSJ - 1][15]);
 }
 
-// Scalars of one k-block as a wavefront needs them: which A blocks of the tile are flagged, the
-// residual slot of the A block it stages, and per scale column of its own i-block a^A a^B and a~^A a^B.
+// Scalars of one k-block as a wavefront needs them: whether its own A block is flagged (bit 0) and whether any
+// of the tile's is (bit 1), the residual slot of the A block it stages (-1: none, or it stages B), and per scale
+// column of its own i-block a^A a^B and a~^A a^B, as bit patterns (a choice between floats would be made by the
+// vector unit).
 template <class G>
 struct KRec {
-  bool flagged[G::kBI];
-  int slot;
-  float s[G::kSC], t[G::kSC];
+  int flags, slot;
+  int s[G::kSC], t[G::kSC];
 };
 
 // The same of 64 consecutive k-blocks, one per lane (flags: one per bit).  Read back with v_readlane
@@ -355,8 +356,7 @@ struct KRec {
 // 196.5 us, 4096 x 16384 x 4096 as TN 301 -> 291, 8192^3 (NT, a fifth of the blocks flagged) 712 -> 704.
 template <class G>
 struct KChunk {
-  unsigned long long flagged[G::kBI];
-  int slot;
+  int flags, slot;
   float s[G::kSC], t[G::kSC];
 };
 
@@ -376,6 +376,18 @@ constexpr int kMagicBits = 0x4B200000;          // 1.25 * 2^23 as binary32: with
                                                 // stays inside [2^23, 2^24), where one ulp is 1
 constexpr float kMagic = 10485760.0f;
 
+#ifdef FQ_ABLATE_EXTRA_SALU
+__device__ __forceinline__ void extra_salu(int chain) {
+#pragma unroll
+  for (int i = 0; i < FQ_ABLATE_EXTRA_SALU; ++i) asm volatile("s_add_i32 %0, %0, 1" : "+s"(chain));
+  asm volatile("" ::"s"(chain));
+}
+#endif
+
+// Where the residual blocks of the tile's A blocks lie in LDS.
+template <class G>
+constexpr int kResOffset = 2 * (G::kASet + G::kBSet);
+
 template <class G, bool kBiased, bool kFb = true>
 __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int jb_first,
                                           int8_t* lds) {
@@ -387,9 +399,6 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
 #endif
   int8_t* const a_ring = lds;                    // [2][kBI blocks]
   int8_t* const b_ring = lds + 2 * G::kASet;     // [2][kBJ blocks]
-  // The rings as the loads take them.  (The biased kernel has no registers to spare: it converts the pointer
-  // each time, which costs the others 1 %.)
-  const uint32_t a_lds = (uint32_t)(uintptr_t)(lds_void*)a_ring, b_lds = a_lds + 2 * G::kASet;
 
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -458,12 +467,14 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
 #pragma unroll
     for (int i = 1; i < kBI; ++i) if (G::a_block(h, 0) == i) own = slot[i];
     const float rs = has_fb ? p.a_res_scales[max(own, 0)] : 0.0f;
-    kc.slot = slot[0];
+    kc.slot = -1;
+    int any = -1;
 #pragma unroll
     for (int i = 0; i < kBI; ++i) {
-      kc.flagged[i] = kFb ? __ballot(in && slot[i] >= 0) : 0ull;
-      if (kSkew ? h == i : sidx == i) kc.slot = slot[i];
+      any = max(any, slot[i]);
+      if (kSkew ? h == i : stage_a && sidx == i) kc.slot = slot[i];
     }
+    kc.flags = kFb && in ? (own >= 0 ? 1 : 0) | (any >= 0 ? 2 : 0) : 0;
     if (kFb) poison |= __ballot(in && own == -2) != 0;
 #pragma unroll
     for (int q = 0; q < G::kSC; ++q) {
@@ -471,62 +482,38 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
       kc.t[q] = rs * sb[q];
     }
   };
-  auto lane_float = [](float v, int l) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-  };
-  auto rec_of = [&](int k) -> KRec<G> {      // k in the chunk that is loaded, or >= nkb
+  auto lane_bits = [](float v, int l) { return __builtin_amdgcn_readlane(__float_as_int(v), l); };
+  // k in the chunk that is loaded; behind the last k-block flags and slot mean nothing
+  auto rec_of = [&](int k) -> KRec<G> {
     KRec<G> r;
-    const int l = k & 63;
-#pragma unroll
-    for (int i = 0; i < kBI; ++i) r.flagged[i] = kFb && k < nkb && ((kc.flagged[i] >> l) & 1) != 0;
-    r.slot = kFb ? __builtin_amdgcn_readlane(kc.slot, l) : -1;
+    r.flags = kFb ? __builtin_amdgcn_readlane(kc.flags, k & 63) : 0;
+    r.slot = kFb ? __builtin_amdgcn_readlane(kc.slot, k & 63) : -1;
 #pragma unroll
     for (int q = 0; q < G::kSC; ++q) {
-      r.s[q] = lane_float(kc.s[q], l);
-      r.t[q] = kFb ? lane_float(kc.t[q], l) : 0.0f;
+      r.s[q] = lane_bits(kc.s[q], k & 63);
+      r.t[q] = kFb ? lane_bits(kc.t[q], k & 63) : 0;
     }
     return r;
   };
-  auto any_flagged = [&](const KRec<G>& r) {
-    bool f = false;
-#pragma unroll
-    for (int i = 0; i < kBI; ++i) f |= r.flagged[i];
-    return kFb && f;
-  };
-  // Stages this wave's 8 KiB share of item (k, res) into ring slot `asel` (A) / k & 1 (B).
-  auto stage_item = [&](int k, int res, const KRec<G>& r, int asel, bool new_b) {
+  // This wave's 8 KiB share of k-block k into its ring, or of residual slot `slot` behind the rings.
+  auto stage_share = [&](const int8_t* src, uint32_t dst) {
 #ifdef FQ_ABLATE_ONE_STAGER
     if (!stager) return;
 #endif
-    if (stage_a) {
-      const int8_t* src;
-      if (res) {
-        if (r.slot < 0) return;   // unflagged block: nothing to bring (its wavefronts skip the item)
-        src = p.a_res + (int64_t)r.slot * kBlockBytes + spart;
-      } else {
-        src = smain + (int64_t)k * kBlockBytes;
-      }
 #ifdef FQ_ABLATE_DMA_HOT
-      src = p.a_codes + (reinterpret_cast<uintptr_t>(src) & 0xFE000u);
+    src = p.a_codes + (reinterpret_cast<uintptr_t>(src) & 0xFE000u);
 #endif
-      if constexpr (kBiased) stage_half_block(src, a_ring + asel * G::kASet + soff, lane);
-      else stage_half_block(src, a_lds + asel * G::kASet + soff, lane);
+    stage_half_block(src, dst, lane);
 #ifdef FQ_ABLATE_ONE_STAGER
-      stage_half_block(src + kBlockBytes / 2, a_ring + asel * G::kASet + soff + kBlockBytes / 2, lane);
+    stage_half_block(src + kBlockBytes / 2, dst + kBlockBytes / 2, lane);
 #endif
-    } else if (new_b) {
-#ifdef FQ_ABLATE_DMA_HOT
-      stage_half_block(p.a_codes + (reinterpret_cast<uintptr_t>(smain + (int64_t)k * kBlockBytes) & 0xFE000u),
-                       b_ring + (k & 1) * G::kBSet + soff, lane);
-#else
-      if constexpr (kBiased) stage_half_block(smain + (int64_t)k * kBlockBytes, b_ring + (k & 1) * G::kBSet + soff, lane);
-      else stage_half_block(smain + (int64_t)k * kBlockBytes, b_lds + (k & 1) * G::kBSet + soff, lane);
-#endif
-#ifdef FQ_ABLATE_ONE_STAGER
-      stage_half_block(smain + (int64_t)k * kBlockBytes + kBlockBytes / 2,
-                       b_ring + (k & 1) * G::kBSet + soff + kBlockBytes / 2, lane);
-#endif
-    }
+  };
+  const uint32_t lds0 = lds_address(lds);
+  const uint32_t my_ring = lds0 + (stage_a ? 0 : 2 * G::kASet) + soff;
+  const int my_set = stage_a ? G::kASet : G::kBSet;
+  auto stage_main = [&](int k) { stage_share(smain + (int64_t)k * kBlockBytes, my_ring + (k & 1 ? my_set : 0)); };
+  auto stage_res = [&](int slot) {
+    stage_share(p.a_res + (int64_t)slot * kBlockBytes + spart, lds0 + kResOffset<G> + soff);
   };
   // kSkew: this wavefront's share of item (k, res) when the two teams (h = 0, 1: the wavefronts
   // of i-block h, one per SIMD each) run half an item apart: a quarter of its own team's A block,
@@ -536,7 +523,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
 #pragma unroll
     for (int i = 1; i < kBI; ++i) if (h == i) blk = ib[i];
     const int quarter = c * (kBlockBytes / 4);
-    int8_t* const dst = a_ring + asel * G::kASet + h * kBlockBytes + quarter;
+    const uint32_t dst = lds_address(a_ring) + asel * G::kASet + h * kBlockBytes + quarter;
     if (!res) stage_quarter_block(p.a_codes + ((int64_t)blk * p.nkb + k) * kBlockBytes + quarter, dst, lane);
     else if (r.slot >= 0) stage_quarter_block(p.a_res + (int64_t)r.slot * kBlockBytes + quarter, dst, lane);
     if (h == 0 && new_b) {
@@ -545,7 +532,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
       for (int j = 1; j < kBJ; ++j) if ((c >> 1) == j) jb = jbt[j];
       const int part = (c >> 1) * kBlockBytes + (c & 1) * (kBlockBytes / 2);
       stage_half_block(p.b_codes + ((int64_t)jb * p.nkb + k) * kBlockBytes + (c & 1) * (kBlockBytes / 2),
-                       b_ring + (k & 1) * G::kBSet + part, lane);
+                       lds_address(b_ring) + (k & 1) * G::kBSet + part, lane);
     }
   };
   WaveState<G> st;
@@ -576,20 +563,21 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
   };
 
   if (nkb > 0) {
-    // ---- prologue: items 0 and 1 into the two ring slots
-    int k = 0, res = 0, t = 0;
+    // ---- prologue: k-blocks 0 and 1 into the two ring slots, and the residual blocks of k-block 0
+    int k = 0, res = 0;
+    [[maybe_unused]] int t = 0;
     KRec<G> r0{}, r1;      // k-blocks k and k + 1
     if constexpr (kSkew) stage_team(0, 0, r0, 0, true);
-    else stage_item(0, 0, r0, 0, true);
+    else stage_main(0);
     load_chunk(0);
     r0 = rec_of(0);
     r1 = rec_of(1);
     if constexpr (kSkew) {
-      if (any_flagged(r0)) stage_team(0, 1, r0, 1, false);
+      if (r0.flags) stage_team(0, 1, r0, 1, false);
       else if (1 < nkb) stage_team(1, 0, r1, 1, true);
     } else {
-      if (any_flagged(r0)) stage_item(0, 1, r0, 1, false);
-      else if (1 < nkb) stage_item(1, 0, r1, 1, true);
+      if (r0.slot >= 0) stage_res(r0.slot);
+      if (1 < nkb) stage_main(1);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);    // vmcnt(0): this wave's direct-to-LDS loads landed
     __syncthreads();
@@ -611,119 +599,151 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
 #pragma unroll
     for (int i = 0; i < G::kSP; ++i) sp[i] = 0.0f;
 
-    int late_b_k = -1;     // B stagers: k-block whose B set is still to be requested (-1: none)
-    if (kSkew && h == 1) asm volatile("s_barrier" ::: "memory");   // team 1 starts one barrier later
-    for (;;) {
-      // The B stagers request their blocks here, two units after the barrier that freed the
-      // ring slot, not right behind it: right after the barrier the four A stagers (one per
-      // SIMD) are blocked on their eight load instructions each, and while they wait for the
-      // address unit to take them, the B stagers, which share their SIMDs, run the last two
-      // units of the item.  With all 64 loads issued at once, both wavefronts of every SIMD sat
-      // blocked and the matrix cores idled for about a fifth of every item.
-      if (late_b_k >= 0) {
-#ifdef FQ_ABLATE_DMA_HOT
-        stage_half_block(p.a_codes + (reinterpret_cast<uintptr_t>(smain + (int64_t)late_b_k * kBlockBytes) & 0xFE000u),
-                         b_ring + (late_b_k & 1) * G::kBSet + soff, lane);
-#else
-        if constexpr (kBiased)
-          stage_half_block(smain + (int64_t)late_b_k * kBlockBytes, b_ring + (late_b_k & 1) * G::kBSet + soff, lane);
-        else stage_half_block(smain + (int64_t)late_b_k * kBlockBytes, b_lds + (late_b_k & 1) * G::kBSet + soff, lane);
-#endif
-      }
-      late_b_k = -1;
-      // ---- the items after this one (all wave-uniform scalar logic)
-      const bool n1res = !res && any_flagged(r0);
-      const int n1k = n1res ? k : k + 1;
-      const bool has1 = n1k < nkb;
-      const bool n2res = !n1res && any_flagged(r1);
-      const int n2k = (n1res || n2res) ? k + 1 : k + 2;
-      const bool has2 = n2k < nkb;
-
-      // ---- this wavefront's i-block in this item: is it flagged, its scales
-      bool mine = r0.flagged[0];
+    auto after_units = [&](const ItemScales<G>& sc) {
 #pragma unroll
-      for (int i = 1; i < kBI; ++i)
-        if (G::a_block(h, 0) == i) mine = r0.flagged[i];
-      // a residual item is work only for the wavefronts whose i-block is flagged at this k
+      for (int i = 0; i < G::kSP; ++i) sp[i] = sc.s[G::kSC == 1 ? 0 : kSJ - 2 + i];
+      if constexpr (kBiased) {
+#pragma unroll
+        for (int q = 0; q < G::kSC; ++q) bias_s[q] += sc.s[q];
+        if (++bias_items == kBiasWindow) {
+          // fold the pending unit, take the bias out, and restart the pipeline: the next unit 0
+          // folds the same tile again with scale 0, which adds nothing
+          drain<G, true>(st, sp);
+          remove_bias();
+#pragma unroll
+          for (int i = 0; i < G::kSP; ++i) sp[i] = 0.0f;
+        }
+      }
+    };
+    auto next_k = [&]() {
+      ++k;
+      r0 = r1;
+      if (__builtin_expect(((k + 1) & 63) == 0, 0)) {
+        if (k + 1 < nkb) load_chunk(k + 1);
+      }
+      r1 = rec_of(k + 1);
+    };
 #ifdef FQ_ABLATE_NO_MULTIPLY
-      const bool active = p.M < 0;
+    const bool multiply = p.M < 0;
 #else
-      const bool active = !res || mine;
+    constexpr bool multiply = true;
 #endif
+    if constexpr (!kSkew) {
+      // One turn is the main product of k-block k or, for the wavefronts whose i-block is flagged at k, its
+      // residual product behind it: the same code, with the A operands from the residual blocks instead of the
+      // ring and without the ring's barrier.  The end of a k-block with residual blocks is one more barrier, which the
+      // wavefronts without one go to at once, and behind which its B blocks and the residual blocks may be
+      // overwritten.  A turn fetches the first operands of the wavefront's own next turn.
+      // What a wavefront does between its units it does while the others do the same and the matrix cores
+      // idle, some 9 cycles per dependent scalar instruction: addresses and parities are carried along instead of
+      // worked out, one v_readlane brings a k-block's flags, choices are made between integers.  And one body for both
+      // kinds of turn leaves no paths to join that hold operands (a branch around the units and a fetch
+      // beside them took all 256 registers, this 231).  Against that form, us: 4096 x 4096 x 11008 215 -> 205, 4096 x
+      // 11008 x 4096 197 -> 188 (5 % of the blocks flagged), 8192^3 665 -> 639 (a fifth), 545 -> 508 without residual
+      // items; gemm_biased_kernel 4096 x 4096 x 11008 190 -> 180.
+      const int a_sum = G::kASet, b0 = 2 * G::kASet, b_sum = 2 * b0 + G::kBSet;     // offset in LDS of the other slot = sum - it
+      int a_at = 0, a_ring_at = 0, b_at = b0;       // A operands of this turn; ring slots of k-block k
+      // what this wavefront requests next: A k-block k + 2, behind the barrier of k; B k-block k + 1, at the top of
+      // the turn behind, if it has not been requested
+      const int8_t* src = smain + (stage_a ? 2 : 1) * kBlockBytes;
+      const uint32_t dst_sum = 2 * my_ring + my_set;
+      uint32_t dst = stage_a ? my_ring : my_ring + my_set;
+      int late = 0, left = nkb - 2;                // k-blocks behind k + 1
+      int cur[G::kSC];
+#pragma unroll
+      for (int q = 0; q < G::kSC; ++q) cur[q] = r0.s[q];
+      for (;;) {
+        // The B stagers request their blocks here, two units after the barrier that freed the
+        // ring slot, not right behind it: right after the barrier the four A stagers (one per
+        // SIMD) are blocked on their eight load instructions each, and while they wait for the
+        // address unit to take them, the B stagers, which share their SIMDs, run the last two
+        // units of the item.  With all 64 loads issued at once, both wavefronts of every SIMD sat
+        // blocked and the matrix cores idled for about a fifth of every item.
+        if (late) stage_share(src, dst);
+        late = 0;
+        ItemScales<G> sc;
+#pragma unroll
+        for (int q = 0; q < G::kSC; ++q) sc.s[q] = __int_as_float(cur[q]);
+        const int8_t* const a_cur = lds + a_at;
+        if (multiply) run_units_range<G, 0, kUnits - 2, kBiased>(st, a_cur, a_cur, b_ring, h, c, lane, sc, sp, magic);
+        if (!kFb || !res) {
+          // All LDS reads of this k-block are issued (the last two units run from registers).  Wait
+          // for them and for the next one's direct-to-LDS loads, then the barrier publishes the next
+          // k-block and frees this one's ring slots.
+          __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+          __syncthreads();
+#ifdef FQ_ABLATE_EXTRA_SALU
+          extra_salu(k);
+#endif
+          if (stage_a) {
+            if (left > 0) stage_share(src, dst);
+            if (kFb && !r0.flags && r1.slot >= 0 && left >= 0) stage_res(r1.slot);
+          } else {
+            late = kFb && r0.flags ? 0 : max(left, 0);
+          }
+        }
+        const int again = kFb ? r0.flags & (res ^ 1) & 1 : 0;
+        const int a_next = kFb && again ? kResOffset<G> : a_sum - a_ring_at;
+        const int b_next = kFb && again ? b_at : b_sum - b_at;
+        if (multiply)
+          run_units_range<G, kUnits - 2, kUnits, kBiased>(st, a_cur, lds + a_next, lds + b_next, h, c, lane, sc, sp, magic);
+        a_at = a_next;
+        after_units(sc);
+        if (kFb && again) {
+          res = 1;
+#pragma unroll
+          for (int q = 0; q < G::kSC; ++q) cur[q] = r0.t[q];
+          continue;
+        }
+        if (left < 0) break;
+        if (kFb && r0.flags) {
+          res = 0;
+          __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+          asm volatile("s_barrier" ::: "memory");
+          if (!stage_a && left > 0) stage_share(src + kBlockBytes, dst_sum - dst);
+          if (r1.slot >= 0) stage_res(r1.slot);
+        }
+        // ---- k-block k + 1
+        --left;
+        a_ring_at = a_sum - a_ring_at;
+        b_at = b_sum - b_at;
+        dst = dst_sum - dst;
+        src += kBlockBytes;
+        next_k();
+#pragma unroll
+        for (int q = 0; q < G::kSC; ++q) cur[q] = r0.s[q];
+      }
+    } else {
+    if (h == 1) asm volatile("s_barrier" ::: "memory");   // team 1 starts one barrier later
+    for (;;) {
+      // ---- the items after this one
+      const int n1res = (r0.flags >> 1) & (res ^ 1), n1k = k + 1 - n1res;
+      const int n2res = (r1.flags >> 1) & (n1res ^ 1), n2k = k + 2 - (n1res | n2res);
+      // a residual item is work only for the wavefronts whose i-block is flagged at this k
+      const bool active = !res || (r0.flags & 1);
       ItemScales<G> sc;
 #pragma unroll
-      for (int q = 0; q < G::kSC; ++q)
-        sc.s[q] = res ? r0.t[q] : r0.s[q];
-
+      for (int q = 0; q < G::kSC; ++q) sc.s[q] = __int_as_float(res ? r0.t[q] : r0.s[q]);
       const int8_t* const a_cur = a_ring + (t & 1) * G::kASet;
       const int8_t* const a_nxt = a_ring + ((t + 1) & 1) * G::kASet;
       const int8_t* const b_nxt = b_ring + (n1k & 1) * G::kBSet;
-
-      if constexpr (kSkew) {
-        // two barriers per item: this one is the other team's item boundary, in the middle of ours
-        if (active) run_units_range<G, 0, 2, kBiased>(st, a_cur, a_nxt, b_nxt, h, c, lane, sc, sp, magic);
-        // Behind this barrier team 0 may overwrite the B set this wavefront took its operands
-        // from.  An active wavefront has multiplied with all of them by now; one that skips the
-        // item has not used them yet and waits for the reads here.
-        else __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
-        asm volatile("s_barrier" ::: "memory");
-        if (active) run_units_range<G, 2, kUnits - 2, kBiased>(st, a_cur, a_nxt, b_nxt, h, c, lane, sc, sp, magic);
-      } else {
-        if (active) run_units_range<G, 0, kUnits - 2, kBiased>(st, a_cur, a_nxt, b_nxt, h, c, lane, sc, sp, magic);
-      }
-
-      // All LDS reads of this item are issued (the last two units run from registers).  Wait
-      // for them and for the next item's direct-to-LDS loads, then the barrier publishes the
-      // next item and frees this item's ring slots for the item after it.
+      // two barriers per item: this one is the other team's item boundary, in the middle of ours
+      if (active) run_units_range<G, 0, 2, kBiased>(st, a_cur, a_nxt, b_nxt, h, c, lane, sc, sp, magic);
+      // Behind this barrier team 0 may overwrite the B set this wavefront took its operands
+      // from.  An active wavefront has multiplied with all of them by now; one that skips the
+      // item has not used them yet and waits for the reads here.
+      else __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+      asm volatile("s_barrier" ::: "memory");
+      if (active) run_units_range<G, 2, kUnits - 2, kBiased>(st, a_cur, a_nxt, b_nxt, h, c, lane, sc, sp, magic);
       __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
       __syncthreads();
-#ifdef FQ_ABLATE_EXTRA_SALU
-      {
-        int chain = k;
-#pragma unroll
-        for (int i = 0; i < FQ_ABLATE_EXTRA_SALU; ++i) asm volatile("s_add_i32 %0, %0, 1" : "+s"(chain));
-        asm volatile("" :: "s"(chain));
-      }
-#endif
-#ifdef FQ_ABLATE_ONE_STAGER
-      if (has2) {
-        if (n2res) stage_item(k + 1, 1, r1, t & 1, false);
-        else stage_item(n2k, 0, r1, t & 1, n2k != n1k);
-      }
-#else
-      if (has2) {
-        if constexpr (kSkew) {
-          if (n2res) stage_team(k + 1, 1, r1, t & 1, false);
-          else stage_team(n2k, 0, r1, t & 1, n2k != n1k);
-        } else if (stage_a) {
-          if (n2res) stage_item(k + 1, 1, r1, t & 1, false);
-          else stage_item(n2k, 0, r1, t & 1, false);
-        } else if (!n2res && n2k != n1k) {
-          late_b_k = n2k;
-        }
-      }
-#endif
-
+      if (n2k < nkb) stage_team(n2k, n2res, r1, t & 1, !n2res);
       if (active) {
         run_units_range<G, kUnits - 2, kUnits, kBiased>(st, a_cur, a_nxt, b_nxt, h, c, lane, sc, sp, magic);
-#pragma unroll
-        for (int i = 0; i < G::kSP; ++i) sp[i] = sc.s[G::kSC == 1 ? 0 : kSJ - 2 + i];
-        if constexpr (kBiased) {
-#pragma unroll
-          for (int q = 0; q < G::kSC; ++q) bias_s[q] += sc.s[q];
-          if (++bias_items == kBiasWindow) {
-            // fold the pending unit, take the bias out, and restart the pipeline: the next unit 0
-            // folds the same tile again with scale 0, which adds nothing
-            drain<G, true>(st, sp);
-            remove_bias();
-#pragma unroll
-            for (int i = 0; i < G::kSP; ++i) sp[i] = 0.0f;
-          }
-        }
+        after_units(sc);
       } else {
-        // nothing to multiply in this item: the pipeline state (the pending tile of the last
-        // active item and its scale) stays as it is; only fetch the next item's first operands,
-        // which the last two units would have done
+        // nothing to multiply in this item: the pipeline state (the pending tile of the last active item and
+        // its scale) stays as it is; only fetch the next item's first operands
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           st.aq[0][i >> 1][i & 1] = lds_frag(a_nxt + G::a_block(h, 0) * kBlockBytes, G::a_group(h, 0),
@@ -736,18 +756,11 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
           }
         }
       }
-      if (!has1) break;
-      // ---- advance to the next item
+      if (n1k >= nkb) break;
       ++t;
-      if (n1res) {
-        res = 1;
-      } else {
-        res = 0;
-        ++k;
-        r0 = r1;
-        if (((k + 1) & 63) == 0 && k + 1 < nkb) load_chunk(k + 1);
-        r1 = rec_of(k + 1);
-      }
+      res = n1res;
+      if (!n1res) next_k();
+    }
     }
     if (kSkew && h == 0) asm volatile("s_barrier" ::: "memory");   // team 1's last item boundary
     drain<G, kBiased>(st, sp);
@@ -858,12 +871,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmParams p) {
 }
 
 // gemm_kernel for an A operand that cannot fall back (gradients of the paper's recipe, activations quantized
-// without a criterion): every item is a k-block, there is no branch around the units and no path to join behind
-// them, and a third of the scalar instructions of an item are gone, all of which sat around its barrier, where no
-// wavefront has anything else to issue.  Same bits; bf16 output unless said, us, gemm_kernel before -> here:
-// 4096 x 4096 x 11008 202 -> 190, 4096 x 11008 x 4096 as NN 185 -> 174, 11008 x 4096 x 4096 as TN with binary32
-// output 215 -> 203, 8192^3 545 -> 511.  (Working out an item's addresses in the slots of an early unit, where the
-// other wavefront of the SIMD leaves issue cycles free, took the rest of the scalars from the barrier and gave nothing.)
+// without a criterion): every turn is a k-block, and what tells the two kinds apart is gone from the scalar work around
+// the barrier, where no wavefront has anything else to issue.  Same bits; with residual slots that nobody uses ->
+// here, us: 8192^3 519 -> 508, 4096 x 4096 x 11008 196 -> 190; as TN 11008 x 4096 x 4096 with binary32 output 215 -> 202
+// against the kernel before both had one body.
 __global__ __launch_bounds__(kThreads, 2) void gemm_main_kernel(GemmParams p) {
   extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
   int ti, tj;
@@ -884,9 +895,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_main_kernel(GemmParams p) {
 // taken out every kBiasWindow items.  Half the vector-ALU instructions of Eq. (1) (the two left per
 // MFMA are the ones its issue leaves free); the additions round at the magnitude of the biased
 // sums, so results differ from gemm_kernel's by up to about 2e-4 of max |C|, whatever K.
-// 256 registers and one in scratch memory: the thread's index, read again once in 64 k-blocks and at the
-// end.  Working it out again in those places instead (no scratch) left the rest of the registers in an order
-// that cost 1 %: 4096 x 4096 x 11008 186.6 -> 188.6 us, 8192^3 with a fifth of the blocks flagged 579 -> 585.
 __global__ __launch_bounds__(kThreads, 2) void gemm_biased_kernel(GemmParams p) {
   extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
   int ti, tj;

@@ -39,3 +39,31 @@ def test_large_tiles_without_fallback(tile, op, K, monkeypatch):
     # the same codes with residual slots that nobody uses: the other kernel
     gf = fq.fq_quantize(gu.to_device_bf16(a), fq.FQ_CRIT_ABSMAX_GT, float("inf"), want_transposed=at)
     assert torch.equal(fq.fq_gemm(op, gf, gb), c)
+
+
+# which of the tile's two block rows are flagged at each of nine k-blocks (1, 2, 3: upper, lower, both)
+PATTERNS = {"first": "300000000", "last": "000000003", "last upper": "000000001", "halves in turn": "121212121",
+            "same half in a row": "111022200", "all": "333333333", "mixed": "013231203"}
+
+
+@pytest.mark.parametrize("pattern", list(PATTERNS))
+def test_patterns_of_flagged_blocks(pattern, monkeypatch):
+    """Residual products of a 256 x 256 tile: the turns of its two halves, the blocks they share in LDS."""
+    monkeypatch.setenv("FQ_GEMM_CUS", "1")
+    assert fq.fq_gemm_path(250, 256) == (fq.FQ_TILES_256x256, 1, 0, 0) == fq.fq_gemm_path(250, 256, biased=True)
+    bits = PATTERNS[pattern]
+    K = 128 * len(bits)
+    a, b = _operands(NT, 250, 256, K, 17, 0)
+    for k, p in enumerate(bits):
+        for half in range(2):
+            if int(p) >> half & 1:
+                a[128 * half + 7 * k, 128 * k + 5] = 0x4300 + k           # 128 and more
+    ga = fq.fq_quantize(gu.to_device_bf16(a), fq.FQ_CRIT_ABSMAX_GT, 12.0)
+    gb = fq.fq_quantize(gu.to_device_bf16(b), fq.FQ_CRIT_NONE, 0.0, capacity=0)
+    oa, ob = fqo.quantize(a, 128, fqo.CRIT_ABSMAX_GT, 12.0), fqo.quantize(b, 128, fqo.CRIT_NONE, 0.0)
+    assert int(oa.fb_count[0]) == sum(bin(int(p)).count("1") for p in bits)
+    gu.announce(f"flagged blocks: {pattern}")
+    ref = fqo.gemm(NT, oa, ob)
+    for _ in range(3):
+        assert np.array_equal(fq.fq_gemm(NT, ga, gb).cpu().numpy(), ref)
+    assert np.abs(fq.fq_gemm_biased(NT, ga, gb).cpu().numpy() - ref).max() <= 1e-3 * np.abs(ref).max()
