@@ -20,6 +20,28 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
                "-Wall", "-Wno-unused-command-line-argument"]
 
 
+NATIVE = os.path.join(HERE, "_fqnative.so")
+
+
+def build_native() -> str:
+    """The Python module of csrc/fq_python.cpp (host code only), for the torch that is installed."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    inc = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include")]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f'-DFQ_TORCH_VERSION="{torch.__version__}"',
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", sysconfig.get_paths()["include"]] + \
+          [f for d in inc for f in ("-isystem", d)] + \
+          ["-o", NATIVE, os.path.join(CSRC, "fq_python.cpp"), "-L", os.path.join(root, "lib"), "-ltorch_python",
+           "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed:\n{r.stderr}")
+    return NATIVE
+
+
 TOOLS = ["mfma_ceiling", "pipeline_probe"]
 TOOL_BIN = os.path.join(HERE, "mfma_ceiling")
 
@@ -105,5 +127,6 @@ def build(force: bool = True, extra_flags=()) -> str:
 
 if __name__ == "__main__":
     print(build())
+    print(build_native())
     print(build_tools())
     print(build_ablations())

@@ -1,0 +1,130 @@
+"""fq_quantize, fq_quantize_sr and fq_gemm through the native module against the same calls through ctypes: the forms of
+their arguments, their errors, the current stream; and on the CPU, what the native module leaves to the Python code."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2503_08040_amd as fq
+from paper_2503_08040_amd import _fqnative
+
+gpu = pytest.mark.gpu
+
+
+def test_anything_unusual_is_left_to_the_python_code():
+    x = torch.zeros((4, 8), dtype=torch.bfloat16)                 # not on the GPU
+    for theta in (1.0, 1, "1", None, torch.tensor(1.0)):
+        assert _fqnative.quantize(x, 1, theta, 0, 128) is None
+    for first in (None, 3, torch.nn.Parameter(x), x.float(), np.zeros((4, 8)), x[0]):
+        assert _fqnative.quantize(first, 1, 1.0, 0, 128) is None
+        assert _fqnative.quantize_sr(first, 1, 0) is None
+    a, b = fq.fq_qtensor(rows=3, cols=4), fq.fq_qtensor(rows=5, cols=4)
+    import ctypes as C
+    args = [C.addressof(a), C.addressof(b), x]
+    assert _fqnative.gemm(7, *args, None, None) is None                           # no such product
+    assert _fqnative.gemm(True, *args, None, None) is None
+    assert _fqnative.gemm(0, *args, None, torch.float16) is None                  # no such output
+    assert _fqnative.gemm(0, *args, None, "f32") is None
+    assert _fqnative.gemm(0, *args, torch.zeros(3, 5), None) is None              # not on the GPU
+    with pytest.raises(TypeError):
+        _fqnative.setup(1, 2)
+
+
+@pytest.fixture
+def both(monkeypatch):
+    """Runs a call through the native module (and makes sure of it) and through ctypes."""
+    fq.QTensor(1, 1)
+    assert fq._native is _fqnative
+
+    def run(call):
+        out = []
+        for native in (True, False):
+            with monkeypatch.context() as m:
+                if not native:
+                    m.setattr(fq, "_native", None)
+                try:
+                    out.append(call())
+                except Exception as e:                     # compared, not hidden
+                    out.append((type(e), getattr(e, "status", None)))
+        return out
+    return run
+
+
+def _state(q):
+    names = ["codes", "scales", "mask"] + (["codes_t"] if q.want_transposed else [])
+    return [q.view(n).clone() for n in names]
+
+
+@gpu
+@pytest.mark.parametrize("shape,pitch", [((1, 8), 8), ((1, 300), 512), ((130, 260), 264), ((7, 1), 1), ((0, 5), 5)])
+def test_quantize_forms(shape, pitch, both):
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((shape[0], pitch), device="cuda", generator=g).bfloat16()[:, :shape[1]]
+    q = fq.QTensor(*shape, want_transposed=True)
+    q.storage.zero_()
+
+    def nearest(theta):
+        fq.fq_quantize(x, fq.FQ_CRIT_ABSMAX_GT, theta, out=q)
+        return _state(q)
+
+    def stochastic(seed):
+        fq.fq_quantize_sr(x, seed, out=q)
+        return _state(q)
+    for f, values in ((nearest, (0.5, 1, float("inf"))), (stochastic, (5, -1, 2 ** 64 + 9))):
+        for v in values:
+            n, p = both(lambda: f(v))
+            assert len(n) == len(p) and all(torch.equal(s, t) for s, t in zip(n, p))
+
+
+@gpu
+@pytest.mark.parametrize("op", [fq.FQ_OP_NT, fq.FQ_OP_NN, fq.FQ_OP_TN])
+def test_gemm_forms(op, both):
+    g = torch.Generator(device="cuda").manual_seed(4)
+    sa, sb = {0: ((33, 200), (70, 200)), 1: ((33, 200), (200, 70)), 2: ((200, 33), (200, 70))}[op]
+    a, b = (fq.fq_quantize(torch.randn(s, device="cuda", generator=g).bfloat16(), fq.FQ_CRIT_NONE, 0.0, capacity=0,
+                           want_transposed=True) for s in (sa, sb))
+    wide = torch.zeros((33, 96), device="cuda")
+    for kw in ({}, {"out_dtype": torch.float32}, {"out_dtype": torch.bfloat16}, {"out": wide[:, 8:78]},
+               {"out": torch.zeros((33, 70), device="cuda", dtype=torch.bfloat16)}):
+        n, p = both(lambda: fq.fq_gemm(op, a, b, **kw).clone())
+        assert n.dtype == p.dtype and n.device == p.device and n.shape == p.shape and torch.equal(n, p)
+    assert fq.fq_gemm(op, a, b, out=wide[:, 8:78]).data_ptr() == wide[:, 8:78].data_ptr()
+    for kw in ({"out_dtype": torch.float16}, {"out": torch.zeros((33, 71), device="cuda")},
+               {"out": torch.zeros((70, 33), device="cuda").t()}):
+        n, p = both(lambda: fq.fq_gemm(op, a, b, **kw))
+        assert n == p and isinstance(n, tuple)
+
+
+@gpu
+def test_errors_are_the_same(both):
+    x = torch.randn((256, 256), device="cuda").bfloat16()
+    q, none = fq.QTensor(256, 256), fq.QTensor(256, 256, capacity=0)
+    for call in (lambda: fq.fq_quantize(x, fq.FQ_CRIT_ABSMAX_GT, 1.0, out=none), lambda: fq.fq_quantize(x, 9, 1.0, out=q),
+                 lambda: fq.fq_quantize(x[:128], 0, 1.0, out=q), lambda: fq.fq_quantize(x.float(), 0, 1.0, out=q),
+                 lambda: fq.fq_quantize(x.t(), 0, 1.0, out=q), lambda: fq.fq_quantize(x, 0, "1", out=q),
+                 lambda: fq.fq_quantize_sr(x, 1.5, out=q), lambda: fq.fq_quantize_sr(x[:, :8], 1, out=q),
+                 lambda: fq.fq_gemm(5, q, q), lambda: fq.fq_gemm(fq.FQ_OP_TN, q, q)):
+        n, p = both(call)
+        assert n == p and isinstance(n, tuple), (n, p)
+
+
+@gpu
+def test_the_current_stream_is_used(both):
+    x = torch.randn((512, 512), device="cuda").bfloat16()
+    q = fq.fq_quantize(x, fq.FQ_CRIT_NONE, 0.0, capacity=0)
+    want = fq.fq_gemm(fq.FQ_OP_NT, q, q)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+
+    def captured():                    # a call on any other stream would not be in the graph
+        graph = torch.cuda.CUDAGraph()
+        out = torch.zeros_like(want)
+        with torch.cuda.graph(graph, stream=side):
+            fq.fq_gemm(fq.FQ_OP_NT, q, q, out=out)
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
+        return out
+    n, p = both(captured)
+    assert torch.equal(n, p)
