@@ -769,11 +769,77 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
 
   // ---- epilogue.  The MFMA result layout (lane = column, registers = rows) would give 32-byte
   // global stores; instead each wavefront transposes its tile through a private LDS patch
-  // (32 rows x 32*kSJ columns of FP32 at a time, row pitch + 4 floats) and writes whole row
-  // segments with 16-byte stores.
+  // (32 rows x 32*kSJ columns at a time) and writes whole row segments with 16-byte stores.
+  // A wavefront whose tile lies inside the output stores it without a condition: in the general form behind it every
+  // 16 bytes have a branch, 30 integer instructions and an LDS read of their own to wait for.  Such a wavefront also
+  // converts to bf16 in front of the patch, two rows to a dword (row pitch + 8 dwords: 2 pitch = 16 banks), which halves
+  // the LDS traffic: 16 KiB x 8 wavefronts written and read at 128 bytes a cycle is what is left, 0.9 us.  One workgroup
+  // is all a compute unit holds, so nothing passes behind its end.  us, without fallback: 11008 x 4096 x 4096 as TN,
+  // binary32 output, 223 -> 214; 11008 x 2048 x 4096 129 -> 121; 4096 x 11008 x 4096, bf16, 206 -> 204 (on a box where
+  // the clock is low).  Non-temporal stores: up to 4 % slower.
   __syncthreads();   // every wavefront is done reading the operand rings
   float* const stg = reinterpret_cast<float*>(lds + w * G::kStageBytesPerWave);
   const int col0 = jb_first * kBlock + c * G::kStageCols;   // first column of this wave's tile
+  const int last_row = (ib_first + G::a_block(h, kSI - 1)) * kBlock + G::a_group(h, kSI - 1) * 32 + 31;
+  if (p.vec_ok && last_row < p.M && col0 + G::kStageCols <= p.N && p.ldc < (1 << 24) && !poison) {      // offsets in 32 bits
+    const uint32_t ldc = (uint32_t)p.ldc;
+    if (p.out_bf16) {
+      uint32_t* const pair = reinterpret_cast<uint32_t*>(stg);
+      constexpr int kPitch = G::kStageCols + 8, kChunks = G::kStageCols / 8;
+      static_assert(16 * kPitch * 4 <= G::kStageBytesPerWave);
+#pragma unroll
+      for (int si = 0; si < kSI; ++si) {
+#pragma unroll
+        for (int sj = 0; sj < kSJ; ++sj)
+#pragma unroll
+          for (int e = 0; e < 16; e += 2)
+            pair[(8 * (e >> 3) + 2 * (lane >> 4) + ((e >> 1) & 1)) * kPitch + sj * 32 + 16 * ((e >> 2) & 1) + (lane & 15)] =
+                pack_bf16x2(st.acc[si][sj][e], st.acc[si][sj][e + 1]);
+        const int row0 = (ib_first + G::a_block(h, si)) * kBlock + G::a_group(h, si) * 32;
+        char* const dst = reinterpret_cast<char*>(p.c) + ((int64_t)row0 * p.ldc + col0) * 2;
+#pragma unroll
+        for (int it = 0; it < 16 * kChunks / 64; ++it) {
+          const int idx = it * 64 + lane;
+          const int rp = idx / kChunks, c8 = (idx % kChunks) * 8;
+          const v4i a = *reinterpret_cast<const v4i*>(pair + rp * kPitch + c8);
+          const v4i b = *reinterpret_cast<const v4i*>(pair + rp * kPitch + c8 + 4);
+          v4i lo, hi;
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            lo[i] = __builtin_amdgcn_perm(a[2 * i + 1], a[2 * i], 0x05040100);
+            lo[2 + i] = __builtin_amdgcn_perm(b[2 * i + 1], b[2 * i], 0x05040100);
+            hi[i] = __builtin_amdgcn_perm(a[2 * i + 1], a[2 * i], 0x07060302);
+            hi[2 + i] = __builtin_amdgcn_perm(b[2 * i + 1], b[2 * i], 0x07060302);
+          }
+          const uint32_t off = (2 * rp * ldc + c8) * 2;
+          *reinterpret_cast<v4i*>(dst + off) = lo;
+          *reinterpret_cast<v4i*>(dst + p.ldc * 2 + off) = hi;
+        }
+      }
+    } else {
+      constexpr int kChunks = G::kStageCols / 4;
+#pragma unroll
+      for (int si = 0; si < kSI; ++si) {
+#pragma unroll
+        for (int sj = 0; sj < kSJ; ++sj)
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            stg[(16 * (e >> 3) + 4 * (lane >> 4) + (e & 3)) * G::kStagePitch + sj * 32 + 16 * ((e >> 2) & 1) + (lane & 15)] =
+                st.acc[si][sj][e];
+        const int row0 = (ib_first + G::a_block(h, si)) * kBlock + G::a_group(h, si) * 32;
+        char* const dst = reinterpret_cast<char*>(p.c) + ((int64_t)row0 * p.ldc + col0) * 4;
+#pragma unroll
+        for (int it = 0; it < 32 * kChunks / 64; ++it) {
+          const int idx = it * 64 + lane;
+          const int rl = idx / kChunks, c4 = (idx % kChunks) * 4;
+          *reinterpret_cast<float4*>(dst + (rl * ldc + c4) * 4) =
+              *reinterpret_cast<const float4*>(stg + rl * G::kStagePitch + c4);
+        }
+      }
+    }
+    return;
+  }
+  // 32 rows x 32*kSJ columns of FP32 at a time, row pitch + 4 floats
 #pragma unroll
   for (int si = 0; si < kSI; ++si) {
     // a flagged block whose residual found no slot cannot be computed: poison its rows
