@@ -940,15 +940,16 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmParams p) {
 // without a criterion): every turn is a k-block, and what tells the two kinds apart is gone from the scalar work around
 // the barrier, where no wavefront has anything else to issue.  Same bits; with residual slots that nobody uses ->
 // here, us: 8192^3 519 -> 508, 4096 x 4096 x 11008 196 -> 190; as TN 11008 x 4096 x 4096 with binary32 output 215 -> 202
-// against the kernel before both had one body.
+// against the kernel before both had one body.  The first p.n_lead of the 1 x 3-block tiles come before the others.
 __global__ __launch_bounds__(kThreads, 2) void gemm_main_kernel(GemmParams p) {
   extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
   int ti, tj;
-  if ((int)blockIdx.x < p.n_main) {
-    tile_of(blockIdx.x, p.main_ti, p.main_tj, ti, tj);
+  const int b = (int)blockIdx.x - p.n_lead;
+  if (b >= 0 && b < p.n_main) {
+    tile_of(b, p.main_ti, p.main_tj, ti, tj);
     tile_body<Geo<2, 2>, false, false>(p, 2 * ti, 2 * tj, lds);
   } else {
-    tile_of(blockIdx.x - p.n_main, p.tail_ni, p.tail_tj, ti, tj);
+    tile_of(b < 0 ? (int)blockIdx.x : (int)blockIdx.x - p.n_main, p.tail_ni, p.tail_tj, ti, tj);
     tile_body<Geo<1, 3>, false, false>(p, p.tail_i0 + ti, p.tail_j0 + 3 * tj, lds);
   }
 }
@@ -1177,7 +1178,17 @@ hipError_t launch_gemm(const GemmParams& p_in, bool debug, hipStream_t st) {
   p.tail_ni = plan.tail_ni;
   p.tail_j0 = plan.tail_j0;
   p.tail_tj = plan.tail_tj;
-  const int grid = plan.n_main + plan.tail_ni * plan.tail_tj;
+  // A round of binary32 tiles is 67 MB that all compute units store at once, while nothing multiplies.  Half of the
+  // 3/4 tiles go first there, so that half of the chip ends its rounds a quarter of one before or behind the other; the
+  // sum of the rounds stays what it is.  Neighbours that no longer work in step share less through L2, which costs more
+  // the longer the contraction is, and tiles of uneven length (fallback) end better with the short ones last.  us,
+  // binary32: 5120 x 5120 x 2048 73.8 -> 70.3, 11008 x 4096 x 1000 74.5 -> 69.3, x 2048 121.8 -> 117.7; with K = 4096
+  // -1.5 (11008 x 4096) to +2 % (5120 x 5120); with 20 % flagged 4096 x 11008 x 2048 137.1 -> 139.2; with bf16 output,
+  // half as much to store, -4 to +2 %.
+  constexpr int kMaxLeadK = 16;    // k-blocks
+  const int n_tail = plan.tail_ni * plan.tail_tj;
+  p.n_lead = !p.a_slot && !p.biased && !p.out_bf16 && p.nkb <= kMaxLeadK ? n_tail / 2 / kXcds * kXcds : 0;
+  const int grid = plan.n_main + n_tail;
   // the kernel needs more dynamic LDS than the default limit: raise it once per device
   static std::atomic<bool> attr_set[kMaxDevices];
   int dev = 0;

@@ -58,6 +58,7 @@ struct GemmParams {
   // tile plan, filled in by launch_gemm: main tiles, their rows and columns; block rows of the tail, its
   // first block row and block column, its tile columns
   int n_main, main_ti, main_tj, tail_ni, tail_i0, tail_j0, tail_tj;
+  int n_lead;                 // tail tiles that come before the main ones
   int group;                  // quantization group edge (128, 64, 32)
   int a_ni, a_nk, b_nj;       // extents of the scale grids along i, k (A) and j (B), in groups
   int biased;                 // tolerance variant: biased INT32 accumulation (gemm_biased_kernel)

@@ -51,3 +51,26 @@ def test_stores(M, N, cus, variant, monkeypatch):
     if not biased:                # the smaller tiles, which store otherwise
         monkeypatch.delenv("FQ_GEMM_CUS")
         assert torch.equal(product(fq.FQ_OP_NT, a, b), full)
+
+
+# tail tiles: 20, 20, 32 and 32, of which 8 and 16 come before the main tiles (no fallback, binary32 output, up to 16 k-blocks)
+@pytest.mark.parametrize("M,N,cus", [(1280, 1900, 24), (1280, 3000, 24), (2560, 3000, 32), (2048, 3000, 40)])
+@pytest.mark.parametrize("K", [200, 2048, 2049])
+def test_order_of_tail_tiles(M, N, cus, K, monkeypatch):
+    monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
+    path = fq.fq_gemm_path(M, N)
+    assert path[0] == fq.FQ_TILES_256x256 and path[2] + path[3] >= 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K)
+    x = torch.randn(M, K, device="cuda", generator=g)
+    x[::300, 150] = 90.0
+    b = fq.fq_quantize(torch.randn(N, K, device="cuda", generator=g).bfloat16(), fq.FQ_CRIT_NONE, 0.0, capacity=0)
+    for a in (fq.fq_quantize(x.bfloat16(), fq.FQ_CRIT_ABSMAX_GT, 30.0),
+              fq.fq_quantize(x.bfloat16(), fq.FQ_CRIT_NONE, 0.0, capacity=0)):
+        gu.announce(f"order of tail tiles {M}x{N}x{K}")
+        full = torch.full((M, N), float("nan"), device="cuda")
+        fq.fq_gemm(fq.FQ_OP_NT, a, b, out=full)
+        monkeypatch.setenv("FQ_GEMM_CUS", "0")           # 256 x 256 or smaller tiles only
+        assert torch.equal(fq.fq_gemm(fq.FQ_OP_NT, a, b), full)
+        monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
+        assert torch.equal(fq.fq_gemm(fq.FQ_OP_NT, a, b, out_dtype=torch.bfloat16), full.bfloat16())
