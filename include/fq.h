@@ -405,7 +405,8 @@ fq_status fq_gemm_tile_plan(int32_t rows_out, int32_t cols_out, int32_t compute_
  * 128 x 128 tiles (one per workgroup, or two side by side), path[1] = their number; these are chosen
  * where the output is less than about a chip's worth of large tiles.  path[0] = 0: the large ones, path[1] = the number of 256 x 256
  * tiles, path[2] and path[3] = the number of 128 x 384 tiles over the last block columns or,
- * where that ends earlier, the last block rows.  All zero for an empty output.  fq_gemm's results do not
+ * where that ends earlier, the last block rows.  An A that has no residual slots (capacity 0) takes the large
+ * tiles on somewhat smaller outputs already.  All zero for an empty output.  fq_gemm's results do not
  * depend on the tiles: every output element is accumulated in Alg. 1's order.
  */
 fq_status fq_gemm_path(int32_t rows_out, int32_t cols_out, int32_t compute_units, int biased,

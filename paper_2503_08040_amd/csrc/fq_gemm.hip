@@ -1066,8 +1066,8 @@ TilePlan plan_tiles(int nib, int njb, int cus) {
 //   32 x 32     240, or 80 per tile and compute unit            (33 x 11008 x 4096; 512 x 4096 x 4096)
 //   128 x 64    1000 for up to three of them (three are resident), or 390 each         (1536 x 4096 x 4096; 3072^3)
 //   128 x 128   850 alone on its compute unit, 1360 a pair (two are resident)
-//   256 x 256   2400 (2250 on an idle chip), one is resident    (4096^3);
-//               gemm_biased_kernel 2050                         (2048 x 4096 x 11008)
+//   256 x 256   2340 for an A with residual slots, 2050 without, one is resident; gemm_biased_kernel 2050
+//                                                               (4096^3; 2048 x 4096 x 11008)
 // and the forms of fq_gemm_ring.hip, for one round of the chip and no more:
 //   128 x 64    380 alone on its compute unit, 675 a pair       (512 x 8192 x 4096; 1024 x 8192 x 4096)
 //   128 x 128   600                                             (1024 x 8192 x 4096)
@@ -1075,13 +1075,16 @@ TilePlan plan_tiles(int nib, int njb, int cus) {
 // So 2048 x 4096 x 4096 takes 128 x 256 (39 us without flagged blocks, 43.5 with 128 x 128 pairs, 76 with
 // 256 x 256), 1536 x 4096 x 4096 three 128 x 64 per compute unit (34.1; 35.1 with 128 x 256, 36.0 with 128 x 64 of
 // the ring in two rounds), 3072^3 128 x 64 too (42; 44 and 48 in two and three rounds of the ring's 128 x 64 and
-// 128 x 128, 61 with 256 x 256) and 4096^3 256 x 256 (79 us; 82 in two rounds of 128 x 256); 512 x 4096 x 4096
+// 128 x 128, 61 with 256 x 256) and 4096^3 256 x 256 (79 us; 82 in two rounds of 128 x 256).  Flagged blocks cost
+// 256 x 256 tiles more than the others, and how many there are is not known here, so the line for an A with slots lies where
+// 20 % are no loss: 3584 x 4096 x 3584 256 x 256 (74 us at 10 %, 84 with 128 x 64), 1152 x 4096 x 9984 128 x 64 (82 at 20 %,
+// 87).  Without slots 1280 x 1024 x 9856 and 4096 x 4096 x 5760 take 256 x 256 too (112 us, 123 with 128 x 128).  512 x 4096 x 4096
 // takes the ring's 128 x 64 (16.3 us; 18.9 with the other, 23.5 with 32 x 32), 256 x 4096 x 4096 32 x 32 (10.8 us,
 // 15.4 with the ring) and 256 x 11008 x 4096 too (28.6 us, 33.2).  64 x 64 tiles were never better than the nearer
 // of their neighbours by more than 3 %.  The smaller tiles have no biased form, so fq_gemm_biased takes them where
 // they beat its own kernel: 2048 x 4096 x 4096 (42 us against 68), but not 2048 x 4096 x 11008 (129 against 117)
 // or 3072 x 11008 x 4096 (170 against 151), which fq_gemm computes on 128 x 128.
-SmallTile plan_small(int M, int N, const TilePlan& big, int cus, bool biased) {
+SmallTile plan_small(int M, int N, const TilePlan& big, int cus, bool biased, bool slots) {
   const double c = cus > 0 ? cus : 256;
   auto tiles = [&](int r, int s) { return (double)((M + r - 1) / r) * ((N + s - 1) / s) / c; };
   const double n64 = tiles(128, 64), n128 = tiles(128, 128);
@@ -1094,7 +1097,7 @@ SmallTile plan_small(int M, int N, const TilePlan& big, int cus, bool biased) {
       {SmallTile::kRing128x64, n64 <= 1.0 ? 380.0 : n64 <= 2.0 ? 675.0 : kNever},
       {SmallTile::kRing128x128, n128 <= 1.0 ? 600.0 : kNever},
       {SmallTile::kRing128x256, tiles(128, 256) <= 1.0 ? 1090.0 : kNever}};
-  double best = (biased ? 2050.0 : 2400.0) * big.cost;
+  double best = (slots && !biased ? 2340.0 : 2050.0) * big.cost;
   SmallTile tile = SmallTile::kNone;
   for (const auto& f : form)
     if (f.est < best) {
@@ -1142,7 +1145,7 @@ void gemm_path(int M, int N, int cus, bool biased, int out[4]) {
   if (nib == 0 || njb == 0) return;
   if (cus <= 0) cus = planning_cus();
   const TilePlan plan = plan_tiles(nib, njb, cus);
-  const SmallTile tile = plan_small(M, N, plan, cus, biased);
+  const SmallTile tile = plan_small(M, N, plan, cus, biased, true);
   auto small = [&](int kind, int r, int c) {
     out[0] = kind;
     out[1] = (int)(((int64_t)M + r - 1) / r) * (int)(((int64_t)N + c - 1) / c);
@@ -1169,7 +1172,7 @@ hipError_t launch_gemm(const GemmParams& p_in, bool debug, hipStream_t st) {
   GemmParams p = p_in;
   const int cus = planning_cus();
   const TilePlan plan = plan_tiles(p.nib, p.njb, cus);
-  if (const SmallTile tile = plan_small(p.M, p.N, plan, cus, p.biased != 0); tile != SmallTile::kNone)
+  if (const SmallTile tile = plan_small(p.M, p.N, plan, cus, p.biased != 0, p.a_slot != nullptr); tile != SmallTile::kNone)
     return launch_gemm_small(p, tile, st);
   p.n_main = plan.n_main;
   p.main_ti = plan.main_ti;

@@ -67,3 +67,18 @@ def test_patterns_of_flagged_blocks(pattern, monkeypatch):
     for _ in range(3):
         assert np.array_equal(fq.fq_gemm(NT, ga, gb).cpu().numpy(), ref)
     assert np.abs(fq.fq_gemm_biased(NT, ga, gb).cpu().numpy() - ref).max() <= 1e-3 * np.abs(ref).max()
+
+
+# outputs on which only an A without residual slots takes 256 x 256 tiles, in one round and with 128 x 384 tails
+@pytest.mark.parametrize("M,N", [(1280, 9700), (4096, 5760), (1400, 8001)])
+def test_planner_line_depends_on_slots(M, N):
+    assert fq.fq_gemm_path(M, N)[0] != fq.FQ_TILES_256x256
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    x = torch.randn(M, 300, device="cuda", generator=g).bfloat16()
+    b = fq.fq_quantize(torch.randn(N, 300, device="cuda", generator=g).bfloat16(), fq.FQ_CRIT_NONE, 0.0, capacity=0)
+    slots = fq.fq_quantize(x, fq.FQ_CRIT_ABSMAX_GT, float("inf"))
+    none = fq.fq_quantize(x, fq.FQ_CRIT_NONE, 0.0, capacity=0)
+    gu.announce(f"planner line {M}x{N}")
+    for dt in (torch.float32, torch.bfloat16):
+        assert torch.equal(fq.fq_gemm(NT, slots, b, out_dtype=dt), fq.fq_gemm(NT, none, b, out_dtype=dt))
