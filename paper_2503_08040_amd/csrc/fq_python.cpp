@@ -5,13 +5,15 @@
 // arguments and torch.empty parsing its own.  Here a call reads them from the tensor itself: 7.8 us.  Only the plain case is
 // taken (torch.Tensor itself, the expected types, the current stream): for anything else these functions return
 // None and the Python code in front of them, which is the definition of what is accepted and of every error, runs.
+// What torch throws here leaves as torch's own Python functions translate it (torch.OutOfMemoryError from the
+// output's allocation, a Python exception from a dispatch mode).
 #include <Python.h>
 #include <torch/csrc/Dtype.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ops/empty.h>
 #include <algorithm>
-#include <exception>
 
 #include "../../include/fq.h"
 
@@ -89,7 +91,8 @@ PyObject* launch(const F& call) {
 }
 
 // quantize(x, crit, theta, address of the fq_qtensor, block) -> status or None
-PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) try {
+PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
   Matrix m;
   long crit, block;
   if (n != 5 || !PyFloat_CheckExact(a[2]) || !int_arg(a[1], &crit) || !int_arg(a[4], &block) || !matrix(a[0], &m))
@@ -99,12 +102,12 @@ PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) try {
   void* st;
   if (PyErr_Occurred() || !current_stream(&st)) return nullptr;
   return launch([&] { return g_quantize(m.ptr, m.rows, m.cols, m.ld, (int32_t)block, (fq_criterion)crit, theta, q, st); });
-} catch (const std::exception& e) {
-  return PyErr_Format(PyExc_RuntimeError, "%s", e.what());
+  END_HANDLE_TH_ERRORS
 }
 
 // quantize_sr(x, seed, address of the fq_qtensor) -> status or None
-PyObject* quantize_sr(PyObject*, PyObject* const* a, Py_ssize_t n) try {
+PyObject* quantize_sr(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
   Matrix m;
   if (n != 3 || !PyLong_CheckExact(a[1]) || !matrix(a[0], &m)) Py_RETURN_NONE;
   const uint64_t seed = PyLong_AsUnsignedLongLongMask(a[1]);
@@ -112,13 +115,13 @@ PyObject* quantize_sr(PyObject*, PyObject* const* a, Py_ssize_t n) try {
   void* st;
   if (PyErr_Occurred() || !current_stream(&st)) return nullptr;
   return launch([&] { return g_quantize_sr(m.ptr, m.rows, m.cols, m.ld, FQ_BLOCK, seed, q, st); });
-} catch (const std::exception& e) {
-  return PyErr_Format(PyExc_RuntimeError, "%s", e.what());
+  END_HANDLE_TH_ERRORS
 }
 
 // gemm(op, address of A's fq_qtensor, of B's, a tensor on the output's device, out or None, dtype or None)
 // -> (status, out) or None
-PyObject* gemm(PyObject*, PyObject* const* a, Py_ssize_t n) try {
+PyObject* gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
   long op;
   if (n != 6 || !int_arg(a[0], &op) || !THPVariable_CheckExact(a[3])) Py_RETURN_NONE;
   const fq_qtensor* const A = static_cast<fq_qtensor*>(PyLong_AsVoidPtr(a[1]));
@@ -164,8 +167,7 @@ PyObject* gemm(PyObject*, PyObject* const* a, Py_ssize_t n) try {
   Py_DECREF(status);
   Py_DECREF(t);
   return r;
-} catch (const std::exception& e) {
-  return PyErr_Format(PyExc_RuntimeError, "%s", e.what());
+  END_HANDLE_TH_ERRORS
 }
 
 PyMethodDef methods[] = {

@@ -1,8 +1,11 @@
 """fq_quantize, fq_quantize_sr and fq_gemm through the native module against the same calls through ctypes: the forms of
 their arguments, their errors, the current stream; and on the CPU, what the native module leaves to the Python code."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
+from torch.utils._python_dispatch import TorchDispatchMode
 
 import paper_2503_08040_amd as fq
 from paper_2503_08040_amd import _fqnative
@@ -18,7 +21,6 @@ def test_anything_unusual_is_left_to_the_python_code():
         assert _fqnative.quantize(first, 1, 1.0, 0, 128) is None
         assert _fqnative.quantize_sr(first, 1, 0) is None
     a, b = fq.fq_qtensor(rows=3, cols=4), fq.fq_qtensor(rows=5, cols=4)
-    import ctypes as C
     args = [C.addressof(a), C.addressof(b), x]
     assert _fqnative.gemm(7, *args, None, None) is None                           # no such product
     assert _fqnative.gemm(True, *args, None, None) is None
@@ -27,6 +29,47 @@ def test_anything_unusual_is_left_to_the_python_code():
     assert _fqnative.gemm(0, *args, torch.zeros(3, 5), None) is None              # not on the GPU
     with pytest.raises(TypeError):
         _fqnative.setup(1, 2)
+
+
+@pytest.fixture
+def structs():
+    """Addresses of two structs of 3 and 5 rows."""
+    keep = [fq.fq_qtensor(rows=n, cols=4) for n in (3, 5)]
+    yield [C.addressof(s) for s in keep]
+
+
+class _Raises(TorchDispatchMode):
+    """Every operation raises the given exception."""
+
+    def __init__(self, error):
+        super().__init__()
+        self.error = error
+
+    def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+        raise self.error
+
+
+@pytest.mark.parametrize("error", [torch.OutOfMemoryError("no memory left"), KeyError("key"), RuntimeError("text"),
+                                   KeyboardInterrupt(), FloatingPointError("a", 2)], ids=lambda e: type(e).__name__)
+def test_errors_of_the_outputs_allocation_are_torchs(error, structs):
+    x = torch.zeros(1)
+    caught = []
+    for allocate in (lambda: torch.empty((3, 5)), lambda: _fqnative.gemm(0, *structs, x, None, None)):
+        with _Raises(error), pytest.raises(BaseException) as e:
+            allocate()
+        caught.append((type(e.value), e.value.args))
+    assert caught[0] == caught[1] == (type(error), error.args)
+
+
+def test_an_allocation_that_fails_is_reported_as_torch_reports_it(structs):
+    huge = [fq.fq_qtensor(rows=2 ** 31 - 1, cols=1) for _ in range(2)]
+    caught = []
+    for allocate in (lambda: torch.empty((2 ** 31 - 1, 2 ** 31 - 1)),
+                     lambda: _fqnative.gemm(0, *(C.addressof(h) for h in huge), torch.zeros(1), None, None)):
+        with pytest.raises(RuntimeError) as e:
+            allocate()
+        caught.append((type(e.value), str(e.value)))
+    assert caught[0] == caught[1]
 
 
 @pytest.fixture
@@ -128,3 +171,17 @@ def test_the_current_stream_is_used(both):
         return out
     n, p = both(captured)
     assert torch.equal(n, p)
+
+
+@gpu
+def test_out_of_memory_keeps_its_type(both):
+    """The output does not fit what torch may take of the card: the allocator refuses, nothing is asked of the driver."""
+    n = 40000                                                    # 6.4 GB
+    q = fq.fq_quantize(torch.zeros((n, 8), device="cuda", dtype=torch.bfloat16), fq.FQ_CRIT_NONE, 0.0, capacity=0)
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(0.01)
+    try:
+        results = both(lambda: fq.fq_gemm(fq.FQ_OP_NT, q, q))
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert results == [(torch.OutOfMemoryError, None)] * 2
