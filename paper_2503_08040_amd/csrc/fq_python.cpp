@@ -81,13 +81,16 @@ bool int_arg(PyObject* o, long* v) {
   return !over && *v >= INT32_MIN && *v <= INT32_MAX;
 }
 
+// call() while other Python threads run.
+template <class F>
+auto without_gil(const F& call) {
+  pybind11::gil_scoped_release others;
+  return call();
+}
+
 template <class F>
 PyObject* launch(const F& call) {
-  fq_status s;
-  Py_BEGIN_ALLOW_THREADS
-  s = call();
-  Py_END_ALLOW_THREADS
-  return PyLong_FromLong(s);
+  return PyLong_FromLong(without_gil(call));
 }
 
 // quantize(x, crit, theta, address of the fq_qtensor, block) -> status or None
@@ -143,7 +146,8 @@ PyObject* gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
       type = reinterpret_cast<THPDtype*>(a[5])->scalar_type;
     }
     if (type != at::kFloat && type != at::kBFloat16) Py_RETURN_NONE;
-    out = at::empty({rows, cols}, THPVariable_Unpack(a[3]).options().dtype(type));
+    const at::TensorOptions options = THPVariable_Unpack(a[3]).options().dtype(type);
+    out = without_gil([&] { return at::empty({rows, cols}, options); });     // may wait for the device or the driver
   } else {
     if (!THPVariable_CheckExact(a[4])) Py_RETURN_NONE;
     out = THPVariable_Unpack(a[4]);

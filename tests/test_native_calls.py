@@ -1,6 +1,8 @@
 """fq_quantize, fq_quantize_sr and fq_gemm through the native module against the same calls through ctypes: the forms of
 their arguments, their errors, the current stream; and on the CPU, what the native module leaves to the Python code."""
 import ctypes as C
+import threading
+import time
 
 import numpy as np
 import pytest
@@ -70,6 +72,45 @@ def test_an_allocation_that_fails_is_reported_as_torch_reports_it(structs):
             allocate()
         caught.append((type(e.value), str(e.value)))
     assert caught[0] == caught[1]
+
+
+@pytest.fixture
+def no_launch():
+    """The native module as if the current device could not be had: a call raises LookupError in front of its launch."""
+    def device():
+        raise LookupError
+    _fqnative.setup(0, 0, 0, device, device)
+    yield
+    fq._native_setup()
+
+
+def test_other_threads_run_while_the_output_is_allocated(no_launch):
+    """As with torch.empty; the allocation takes long here because torch's deterministic mode fills it."""
+    n = 16000
+    q, over, ticks = fq.fq_qtensor(rows=n, cols=1), threading.Event(), []
+
+    def tick():
+        while not over.wait(0.001):
+            ticks.append(time.perf_counter())
+    during = []
+    thread = threading.Thread(target=tick)
+    thread.start()
+    torch.use_deterministic_algorithms(True)
+    try:
+        for allocate in (lambda: torch.empty((n, n)),
+                         lambda: _fqnative.gemm(0, C.addressof(q), C.addressof(q), torch.zeros(1), None, None)):
+            start = time.perf_counter()
+            try:
+                allocate()
+            except LookupError:
+                pass
+            end = time.perf_counter()
+            during.append(sum(start < t < end for t in ticks))
+    finally:
+        torch.use_deterministic_algorithms(False)
+        over.set()
+        thread.join()
+    assert min(during) >= 5, during
 
 
 @pytest.fixture
