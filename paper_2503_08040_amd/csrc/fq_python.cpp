@@ -12,6 +12,7 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/ops/empty.h>
 #include <algorithm>
 
@@ -146,6 +147,8 @@ PyObject* gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
       type = reinterpret_cast<THPDtype*>(a[5])->scalar_type;
     }
     if (type != at::kFloat && type != at::kBFloat16) Py_RETURN_NONE;
+    // a mode that sees torch's functions sees torch.empty of the Python code
+    if (at::impl::torch_function_mode_enabled()) Py_RETURN_NONE;
     const at::TensorOptions options = THPVariable_Unpack(a[3]).options().dtype(type);
     out = without_gil([&] { return at::empty({rows, cols}, options); });     // may wait for the device or the driver
   } else {

@@ -7,6 +7,7 @@ import time
 import numpy as np
 import pytest
 import torch
+from torch.overrides import TorchFunctionMode
 from torch.utils._python_dispatch import TorchDispatchMode
 
 import paper_2503_08040_amd as fq
@@ -82,6 +83,24 @@ def no_launch():
     _fqnative.setup(0, 0, 0, device, device)
     yield
     fq._native_setup()
+
+
+class _Sees(TorchFunctionMode):
+    """Notes the functions of torch that are called."""
+
+    def __init__(self):
+        super().__init__()
+        self.seen = []
+
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        self.seen.append(func)
+        return func(*args, **(kwargs or {}))
+
+
+def test_a_mode_that_sees_torchs_functions_sees_the_allocation(structs, no_launch):
+    x = torch.zeros(1)
+    with _Sees():
+        assert _fqnative.gemm(0, *structs, x, None, None) is None
 
 
 def test_other_threads_run_while_the_output_is_allocated(no_launch):
@@ -226,3 +245,14 @@ def test_out_of_memory_keeps_its_type(both):
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert results == [(torch.OutOfMemoryError, None)] * 2
+
+
+@gpu
+def test_a_mode_sees_the_outputs_allocation(both):
+    q = fq.fq_quantize(torch.randn((32, 32), device="cuda").bfloat16(), fq.FQ_CRIT_NONE, 0.0, capacity=0)
+
+    def empties():
+        with _Sees() as mode:
+            fq.fq_gemm(fq.FQ_OP_NT, q, q)
+        return mode.seen.count(torch.empty)
+    assert both(empties) == [1, 1]
