@@ -433,6 +433,11 @@ fq_status fq_qtensor_check(const fq_qtensor *t, int32_t *count_out, void *hip_st
 /* Static, never-NULL description of a status code (host). */
 const char *fq_status_string(fq_status s);
 
+/* Which text of this header the library was compiled with: the value of FQ_HEADER_TAG, for which the build gives a
+ * hash of the file; empty if none was given.  Code that holds its own compiled copy of the structs and signatures
+ * compares it with its own tag before it calls.  Static, never NULL (host). */
+const char *fq_header_tag(void);
+
 #ifdef __cplusplus
 }
 #endif

@@ -29,7 +29,7 @@ LIB_PATH = os.environ.get("FQ_LIBRARY") or os.path.join(_HERE, "libfq.so")
 EXPORTS = ["fq_qtensor_bytes", "fq_qtensor_bind", "fq_quantize", "fq_quantize_sr", "fq_quantize_topk",
            "fq_threshold_update", "fq_gemm", "fq_gemm_plain", "fq_gemm_biased",
            "fq_gemm_debug_partials", "fq_codes_to_rowmajor", "fq_qtensor_check",
-           "fq_status_string", "fq_ctx_packed_bytes", "fq_ctx_scales_bytes", "fq_ctx_quantize",
+           "fq_status_string", "fq_header_tag", "fq_ctx_packed_bytes", "fq_ctx_scales_bytes", "fq_ctx_quantize",
            "fq_ctx_dequantize", "fq_gemm_tile_plan", "fq_gemm_path",
            "fq_glu_forward", "fq_glu_backward", "fq_rmsnorm_forward",
            "fq_rmsnorm_backward", "fq_rmsnorm_backward_static"]
@@ -96,6 +96,8 @@ def lib():
         L.fq_qtensor_check.argtypes = [C.POINTER(fq_qtensor), C.POINTER(C.c_int32), C.c_void_p]
         L.fq_status_string.restype = C.c_char_p
         L.fq_status_string.argtypes = [C.c_int]
+        L.fq_header_tag.restype = C.c_char_p
+        L.fq_header_tag.argtypes = []
         for f in (L.fq_ctx_packed_bytes, L.fq_ctx_scales_bytes):
             f.restype = C.c_size_t
             f.argtypes = [C.c_int32, C.c_int32]
@@ -134,6 +136,11 @@ def lib():
 
 def status_string(status: int) -> str:
     return lib().fq_status_string(int(status)).decode()
+
+
+def fq_header_tag() -> str:
+    """Which fq.h the library was compiled with."""
+    return lib().fq_header_tag().decode()
 
 
 def _check(status, where):
@@ -181,7 +188,8 @@ _native_lib = None
 
 def _native_setup():
     """Looks for the native module and hands it the loaded library's entry points.  Without it, or with one that was
-    built for another torch or a torch without the quick way to the current stream, every call takes the Python code."""
+    built for another torch or another fq.h than the library, or a torch without the quick way to the current stream,
+    every call takes the Python code."""
     global _native, _native_lib
     _native_lib = lib()
     torch = _t()
@@ -190,7 +198,8 @@ def _native_setup():
         from . import _fqnative
     except ImportError:
         return
-    if device and raw and _fqnative.torch_version == torch.__version__:
+    same_header = 0 < len(_fqnative.header_tag) and _fqnative.header_tag == fq_header_tag()
+    if device and raw and same_header and _fqnative.torch_version == torch.__version__:
         _fqnative.setup(*(C.cast(f, C.c_void_p).value for f in (_native_lib.fq_quantize, _native_lib.fq_quantize_sr,
                                                                  _native_lib.fq_gemm)), device, raw)
         _native = _fqnative

@@ -1,10 +1,13 @@
 """Compile the HIP sources into paper_2503_08040_amd/libfq.so (gfx950 only)."""
+import hashlib
+import importlib.util
 import os
 import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfq.so")
+HEADER = os.path.join(HERE, "..", "include", "fq.h")
 SOURCES = ["fq_api.hip", "fq_quantize.hip", "fq_gemm.hip", "fq_gemm_tile.hip", "fq_gemm_ring.hip", "fq_group.hip", "fq_ctx.hip"]
 HEADERS = ["fq_device.h", "fq_gemm_unit.h", "fq_kernels.h", os.path.join("..", "..", "include", "fq.h")]
 
@@ -21,6 +24,13 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
 
 
 NATIVE = os.path.join(HERE, "_fqnative.so")
+NATIVE_SOURCE = os.path.join(CSRC, "fq_python.cpp")
+
+
+def header_flag() -> str:
+    """What the library and the Python module are compiled with, so that each knows the other's fq.h."""
+    with open(HEADER, "rb") as f:
+        return f'-DFQ_HEADER_TAG="{hashlib.sha256(f.read()).hexdigest()[:16]}"'
 
 
 def build_native() -> str:
@@ -31,10 +41,10 @@ def build_native() -> str:
     root = os.path.dirname(torch.__file__)
     inc = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include")]
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-           f'-DFQ_TORCH_VERSION="{torch.__version__}"',
+           f'-DFQ_TORCH_VERSION="{torch.__version__}"', header_flag(),
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", sysconfig.get_paths()["include"]] + \
           [f for d in inc for f in ("-isystem", d)] + \
-          ["-o", NATIVE, os.path.join(CSRC, "fq_python.cpp"), "-L", os.path.join(root, "lib"), "-ltorch_python",
+          ["-o", NATIVE, NATIVE_SOURCE, "-L", os.path.join(root, "lib"), "-ltorch_python",
            "-ltorch_cpu", "-lc10"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
@@ -90,7 +100,7 @@ def build_ablations(names=None, jobs: int = 6) -> list:
     names = list(ABLATIONS) if names is None else list(names)
 
     def one(name):
-        cmd = [hipcc] + HIPCC_FLAGS + ["-Wno-unused-but-set-variable", "-Wno-unused-variable"] + \
+        cmd = [hipcc] + HIPCC_FLAGS + [header_flag(), "-Wno-unused-but-set-variable", "-Wno-unused-variable"] + \
               ABLATIONS[name] + ["-o", ablation_lib(name)] + [os.path.join(CSRC, f) for f in SOURCES]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
@@ -101,19 +111,39 @@ def build_ablations(names=None, jobs: int = 6) -> list:
         return list(ex.map(one, names))
 
 
-def stale() -> bool:
-    if not os.path.exists(LIB):
+def _older(target, deps) -> bool:
+    if not os.path.exists(target):
         return True
-    t = os.path.getmtime(LIB)
-    deps = [os.path.join(CSRC, f) for f in SOURCES + HEADERS]
+    t = os.path.getmtime(target)
     return any(os.path.getmtime(d) > t for d in deps)
 
 
+def _stale_library() -> bool:
+    return _older(LIB, [os.path.join(CSRC, f) for f in SOURCES + HEADERS])
+
+
+def _stale_native() -> bool:
+    # the library itself does not need torch, the module does
+    return importlib.util.find_spec("torch") is not None and _older(NATIVE, [NATIVE_SOURCE, HEADER])
+
+
+def stale() -> bool:
+    return _stale_library() or _stale_native()
+
+
 def build(force: bool = True, extra_flags=()) -> str:
-    if not force and not stale():
-        return LIB
+    """The library and, beside it, the Python module, each if it is older than its sources or force is set."""
+    library, native = force or _stale_library(), force or _stale_native()
+    if library:
+        _build_library(extra_flags)
+    if native and importlib.util.find_spec("torch") is not None:
+        build_native()
+    return LIB
+
+
+def _build_library(extra_flags):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + HIPCC_FLAGS + list(extra_flags) + ["-o", LIB] + \
+    cmd = [hipcc] + HIPCC_FLAGS + [header_flag()] + list(extra_flags) + ["-o", LIB] + \
           [os.path.join(CSRC, f) for f in SOURCES]
     r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
@@ -122,11 +152,10 @@ def build(force: bool = True, extra_flags=()) -> str:
         raise RuntimeError(f"hipcc failed:\n{err}")
     if err.strip():
         print(err)
-    return LIB
 
 
 if __name__ == "__main__":
     print(build())
-    print(build_native())
+    print(NATIVE)
     print(build_tools())
     print(build_ablations())

@@ -552,4 +552,9 @@ const char* fq_status_string(fq_status s) {
   return "unknown status";
 }
 
+#ifndef FQ_HEADER_TAG
+#define FQ_HEADER_TAG ""
+#endif
+const char* fq_header_tag(void) { return FQ_HEADER_TAG; }
+
 }  // extern "C"

@@ -189,6 +189,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fqnative", nullptr, -1, methods, 
 
 PyMODINIT_FUNC PyInit__fqnative() {
   PyObject* m = PyModule_Create(&module);
-  if (m) PyModule_AddStringConstant(m, "torch_version", FQ_TORCH_VERSION);
+  if (m) {
+    PyModule_AddStringConstant(m, "torch_version", FQ_TORCH_VERSION);
+    PyModule_AddStringConstant(m, "header_tag", FQ_HEADER_TAG);      // of fq.h: the structs read and the entry points called
+  }
   return m;
 }

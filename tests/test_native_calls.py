@@ -1,8 +1,10 @@
 """fq_quantize, fq_quantize_sr and fq_gemm through the native module against the same calls through ctypes: the forms of
 their arguments, their errors, the current stream; and on the CPU, what the native module leaves to the Python code."""
 import ctypes as C
+import os
 import threading
 import time
+import types
 
 import numpy as np
 import pytest
@@ -11,7 +13,9 @@ from torch.overrides import TorchFunctionMode
 from torch.utils._python_dispatch import TorchDispatchMode
 
 import paper_2503_08040_amd as fq
-from paper_2503_08040_amd import _fqnative
+from paper_2503_08040_amd import build
+
+_fqnative = pytest.importorskip("paper_2503_08040_amd._fqnative", reason="the native module has not been built")
 
 gpu = pytest.mark.gpu
 
@@ -32,6 +36,45 @@ def test_anything_unusual_is_left_to_the_python_code():
     assert _fqnative.gemm(0, *args, torch.zeros(3, 5), None) is None              # not on the GPU
     with pytest.raises(TypeError):
         _fqnative.setup(1, 2)
+
+
+def test_the_module_belongs_to_the_library():
+    tag = build.header_flag().split('"')[1]
+    assert len(tag) == 16 and _fqnative.header_tag == tag == fq.fq_header_tag()
+
+
+@pytest.mark.parametrize("torch_version,header_tag,taken", [(torch.__version__, None, True), (torch.__version__, "", False),
+                                                            (torch.__version__, "0123456789abcdef", False),
+                                                            ("0.1", None, False)])
+def test_a_module_built_for_something_else_is_not_used(torch_version, header_tag, taken, monkeypatch):
+    calls = []
+    other = types.SimpleNamespace(torch_version=torch_version, setup=lambda *a: calls.append(a),
+                                  header_tag=_fqnative.header_tag if header_tag is None else header_tag)
+    monkeypatch.setattr(fq, "_fqnative", other)
+    monkeypatch.setattr(fq, "_native", None)
+    fq._native_setup()
+    assert (fq._native is other) == taken == (len(calls) == 1)
+
+
+def test_the_module_is_rebuilt_with_the_header(tmp_path, monkeypatch):
+    sources = {"SOURCES": "a.hip", "HEADERS": "a.h", "HEADER": "fq.h", "NATIVE_SOURCE": "m.cpp", "LIB": "l.so", "NATIVE": "m.so"}
+    for name, f in sources.items():
+        path = tmp_path / f
+        path.write_text("")
+        os.utime(path, (100, 200 if f.endswith(".so") else 100))
+        monkeypatch.setattr(build, name, [str(path)] if name in ("SOURCES", "HEADERS") else str(path))
+    built = []
+    monkeypatch.setattr(build, "_build_library", lambda flags: built.append("library"))
+    monkeypatch.setattr(build, "build_native", lambda: built.append("module"))
+    assert not build.stale() and build.build(force=False) and built == []
+    os.utime(tmp_path / "m.cpp", (300, 300))
+    assert build.stale() and build.build(force=False) and built == ["module"]
+    os.utime(tmp_path / "m.so", (400, 400))
+    assert not build.stale()
+    for h in ("fq.h", "a.h"):                       # the library's headers are listed, fq.h among them
+        os.utime(tmp_path / h, (500, 500))
+    assert build.stale() and build.build(force=False) and built == ["module", "library", "module"]
+    assert build.build() and built[3:] == ["library", "module"]
 
 
 @pytest.fixture
