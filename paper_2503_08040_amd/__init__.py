@@ -21,6 +21,8 @@ FQ_CRIT_NONE, FQ_CRIT_ABSMAX_GT, FQ_CRIT_ALL, FQ_CRIT_L1_GT, FQ_CRIT_L1REL_GT, F
 FQ_OP_NT, FQ_OP_NN, FQ_OP_TN = 0, 1, 2
 FQ_OUT_F32, FQ_OUT_BF16 = 0, 1
 FQ_TILES_256x256, FQ_TILES_32x32, FQ_TILES_128x64, FQ_TILES_128x128 = 0, 1, 2, 3
+FQ_FORM_256x256, FQ_FORM_32x32, FQ_FORM_128x64, FQ_FORM_128x128, FQ_FORM_LOADERS_128x64, FQ_FORM_LOADERS_128x128, \
+    FQ_FORM_LOADERS_128x256 = 0, 1, 2, 3, 4, 5, 6
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # FQ_LIBRARY: another build of the same library to load instead (the benchmark's ablation builds)
@@ -30,7 +32,7 @@ EXPORTS = ["fq_qtensor_bytes", "fq_qtensor_bind", "fq_quantize", "fq_quantize_sr
            "fq_threshold_update", "fq_gemm", "fq_gemm_plain", "fq_gemm_biased",
            "fq_gemm_debug_partials", "fq_codes_to_rowmajor", "fq_qtensor_check",
            "fq_status_string", "fq_header_tag", "fq_ctx_packed_bytes", "fq_ctx_scales_bytes", "fq_ctx_quantize",
-           "fq_ctx_dequantize", "fq_gemm_tile_plan", "fq_gemm_path",
+           "fq_ctx_dequantize", "fq_gemm_tile_plan", "fq_gemm_path", "fq_gemm_form",
            "fq_glu_forward", "fq_glu_backward", "fq_rmsnorm_forward",
            "fq_rmsnorm_backward", "fq_rmsnorm_backward_static"]
 
@@ -130,6 +132,8 @@ def lib():
         L.fq_gemm_tile_plan.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
         L.fq_gemm_path.restype = C.c_int
         L.fq_gemm_path.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int, C.POINTER(C.c_int32)]
+        L.fq_gemm_form.restype = C.c_int
+        L.fq_gemm_form.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int, C.c_int, C.POINTER(C.c_int32)]
         _lib = L
     return _lib
 
@@ -454,11 +458,19 @@ def fq_gemm_tile_plan(rows_out, cols_out, compute_units=0):
 
 def fq_gemm_path(rows_out, cols_out, compute_units=0, biased=False):
     """(FQ_TILES_*, their number, 128x384 tiles over the last block columns, over the last block rows) of
-    fq_gemm or fq_gemm_biased."""
+    fq_gemm or fq_gemm_biased, for an A that can fall back."""
     out = (C.c_int32 * 4)()
     _check(lib().fq_gemm_path(int(rows_out), int(cols_out), int(compute_units), int(bool(biased)), out),
            "fq_gemm_path")
     return tuple(int(v) for v in out)
+
+
+def fq_gemm_form(rows_out, cols_out, compute_units=0, biased=False, falls_back=True):
+    """(FQ_FORM_*, workgroups): the kernel of fq_gemm or fq_gemm_biased for an A that can fall back or cannot."""
+    out = (C.c_int32 * 2)()
+    _check(lib().fq_gemm_form(int(rows_out), int(cols_out), int(compute_units), int(bool(biased)),
+                              int(bool(falls_back)), out), "fq_gemm_form")
+    return int(out[0]), int(out[1])
 
 
 def _pitch(t):

@@ -496,6 +496,22 @@ fq_status fq_gemm_path(int32_t rows_out, int32_t cols_out, int32_t compute_units
   return FQ_OK;
 }
 
+static_assert((int)fq::SmallTile::kNone == FQ_FORM_256x256 && (int)fq::SmallTile::k32x32 == FQ_FORM_32x32 &&
+              (int)fq::SmallTile::k128x64 == FQ_FORM_128x64 && (int)fq::SmallTile::k128x128 == FQ_FORM_128x128 &&
+              (int)fq::SmallTile::kRing128x64 == FQ_FORM_LOADERS_128x64 &&
+              (int)fq::SmallTile::kRing128x128 == FQ_FORM_LOADERS_128x128 &&
+              (int)fq::SmallTile::kRing128x256 == FQ_FORM_LOADERS_128x256);
+
+fq_status fq_gemm_form(int32_t rows_out, int32_t cols_out, int32_t compute_units, int biased, int falls_back,
+                       int32_t form[2]) {
+  if (!form) return FQ_ERR_NULL;
+  if (rows_out < 0 || cols_out < 0) return FQ_ERR_SHAPE;
+  int out[2];
+  fq::gemm_form(rows_out, cols_out, compute_units, biased != 0, falls_back != 0, out);
+  form[0] = out[0]; form[1] = out[1];
+  return FQ_OK;
+}
+
 fq_status fq_gemm_debug_partials(fq_op op, const fq_qtensor* A, const fq_qtensor* B,
                                  int32_t k_block, int residual_term, int32_t* p_out,
                                  void* hip_stream) {

@@ -1138,27 +1138,58 @@ void gemm_tile_plan(int nib, int njb, int cus, int out[3]) {
   out[2] = plan.tail_tj;
 }
 
+namespace {
+
+int ceil_tiles(int n, int edge) { return (int)(((int64_t)n + edge - 1) / edge); }
+
+struct Choice {
+  TilePlan plan;
+  SmallTile tile;       // kNone: the plan's
+};
+
+// What a product is computed with; M and N are not zero.
+Choice choose(int M, int N, int cus, bool biased, bool slots) {
+  const TilePlan plan = plan_tiles(ceil_tiles(M, kBlock), ceil_tiles(N, kBlock), cus);
+  return {plan, plan_small(M, N, plan, cus, biased, slots)};
+}
+
+}  // namespace
+
+void gemm_form(int M, int N, int cus, bool biased, bool slots, int out[2]) {
+  out[0] = out[1] = 0;
+  if (M == 0 || N == 0) return;
+  const Choice c = choose(M, N, cus > 0 ? cus : planning_cus(), biased, slots);
+  constexpr int kEdges[][2] = {{0, 0}, {32, 32}, {128, 64}, {128, 128}, {128, 64}, {128, 128}, {128, 256}};
+  const int* const e = kEdges[(int)c.tile];
+  out[0] = (int)c.tile;
+  out[1] = c.tile == SmallTile::kNone ? c.plan.n_main + c.plan.tail_ni * c.plan.tail_tj
+                                      : ceil_tiles(M, e[0]) * ceil_tiles(N, e[1]);
+}
+
 void gemm_path(int M, int N, int cus, bool biased, int out[4]) {
-  auto blocks = [](int n) { return (int)(((int64_t)n + kBlock - 1) / kBlock); };
-  const int nib = blocks(M), njb = blocks(N);
   out[0] = out[1] = out[2] = out[3] = 0;
-  if (nib == 0 || njb == 0) return;
-  if (cus <= 0) cus = planning_cus();
-  const TilePlan plan = plan_tiles(nib, njb, cus);
-  const SmallTile tile = plan_small(M, N, plan, cus, biased, true);
-  auto small = [&](int kind, int r, int c) {
-    out[0] = kind;
-    out[1] = (int)(((int64_t)M + r - 1) / r) * (int)(((int64_t)N + c - 1) / c);
-  };
-  if (tile == SmallTile::k32x32) {
-    small(1, 32, 32);
-  } else if (tile == SmallTile::k128x64 || tile == SmallTile::kRing128x64) {
-    small(2, 128, 64);
-  } else if (tile != SmallTile::kNone) {
-    small(3, 128, 128);
-  } else {
-    out[1] = plan.n_main;
-    out[plan.tail_i0 > 0 ? 3 : 2] = plan.tail_ni * plan.tail_tj;
+  if (M == 0 || N == 0) return;
+  const Choice c = choose(M, N, cus > 0 ? cus : planning_cus(), biased, true);
+  switch (c.tile) {
+    case SmallTile::kNone:
+      out[1] = c.plan.n_main;
+      out[c.plan.tail_i0 > 0 ? 3 : 2] = c.plan.tail_ni * c.plan.tail_tj;
+      return;
+    case SmallTile::k32x32:
+      out[0] = 1;
+      out[1] = ceil_tiles(M, 32) * ceil_tiles(N, 32);
+      return;
+    case SmallTile::k128x64:
+    case SmallTile::kRing128x64:
+      out[0] = 2;
+      out[1] = ceil_tiles(M, 128) * ceil_tiles(N, 64);
+      return;
+    case SmallTile::k128x128:
+    case SmallTile::kRing128x128:
+    case SmallTile::kRing128x256:
+      out[0] = 3;
+      out[1] = ceil_tiles(M, 128) * ceil_tiles(N, 128);
+      return;
   }
 }
 
@@ -1170,10 +1201,8 @@ hipError_t launch_gemm(const GemmParams& p_in, bool debug, hipStream_t st) {
   }
   if (p_in.nib == 0 || p_in.njb == 0) return hipSuccess;
   GemmParams p = p_in;
-  const int cus = planning_cus();
-  const TilePlan plan = plan_tiles(p.nib, p.njb, cus);
-  if (const SmallTile tile = plan_small(p.M, p.N, plan, cus, p.biased != 0, p.a_slot != nullptr); tile != SmallTile::kNone)
-    return launch_gemm_small(p, tile, st);
+  const auto [plan, tile] = choose(p.M, p.N, planning_cus(), p.biased != 0, p.a_slot != nullptr);
+  if (tile != SmallTile::kNone) return launch_gemm_small(p, tile, st);
   p.n_main = plan.n_main;
   p.main_ti = plan.main_ti;
   p.main_tj = plan.main_tj;

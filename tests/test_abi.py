@@ -192,3 +192,44 @@ def test_gemm_path_says_what_covers_the_output():
     p = (C.c_int32 * 4)()
     assert fq.lib().fq_gemm_path(-1, 5, 4, 0, p) == fq.FQ_ERR_SHAPE
     assert fq.lib().fq_gemm_path(5, 5, 4, 0, None) == fq.FQ_ERR_NULL
+
+
+def test_gemm_form_says_which_kernel_runs():
+    """fq_gemm_form (host-only): the kernels of the documented shapes, as many workgroups as cover the output, and the
+    tiles that fq_gemm_path names for an A that can fall back."""
+    import random
+    ceil = lambda a, b: -(-a // b)
+    edges = {fq.FQ_FORM_32x32: (32, 32, fq.FQ_TILES_32x32), fq.FQ_FORM_128x64: (128, 64, fq.FQ_TILES_128x64),
+             fq.FQ_FORM_128x128: (128, 128, fq.FQ_TILES_128x128), fq.FQ_FORM_LOADERS_128x64: (128, 64, fq.FQ_TILES_128x64),
+             fq.FQ_FORM_LOADERS_128x128: (128, 128, fq.FQ_TILES_128x128),
+             fq.FQ_FORM_LOADERS_128x256: (128, 256, fq.FQ_TILES_128x128)}
+    rng = random.Random(2)
+    seen = set()
+    for _ in range(800):
+        rows, cols = (int(round(2 ** rng.uniform(0, 13.5))) for _ in range(2))
+        cus, biased = rng.choice([1, 2, 3, 8, 64, 256, 304]), rng.random() < 0.3
+        for falls_back in (True, False):
+            form, n = fq.fq_gemm_form(rows, cols, cus, biased, falls_back)
+            seen.add((form, falls_back))
+            if form != fq.FQ_FORM_256x256:
+                r, c, _ = edges[form]
+                assert n == ceil(rows, r) * ceil(cols, c)
+                # the kernels with wavefronts that only load run one round of workgroups, or two of the smallest
+                assert form < fq.FQ_FORM_LOADERS_128x64 or n <= cus * (2 if form == fq.FQ_FORM_LOADERS_128x64 else 1)
+            if falls_back:
+                path = fq.fq_gemm_path(rows, cols, cus, biased)
+                assert path[0] == (edges[form][2] if form else fq.FQ_TILES_256x256)
+                if form == fq.FQ_FORM_256x256:
+                    assert n == path[1] + path[2] + path[3]
+    assert seen == {(f, b) for f in range(7) for b in (True, False)}
+    for rows, cols, form, n in [(33, 11008, fq.FQ_FORM_32x32, 688), (777, 2200, fq.FQ_FORM_LOADERS_128x64, 245),
+                                (512, 4096, fq.FQ_FORM_LOADERS_128x64, 256), (2048, 2048, fq.FQ_FORM_LOADERS_128x128, 256),
+                                (2048, 4096, fq.FQ_FORM_LOADERS_128x256, 256), (1536, 4096, fq.FQ_FORM_128x64, 768),
+                                (3072, 3072, fq.FQ_FORM_128x64, 1152), (2048, 9984, fq.FQ_FORM_128x128, 1248),
+                                (4096, 11008, fq.FQ_FORM_256x256, 768)]:
+        for falls_back in (True, False):
+            assert fq.fq_gemm_form(rows, cols, 256, falls_back=falls_back) == (form, n)
+    assert fq.fq_gemm_form(0, 5, 256) == fq.fq_gemm_form(5, 0, 256) == (0, 0)
+    p = (C.c_int32 * 2)()
+    assert fq.lib().fq_gemm_form(-1, 5, 4, 0, 0, p) == fq.FQ_ERR_SHAPE
+    assert fq.lib().fq_gemm_form(5, 5, 4, 0, 0, None) == fq.FQ_ERR_NULL
