@@ -401,13 +401,14 @@ fq_status fq_gemm_tile_plan(int32_t rows_out, int32_t cols_out, int32_t compute_
 
 /*
  * The tiles that fq_gemm (biased = 0) or fq_gemm_biased (1) computes a rows_out x cols_out output
- * with, for an A that can fall back (host-only inspection, compute_units as above).  path[0] = 1: 32 x 32,
+ * with, for an A that can fall back and a long contraction (host-only inspection, compute_units as above).  path[0] = 1: 32 x 32,
  * 2: 128 x 64, 3: 128 x 128 tiles (one per workgroup, or two side by side), path[1] = their number; these are
  * chosen where the output is less than about a chip's worth of large tiles.  path[0] = 0: the large ones,
  * path[1] = the number of 256 x 256 tiles, path[2] and path[3] = the number of 128 x 384 tiles over the last
  * block columns or, where that ends earlier, the last block rows.  An A that cannot fall back (its criterion is
- * FQ_CRIT_NONE, whatever its capacity) takes the large tiles on somewhat smaller outputs already; which form that is
- * and which of two kernels runs tiles of one size, fq_gemm_form says.  All zero for an empty output.  fq_gemm's
+ * FQ_CRIT_NONE, whatever its capacity) takes the large tiles on somewhat smaller outputs already, and short contractions
+ * (up to 15 k-blocks) can take other small tiles; which those are and which of two kernels runs tiles of one size,
+ * fq_gemm_form says.  All zero for an empty output.  fq_gemm's
  * results do not depend on the tiles: every output element is accumulated in Alg. 1's order.
  */
 fq_status fq_gemm_path(int32_t rows_out, int32_t cols_out, int32_t compute_units, int biased,
@@ -426,13 +427,13 @@ typedef enum fq_form {
 } fq_form;
 
 /*
- * The kernel that fq_gemm (biased = 0) or fq_gemm_biased (1) launches for a rows_out x cols_out output of blocks of
- * 128 and an A that can fall back (falls_back = 1: quantized with a criterion) or cannot (0: with FQ_CRIT_NONE or
+ * The kernel that fq_gemm (biased = 0) or fq_gemm_biased (1) launches for a rows_out x cols_out output, a
+ * contraction of that length, blocks of 128 and an A that can fall back (falls_back = 1: quantized with a criterion) or cannot (0: with FQ_CRIT_NONE or
  * fq_quantize_sr): form[0] is an fq_form, form[1] the number of workgroups (0 for an empty output).  Host-only
  * inspection, compute_units as above.
  */
-fq_status fq_gemm_form(int32_t rows_out, int32_t cols_out, int32_t compute_units, int biased, int falls_back,
-                       int32_t form[2]);
+fq_status fq_gemm_form(int32_t rows_out, int32_t cols_out, int32_t contraction, int32_t compute_units, int biased,
+                       int falls_back, int32_t form[2]);
 
 /* (With blocks of 64 or 32, k_block counts blocks of that size.)
  * The INT32 block product of k-block `k_block` alone (Alg. 1's INT x INT

@@ -133,7 +133,7 @@ def lib():
         L.fq_gemm_path.restype = C.c_int
         L.fq_gemm_path.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int, C.POINTER(C.c_int32)]
         L.fq_gemm_form.restype = C.c_int
-        L.fq_gemm_form.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int, C.c_int, C.POINTER(C.c_int32)]
+        L.fq_gemm_form.argtypes = [C.c_int32] * 4 + [C.c_int, C.c_int, C.POINTER(C.c_int32)]
         _lib = L
     return _lib
 
@@ -458,17 +458,17 @@ def fq_gemm_tile_plan(rows_out, cols_out, compute_units=0):
 
 def fq_gemm_path(rows_out, cols_out, compute_units=0, biased=False):
     """(FQ_TILES_*, their number, 128x384 tiles over the last block columns, over the last block rows) of
-    fq_gemm or fq_gemm_biased, for an A that can fall back."""
+    fq_gemm or fq_gemm_biased, for an A that can fall back and a long contraction."""
     out = (C.c_int32 * 4)()
     _check(lib().fq_gemm_path(int(rows_out), int(cols_out), int(compute_units), int(bool(biased)), out),
            "fq_gemm_path")
     return tuple(int(v) for v in out)
 
 
-def fq_gemm_form(rows_out, cols_out, compute_units=0, biased=False, falls_back=True):
+def fq_gemm_form(rows_out, cols_out, contraction, compute_units=0, biased=False, falls_back=True):
     """(FQ_FORM_*, workgroups): the kernel of fq_gemm or fq_gemm_biased for an A that can fall back or cannot."""
     out = (C.c_int32 * 2)()
-    _check(lib().fq_gemm_form(int(rows_out), int(cols_out), int(compute_units), int(bool(biased)),
+    _check(lib().fq_gemm_form(int(rows_out), int(cols_out), int(contraction), int(compute_units), int(bool(biased)),
                               int(bool(falls_back)), out), "fq_gemm_form")
     return int(out[0]), int(out[1])
 

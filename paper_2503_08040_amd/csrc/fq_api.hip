@@ -502,12 +502,12 @@ static_assert((int)fq::SmallTile::kNone == FQ_FORM_256x256 && (int)fq::SmallTile
               (int)fq::SmallTile::kRing128x128 == FQ_FORM_LOADERS_128x128 &&
               (int)fq::SmallTile::kRing128x256 == FQ_FORM_LOADERS_128x256);
 
-fq_status fq_gemm_form(int32_t rows_out, int32_t cols_out, int32_t compute_units, int biased, int falls_back,
-                       int32_t form[2]) {
+fq_status fq_gemm_form(int32_t rows_out, int32_t cols_out, int32_t contraction, int32_t compute_units, int biased,
+                       int falls_back, int32_t form[2]) {
   if (!form) return FQ_ERR_NULL;
-  if (rows_out < 0 || cols_out < 0) return FQ_ERR_SHAPE;
+  if (rows_out < 0 || cols_out < 0 || contraction < 0) return FQ_ERR_SHAPE;
   int out[2];
-  fq::gemm_form(rows_out, cols_out, compute_units, biased != 0, falls_back != 0, out);
+  fq::gemm_form(rows_out, cols_out, contraction, compute_units, biased != 0, falls_back != 0, out);
   form[0] = out[0]; form[1] = out[1];
   return FQ_OK;
 }

@@ -1072,6 +1072,19 @@ TilePlan plan_tiles(int nib, int njb, int cus) {
 //   128 x 64    380 alone on its compute unit, 675 a pair       (512 x 8192 x 4096; 1024 x 8192 x 4096)
 //   128 x 128   600                                             (1024 x 8192 x 4096)
 //   128 x 256   1090                                            (2048 x 8192 x 4096)
+// Those start later: nothing is multiplied before a loader has brought the first items, and with residual slots the slots
+// before them.  So they are for contractions that make up for it.  M x K x N, bf16, us, without loaders -> with them:
+//   without slots     2048 x 256 x 2048   5.9 -> 6.4    512 x 256 x 4096   4.6 -> 4.8    2048 x 896 x 4096   14.9 -> 14.1
+//                     2048 x 1024 x 2048  9.7 -> 9.4    512 x 1024 x 4096  7.4 -> 7.0
+//   10 % flagged      2048 x 256 x 2048   6.2 -> 6.9    512 x 256 x 4096   5.0 -> 5.4    2048 x 896 x 4096   16.3 -> 17.3
+//   20 % flagged      2048 x 1280 x 2048 13.0 -> 12.7   512 x 1280 x 4096  9.2 -> 8.9    2048 x 1536 x 4096  24.6 -> 26.3
+//                     2048 x 1536 x 2048 15.0 -> 13.8   512 x 1536 x 4096 10.4 -> 10.1   2048 x 2048 x 4096  33.4 -> 32.2
+// Hence 8 k-blocks without slots, 12 with, 16 for 128 x 256.  On fewer, 128 x 64 tiles without loaders are priced by their
+// latency, 520 for one, and 390 for each of more.  32 x 32 tiles start soonest: with up to five of them per compute unit
+// they are as fast without slots and faster with, as long as A stays in an XCD's L2, 4 MiB (20 % flagged, 32 x 32 and
+// loaders: 1024 x 2048 x 1280 10.4 and 11.5, x 4096 20.1 and 18.5; 2048 x 1536 x 640 9.3 and 9.7, x 2048 13.0 and 11.8;
+// 4096 x 1024 x 320 9.5 and 8.0).  With six per compute unit the loaders take 5 to 15 % less without slots from 8 k-blocks
+// on, as much with 20 % flagged from 16 on (1024 x 1536 x 1536 8.6 and 8.0, 9.6 and 9.8), up to 7 % more with half of them.
 // So 2048 x 4096 x 4096 takes 128 x 256 (39 us without flagged blocks, 43.5 with 128 x 128 pairs, 76 with
 // 256 x 256), 1536 x 4096 x 4096 three 128 x 64 per compute unit (34.1; 35.1 with 128 x 256, 36.0 with 128 x 64 of
 // the ring in two rounds), 3072^3 128 x 64 too (42; 44 and 48 in two and three rounds of the ring's 128 x 64 and
@@ -1084,19 +1097,22 @@ TilePlan plan_tiles(int nib, int njb, int cus) {
 // of their neighbours by more than 3 %.  The smaller tiles have no biased form, so fq_gemm_biased takes them where
 // they beat its own kernel: 2048 x 4096 x 4096 (42 us against 68), but not 2048 x 4096 x 11008 (129 against 117)
 // or 3072 x 11008 x 4096 (170 against 151), which fq_gemm computes on 128 x 128.
-SmallTile plan_small(int M, int N, const TilePlan& big, int cus, bool biased, bool slots) {
+SmallTile plan_small(int M, int N, int nkb, const TilePlan& big, int cus, bool biased, bool slots) {
   const double c = cus > 0 ? cus : 256;
   auto tiles = [&](int r, int s) { return (double)((M + r - 1) / r) * ((N + s - 1) / s) / c; };
   const double n64 = tiles(128, 64), n128 = tiles(128, 128);
   const double pairs = std::floor(n128 / 2.0), rest = n128 - 2.0 * pairs;
   constexpr double kNever = 1e300;
+  constexpr int64_t kXcdL2 = 4 << 20;
+  const bool loaders = nkb >= (slots ? 12 : 8);
+  const double ring64 = (int64_t)M * nkb * kBlock >= kXcdL2 ? 380.0 : slots && nkb < 16 ? 520.0 : 400.0;
   const struct { SmallTile kind; double est; } form[] = {
       {SmallTile::k32x32, std::max(240.0, 80.0 * tiles(32, 32))},
-      {SmallTile::k128x64, n64 <= 3.0 ? 1000.0 : 390.0 * n64},
+      {SmallTile::k128x64, n64 > 3.0 ? 390.0 * n64 : loaders ? 1000.0 : std::max(520.0, 390.0 * (n64 <= 2.0 ? std::ceil(n64) : n64))},
       {SmallTile::k128x128, 1360.0 * pairs + (rest > 1.0 ? 1360.0 : rest > 0.0 ? 850.0 : 0.0)},
-      {SmallTile::kRing128x64, n64 <= 1.0 ? 380.0 : n64 <= 2.0 ? 675.0 : kNever},
-      {SmallTile::kRing128x128, n128 <= 1.0 ? 600.0 : kNever},
-      {SmallTile::kRing128x256, tiles(128, 256) <= 1.0 ? 1090.0 : kNever}};
+      {SmallTile::kRing128x64, !loaders ? kNever : n64 <= 1.0 ? ring64 : n64 <= 2.0 ? 675.0 : kNever},
+      {SmallTile::kRing128x128, loaders && n128 <= 1.0 ? 600.0 : kNever},
+      {SmallTile::kRing128x256, loaders && (!slots || nkb >= 16) && tiles(128, 256) <= 1.0 ? 1090.0 : kNever}};
   double best = (slots && !biased ? 2340.0 : 2050.0) * big.cost;
   SmallTile tile = SmallTile::kNone;
   for (const auto& f : form)
@@ -1147,18 +1163,18 @@ struct Choice {
   SmallTile tile;       // kNone: the plan's
 };
 
-// What a product is computed with; M and N are not zero.
-Choice choose(int M, int N, int cus, bool biased, bool slots) {
+// What a product of nkb k-blocks is computed with; M and N are not zero.
+Choice choose(int M, int N, int nkb, int cus, bool biased, bool slots) {
   const TilePlan plan = plan_tiles(ceil_tiles(M, kBlock), ceil_tiles(N, kBlock), cus);
-  return {plan, plan_small(M, N, plan, cus, biased, slots)};
+  return {plan, plan_small(M, N, nkb, plan, cus, biased, slots)};
 }
 
 }  // namespace
 
-void gemm_form(int M, int N, int cus, bool biased, bool slots, int out[2]) {
+void gemm_form(int M, int N, int K, int cus, bool biased, bool slots, int out[2]) {
   out[0] = out[1] = 0;
   if (M == 0 || N == 0) return;
-  const Choice c = choose(M, N, cus > 0 ? cus : planning_cus(), biased, slots);
+  const Choice c = choose(M, N, ceil_tiles(K, kBlock), cus > 0 ? cus : planning_cus(), biased, slots);
   constexpr int kEdges[][2] = {{0, 0}, {32, 32}, {128, 64}, {128, 128}, {128, 64}, {128, 128}, {128, 256}};
   const int* const e = kEdges[(int)c.tile];
   out[0] = (int)c.tile;
@@ -1169,7 +1185,8 @@ void gemm_form(int M, int N, int cus, bool biased, bool slots, int out[2]) {
 void gemm_path(int M, int N, int cus, bool biased, int out[4]) {
   out[0] = out[1] = out[2] = out[3] = 0;
   if (M == 0 || N == 0) return;
-  const Choice c = choose(M, N, cus > 0 ? cus : planning_cus(), biased, true);
+  constexpr int kLong = 1 << 20;      // k-blocks
+  const Choice c = choose(M, N, kLong, cus > 0 ? cus : planning_cus(), biased, true);
   switch (c.tile) {
     case SmallTile::kNone:
       out[1] = c.plan.n_main;
@@ -1201,7 +1218,7 @@ hipError_t launch_gemm(const GemmParams& p_in, bool debug, hipStream_t st) {
   }
   if (p_in.nib == 0 || p_in.njb == 0) return hipSuccess;
   GemmParams p = p_in;
-  const auto [plan, tile] = choose(p.M, p.N, planning_cus(), p.biased != 0, p.a_slot != nullptr);
+  const auto [plan, tile] = choose(p.M, p.N, p.nkb, planning_cus(), p.biased != 0, p.a_slot != nullptr);
   if (tile != SmallTile::kNone) return launch_gemm_small(p, tile, st);
   p.n_main = plan.n_main;
   p.main_ti = plan.main_ti;

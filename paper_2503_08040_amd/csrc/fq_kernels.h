@@ -146,10 +146,10 @@ hipError_t launch_gemm_group(const GemmParams& p, bool debug, hipStream_t st);
 void gemm_tile_plan(int nib, int njb, int cus, int out[3]);
 // out = {0 and those with 2x2-block tiles, or 1, 2, 3 and the number of 32x32, 128x64, 128x128 tiles; 1x3-block
 // tiles over the last block columns, over the last block rows}: the tiles launch_gemm covers the output with if A has
-// residual slots.
+// residual slots and the contraction is long.
 void gemm_path(int M, int N, int cus, bool biased, int out[4]);
 // out = {SmallTile, workgroups}: what launch_gemm launches for an A with or without residual slots.
-void gemm_form(int M, int N, int cus, bool biased, bool slots, int out[2]);
+void gemm_form(int M, int N, int K, int cus, bool biased, bool slots, int out[2]);
 hipError_t launch_rmsnorm(const RmsParams& p, bool backward, hipStream_t st);
 hipError_t launch_glu(const GluParams& p, bool backward, hipStream_t st);
 hipError_t launch_ctx(const CtxParams& p, bool dequantize, hipStream_t st);

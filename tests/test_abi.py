@@ -195,8 +195,8 @@ def test_gemm_path_says_what_covers_the_output():
 
 
 def test_gemm_form_says_which_kernel_runs():
-    """fq_gemm_form (host-only): the kernels of the documented shapes, as many workgroups as cover the output, and the
-    tiles that fq_gemm_path names for an A that can fall back."""
+    """fq_gemm_form (host-only): the kernels of the documented shapes, as many workgroups as cover the output, and for a
+    long contraction and an A that can fall back the tiles that fq_gemm_path names."""
     import random
     ceil = lambda a, b: -(-a // b)
     edges = {fq.FQ_FORM_32x32: (32, 32, fq.FQ_TILES_32x32), fq.FQ_FORM_128x64: (128, 64, fq.FQ_TILES_128x64),
@@ -209,7 +209,7 @@ def test_gemm_form_says_which_kernel_runs():
         rows, cols = (int(round(2 ** rng.uniform(0, 13.5))) for _ in range(2))
         cus, biased = rng.choice([1, 2, 3, 8, 64, 256, 304]), rng.random() < 0.3
         for falls_back in (True, False):
-            form, n = fq.fq_gemm_form(rows, cols, cus, biased, falls_back)
+            form, n = fq.fq_gemm_form(rows, cols, 2 ** 24, cus, biased, falls_back)
             seen.add((form, falls_back))
             if form != fq.FQ_FORM_256x256:
                 r, c, _ = edges[form]
@@ -228,8 +228,30 @@ def test_gemm_form_says_which_kernel_runs():
                                 (3072, 3072, fq.FQ_FORM_128x64, 1152), (2048, 9984, fq.FQ_FORM_128x128, 1248),
                                 (4096, 11008, fq.FQ_FORM_256x256, 768)]:
         for falls_back in (True, False):
-            assert fq.fq_gemm_form(rows, cols, 256, falls_back=falls_back) == (form, n)
-    assert fq.fq_gemm_form(0, 5, 256) == fq.fq_gemm_form(5, 0, 256) == (0, 0)
+            assert fq.fq_gemm_form(rows, cols, 4096, 256, falls_back=falls_back) == (form, n)
+    assert fq.fq_gemm_form(0, 5, 128, 256) == fq.fq_gemm_form(5, 0, 128, 256) == (0, 0)
+    assert fq.fq_gemm_form(5, 5, 0, 256) == (fq.FQ_FORM_32x32, 1)
     p = (C.c_int32 * 2)()
-    assert fq.lib().fq_gemm_form(-1, 5, 4, 0, 0, p) == fq.FQ_ERR_SHAPE
-    assert fq.lib().fq_gemm_form(5, 5, 4, 0, 0, None) == fq.FQ_ERR_NULL
+    assert fq.lib().fq_gemm_form(-1, 5, 128, 4, 0, 0, p) == fq.FQ_ERR_SHAPE
+    assert fq.lib().fq_gemm_form(5, 5, -1, 4, 0, 0, p) == fq.FQ_ERR_SHAPE
+    assert fq.lib().fq_gemm_form(5, 5, 128, 4, 0, 0, None) == fq.FQ_ERR_NULL
+
+
+def test_short_contractions_take_tiles_without_loaders():
+    """The tiles with wavefronts that only load start later than the others, which a short contraction does not make up
+    for: with them 2048 x 2048 outputs of two k-blocks took 9 to 15 % longer."""
+    loaders = (fq.FQ_FORM_LOADERS_128x64, fq.FQ_FORM_LOADERS_128x128, fq.FQ_FORM_LOADERS_128x256)
+    form = lambda rows, cols, nkb, falls_back: fq.fq_gemm_form(rows, cols, 128 * nkb, 256, falls_back=falls_back)[0]
+    for rows, cols, without in [(512, 4096, fq.FQ_FORM_128x64), (777, 2200, fq.FQ_FORM_128x64),
+                                (2048, 2048, fq.FQ_FORM_128x64), (3496, 640, fq.FQ_FORM_32x32),
+                                (1838, 1280, fq.FQ_FORM_32x32), (2048, 4096, fq.FQ_FORM_128x128),
+                                (1600, 4000, fq.FQ_FORM_128x64), (128, 10368, fq.FQ_FORM_32x32)]:
+        for falls_back in (True, False):
+            forms = [form(rows, cols, nkb, falls_back) for nkb in range(40)]
+            first = next(k for k, f in enumerate(forms) if f in loaders)
+            assert forms[:first] == [without] * first and len(set(forms[first:])) == 1
+            wide = forms[-1] == fq.FQ_FORM_LOADERS_128x256
+            assert first == (8 if not falls_back else 16 if wide or (rows, cols) == (128, 10368) else 12)
+    # up to five 32 x 32 tiles per compute unit: as long as A fits an XCD's L2
+    assert form(1024, 1280, 31, True) == form(1024, 1280, 31, False) == fq.FQ_FORM_32x32
+    assert form(1024, 1280, 32, True) == form(1024, 1280, 32, False) == fq.FQ_FORM_LOADERS_128x64
