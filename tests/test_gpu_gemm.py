@@ -142,6 +142,7 @@ def test_mixed_tile_geometries(op, sa, sb, cus, kind, monkeypatch):
     path = fq.fq_gemm_path(Mo, No)
     assert path[0] == kind, f"path {path}"
     assert kind != LARGE or (path[1] > 0 and path[2] > 0), f"path {path} does not use both geometries"
+    assert fq.fq_gemm_form(Mo, No, sa[0] if op == fq.FQ_OP_TN else sa[1])[0] == kind, "another kernel's tiles of that size"
     assert int(oa.fb_count[0]) > 0
     c = _check_gemm(op, ga, gb, oa, ob, f"mixed op={op} {sa}x{sb} cus={cus} path={path}", partials=False)
     # the tiles do not change a single bit of the result
@@ -156,7 +157,7 @@ def test_scale_products_in_the_subnormal_range(cols, cus, kind, monkeypatch):
     the scales, the FMA with it and the accumulator must behave as IEEE binary32 without
     flush-to-zero on both sides."""
     monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
-    assert fq.fq_gemm_path(256, cols)[0] == kind
+    assert fq.fq_gemm_path(256, cols)[0] == fq.fq_gemm_form(256, cols, 512)[0] == kind
     rng = np.random.default_rng(44)
     a = rng.standard_normal((256, 512))
     for bk, k in enumerate((-126, -118, -110, -104)):
@@ -192,7 +193,7 @@ def test_strided_output_and_reuse():
 @pytest.mark.parametrize("cus,kind", [(256, fq.FQ_TILES_32x32), (3, T128x64), (2, T128x128), (1, LARGE)])
 def test_empty_contraction_and_empty_output(cus, kind, monkeypatch):
     monkeypatch.setenv("FQ_GEMM_CUS", str(cus))
-    assert fq.fq_gemm_path(256, 256)[0] == kind
+    assert fq.fq_gemm_path(256, 256)[0] == fq.fq_gemm_form(256, 256, 0, falls_back=False)[0] == kind
     a = fq.fq_quantize(torch.empty((256, 0), dtype=torch.bfloat16, device="cuda"),
                        fq.FQ_CRIT_NONE, 0.0, capacity=0)
     b = fq.fq_quantize(torch.empty((256, 0), dtype=torch.bfloat16, device="cuda"),
@@ -242,7 +243,7 @@ def test_capacity_overflow_poisons_exactly_the_affected_block_rows(shape_a, shap
     bad = (slot == -2).any(axis=1)
     assert bad.any()
     path = fq.fq_gemm_path(shape_a[0], shape_b[0])
-    assert path[0] == kind and (path[2] > 0) == tail
+    assert path[0] == fq.fq_gemm_form(shape_a[0], shape_b[0], shape_a[1])[0] == kind and (path[2] > 0) == tail
     gu.announce(f"gemm with overflowed residual slots, path {path}")
     c = fq.fq_gemm(fq.FQ_OP_NT, ga, gb).cpu().numpy()
     ref = fqo.gemm(fqo.OP_NT, fqo.quantize(a_bits, 128, fqo.CRIT_ALL, 0.0),
