@@ -255,3 +255,14 @@ def test_short_contractions_take_tiles_without_loaders():
     # up to five 32 x 32 tiles per compute unit: as long as A fits an XCD's L2
     assert form(1024, 1280, 31, True) == form(1024, 1280, 31, False) == fq.FQ_FORM_32x32
     assert form(1024, 1280, 32, True) == form(1024, 1280, 32, False) == fq.FQ_FORM_LOADERS_128x64
+
+
+def test_outputs_that_take_large_tiles_only_if_a_cannot_fall_back():
+    """The line of the large tiles: 2050 ns per k-block without residual slots, 2340 with them, against 128 x 64 tiles of
+    390 each and pairs of 128 x 128 of 1360, on 256 compute units."""
+    kinds = lambda rows, cols: [fq.fq_gemm_form(rows, cols, 4096, 256, falls_back=f)[0] for f in (True, False)]
+    for rows, cols, tiles in [(1280, 9700, fq.FQ_FORM_128x128), (4096, 5760, fq.FQ_FORM_128x128),
+                              (1400, 8001, fq.FQ_FORM_128x64), (2048, 11008, fq.FQ_FORM_128x128)]:
+        assert kinds(rows, cols) == [tiles, fq.FQ_FORM_256x256]
+    assert kinds(3584, 3584) == kinds(1280, 9856) == [fq.FQ_FORM_256x256] * 2      # 6.1 and 6.02 128 x 64 tiles per unit
+    assert kinds(1280, 8576) == kinds(2560, 4096) == [fq.FQ_FORM_128x64] * 2       # 5.2 and 5

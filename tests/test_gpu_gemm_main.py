@@ -72,7 +72,8 @@ def test_patterns_of_flagged_blocks(pattern, monkeypatch):
 # outputs on which only an A without residual slots takes 256 x 256 tiles, in one round and with 128 x 384 tails
 @pytest.mark.parametrize("M,N", [(1280, 9700), (4096, 5760), (1400, 8001)])
 def test_planner_line_depends_on_slots(M, N):
-    assert fq.fq_gemm_path(M, N)[0] != fq.FQ_TILES_256x256
+    assert fq.fq_gemm_form(M, N, 300)[0] != fq.FQ_FORM_256x256
+    assert fq.fq_gemm_form(M, N, 300, falls_back=False)[0] == fq.FQ_FORM_256x256
     g = torch.Generator(device="cuda")
     g.manual_seed(M)
     x = torch.randn(M, 300, device="cuda", generator=g).bfloat16()
