@@ -44,6 +44,7 @@
 #include <type_traits>
 
 #include "fq_device.h"
+#include "fq_gemm_unit.h"
 #include "fq_kernels.h"
 
 // Ablation switches (measurement support; the library itself is built with none of them, and a
@@ -69,16 +70,10 @@ namespace {
 
 constexpr int kThreads = 512;
 constexpr int kMaxDevices = 64;   // per-device host-side caches
-constexpr int kXcds = 8;      // accelerator complex dies, each with a private L2
 constexpr int kGroupN = 4;    // tile columns per rasterization group
 constexpr int kRingBytes = 2 * kBlockBytes;     // one A pair or one B pair
 constexpr int kLdsBytes = 5 * kRingBytes;       // all 160 KiB: two A sets, two B sets, the residual blocks of an
                                                 // A set; the epilogue staging patches re-use the same memory
-
-typedef __attribute__((address_space(3))) void lds_void;
-
-// Address of a __shared__ object as the LDS instructions take it.
-__device__ __forceinline__ uint32_t lds_address(int8_t* q) { return (uint32_t)(uintptr_t)(lds_void*)q; }
 
 // One wavefront copies 4 KiB (4 fragments) global -> LDS with direct loads.  `src` and `lds_dst` are
 // wave-uniform; the per-lane part of the address is the 32-bit offset lane*16 (scalar-base form), and
@@ -88,29 +83,11 @@ __device__ __forceinline__ uint32_t lds_address(int8_t* q) { return (uint32_t)(u
 // ones issued just before included.  Whoever reads the LDS waits with s_waitcnt vmcnt(0) and a barrier.
 // 8192^3 with a fifth of the blocks flagged 678 -> 665 us, 4096 x 4096 x 11008 220.6 -> 217.5.
 __device__ __forceinline__ void stage_quarter_block(const int8_t* src, uint32_t lds_dst, int lane) {
-  const unsigned voff = (unsigned)lane * 16u;
-  // make the uniformity of the base explicit (folds away when it is already scalar)
-  const uint64_t a = reinterpret_cast<uint64_t>(src);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-  uint64_t base = ((uint64_t)hi << 32) | lo;
-  const uint32_t to = __builtin_amdgcn_readfirstlane(lds_dst);
 #ifdef FQ_ABLATE_NO_DMA
-  if (voff != 0xFFFFFFFFu) return;
+  if (lane >= 0) return;
 #endif
-  static_assert(kFragBytes == 1024, "offsets below");
-  // The block keeps the wait states its loads need by itself, as the compiler does not look inside: the
-  // second move is the one between a write to m0 and its use, and leaves the base written by the scalar
-  // unit, whatever wrote it before (a vector instruction would have to be five wait states away).
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"     // that m0 is a register nobody keeps values in is known
-  asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %0\n\t"
-               "global_load_lds_dwordx4 %2, %0\n\t"
-               "global_load_lds_dwordx4 %2, %0 offset:1024\n\t"
-               "global_load_lds_dwordx4 %2, %0 offset:2048\n\t"
-               "global_load_lds_dwordx4 %2, %0 offset:3072"
-               : "+s"(base) : "s"(to), "v"(voff) : "memory", "m0");
-#pragma clang diagnostic pop
+  static_assert(kFragBytes == 1024);
+  load_lds<4>(src, lds_dst, lane);
 }
 // 8 KiB
 __device__ __forceinline__ void stage_half_block(const int8_t* src, uint32_t lds_dst, int lane) {
@@ -137,12 +114,6 @@ __device__ inline v4i lds_frag(const int8_t* blk, int rg, int rh, int ks, int la
 }
 
 
-// Empty volatile asm statements that take values as read-write register operands.  The
-// compiler may not reorder volatile asm, so the instructions producing the operands stay
-// before the statement and their consumers after it: this pins the source order of otherwise
-// freely movable pure instructions (MFMA, convert, FMA) without emitting any code.
-__device__ __forceinline__ void pin(v4i& x) { asm volatile("" : "+v"(x)); }
-__device__ __forceinline__ void pin(float& a, float& b) { asm volatile("" : "+v"(a), "+v"(b)); }
 // acc += s * t, s uniform.
 __device__ __forceinline__ void fma_in_place(float& acc, float s, float t) {
   asm volatile("v_fmac_f32_e32 %0, %1, %2" : "+v"(acc) : "s"(s), "v"(t));
@@ -908,16 +879,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
 // XCD tiles from all tile-rows, so fallback blocks clustered in a few block-rows (the worst
 // case of Sec. 6.3) load the XCDs evenly.  b in [0, tiles_i * tiles_j) -> (ti, tj), a bijection.
 __device__ __forceinline__ void tile_of(int b, int tiles_i, int tiles_j, int& ti, int& tj) {
-  const int total = tiles_i * tiles_j;
-  const int xcd = b % kXcds, l = b / kXcds;
-  const int q = total / kXcds, rem = total % kXcds;
-  const int L = xcd * q + min(xcd, rem) + l;
-  const int group = kGroupN * tiles_i;
-  const int g0 = (L / group) * kGroupN;
-  const int gn = min(kGroupN, tiles_j - g0);
-  const int within = L - (L / group) * group;
-  tj = g0 + within % gn;
-  ti = within / gn;
+  tile_at<kGroupN>(xcd_run(b, tiles_i * tiles_j), tiles_i, tiles_j, ti, tj);
 }
 
 }  // namespace

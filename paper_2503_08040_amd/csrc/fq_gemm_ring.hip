@@ -121,15 +121,7 @@ __global__ __launch_bounds__(G::kThreads, G::kOcc) void gemm_ring_kernel(GemmPar
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nkb = p.nkb;
   int ti, tj;
-  {
-    const int L = xcd_run(blockIdx.x, gridDim.x);
-    const int group = G::kGroupN * tiles_i;
-    const int g0 = (L / group) * G::kGroupN;
-    const int gn = min(G::kGroupN, tiles_j - g0);
-    const int within = L - (L / group) * group;
-    tj = g0 + within % gn;
-    ti = within / gn;
-  }
+  tile_at<G::kGroupN>(xcd_run(blockIdx.x, gridDim.x), tiles_i, tiles_j, ti, tj);
   const int rg0 = ti * G::kRows, cg0 = tj * G::kCols;       // first groups of the tile
   const int ib = rg0 >> 2;
   auto jb_of = [&](int group) { return min((cg0 + group) >> 2, p.njb - 1); };
@@ -225,7 +217,6 @@ __global__ __launch_bounds__(G::kThreads, G::kOcc) void gemm_ring_kernel(GemmPar
       for (int i = 0; i < n; ++i) {
         // item t + 1 has to be there, those behind it may be under way
         if (ahead == kS - 1) wait_vm<(kS - 2) * G::kL>();
-        else if (kS > 3 && ahead == kS - 2) wait_vm<(kS > 3 ? kS - 3 : 0) * G::kL>();
         else wait_vm<0>();
         asm volatile("s_barrier" ::: "memory");
         if (k < nkb) {

@@ -246,15 +246,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void gemm_tile_kernel(GemmParams p
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nkb = p.nkb;
   int ti, tj;
-  {
-    const int L = xcd_run(blockIdx.x, gridDim.x);
-    const int group = kGroupN * tiles_i;
-    const int g0 = (L / group) * kGroupN;
-    const int gn = min(kGroupN, tiles_j - g0);
-    const int within = L - (L / group) * group;
-    tj = g0 + within % gn;
-    ti = within / gn;
-  }
+  tile_at<kGroupN>(xcd_run(blockIdx.x, gridDim.x), tiles_i, tiles_j, ti, tj);
   const int cg0 = tj * kWU, ib = ti, jb = cg0 >> 2, rg = 4 * ti + w;
   const int kg = lane >> 4, l15 = lane & 15;
   const int koff = (kg >> 1) * 1024 + (kg & 1) * 512;

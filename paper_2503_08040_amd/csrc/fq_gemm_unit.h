@@ -1,5 +1,5 @@
-// Pieces of the small-tile GEMM kernels: operand order, the multiply-and-fold pipeline of one 32 x 32
-// sub-tile, direct loads into LDS, stores of a sub-tile.
+// Pieces of the GEMM kernels: the order of the tiles, direct loads into LDS; and of the small-tile ones: operand order,
+// the multiply-and-fold pipeline of one 32 x 32 sub-tile, stores of a sub-tile.
 #pragma once
 #include "fq_device.h"
 #include "fq_kernels.h"
@@ -82,7 +82,21 @@ __device__ __forceinline__ int xcd_run(int b, int total) {
   return xcd * q + min(xcd, rem) + l;
 }
 
-// Empty volatile asm: pins the source order of pure instructions without emitting code.
+// Place L of the tile order -> tile: groups of kGroupN tile columns, walked row by row.
+template <int kGroupN>
+__device__ __forceinline__ void tile_at(int L, int tiles_i, int tiles_j, int& ti, int& tj) {
+  const int group = kGroupN * tiles_i;
+  const int g0 = (L / group) * kGroupN;
+  const int gn = min(kGroupN, tiles_j - g0);
+  const int within = L - (L / group) * group;
+  tj = g0 + within % gn;
+  ti = within / gn;
+}
+
+// Empty volatile asm statements that take values as read-write register operands.  The
+// compiler may not reorder volatile asm, so the instructions producing the operands stay
+// before the statement and their consumers after it: this pins the source order of otherwise
+// freely movable pure instructions (MFMA, convert, FMA) without emitting any code.
 __device__ __forceinline__ void pin(v4i& x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void pin(float& a, float& b) { asm volatile("" : "+v"(a), "+v"(b)); }
 
