@@ -1,9 +1,12 @@
 """Python binding of libfq (Fallback Quantization on MI355X).
 
-Thin ctypes layer over the C ABI declared in include/fq.h: same names, argument
-marshalling only.  PyTorch supplies device memory and the current stream; every
-step of the path runs in the library's HIP kernels.  If the compiled library is
-missing, importing this package's functions raises -- there is no fallback.
+Thin layer over the C ABI declared in include/fq.h: same names, argument
+marshalling only, in ctypes and, for the plain forms of fq_quantize,
+fq_quantize_sr and fq_gemm, in the C++ module _fqnative (csrc/fq_python.cpp),
+which also allocates fq_gemm's output.  PyTorch supplies device memory and the
+current stream; every step of the path runs in the library's HIP kernels.  If
+the compiled library is missing, calling this package's functions raises --
+there is no fallback; without _fqnative every call goes through ctypes.
 """
 import ctypes as C
 import os

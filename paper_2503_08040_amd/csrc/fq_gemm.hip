@@ -609,7 +609,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, int ib_first, int
       // idle, some 9 cycles per dependent scalar instruction: addresses and parities are carried along instead of
       // worked out, one v_readlane brings a k-block's flags, choices are made between integers.  And one body for both
       // kinds of turn leaves no paths to join that hold operands (a branch around the units and a fetch
-      // beside them took all 256 registers, this 231).  Against that form, us: 4096 x 4096 x 11008 215 -> 205, 4096 x
+      // beside them took all 256 registers, this 230).  Against that form, us: 4096 x 4096 x 11008 215 -> 205, 4096 x
       // 11008 x 4096 197 -> 188 (5 % of the blocks flagged), 8192^3 665 -> 639 (a fifth), 545 -> 508 without residual
       // items; gemm_biased_kernel 4096 x 4096 x 11008 190 -> 180.
       const int a_sum = G::kASet, b0 = 2 * G::kASet, b_sum = 2 * b0 + G::kBSet;     // offset in LDS of the other slot = sum - it
@@ -1052,8 +1052,9 @@ TilePlan plan_tiles(int nib, int njb, int cus) {
 // the ring in two rounds), 3072^3 128 x 64 too (42; 44 and 48 in two and three rounds of the ring's 128 x 64 and
 // 128 x 128, 61 with 256 x 256) and 4096^3 256 x 256 (79 us; 82 in two rounds of 128 x 256).  Flagged blocks cost
 // 256 x 256 tiles more than the others, and how many there are is not known here, so the line for an A with slots lies where
-// 20 % are no loss: 3584 x 4096 x 3584 256 x 256 (74 us at 10 %, 84 with 128 x 64), 1152 x 4096 x 9984 128 x 64 (82 at 20 %,
-// 87).  Without slots 1280 x 1024 x 9856 and 4096 x 4096 x 5760 take 256 x 256 too (112 us, 123 with 128 x 128).  512 x 4096 x 4096
+// up to 30 % are no loss: 3584 x 4096 x 3584 takes 256 x 256 (70 us at 10 %, 85 at 30 %; 81 and 92 with 128 x 64) and so
+// does 1280 x 1024 x 9856 (23.6 and 28.4; 25.3 and 27.9), but not 1280 x 2048 x 9000 (42.5 us with 128 x 64 at 20 %; 44.9).
+// Without slots that one (34.6; 35.7) and 4096 x 4096 x 5760 (112; 123 with 128 x 128) take them too.  512 x 4096 x 4096
 // takes the ring's 128 x 64 (16.3 us; 18.9 with the other, 23.5 with 32 x 32), 256 x 4096 x 4096 32 x 32 (10.8 us,
 // 15.4 with the ring) and 256 x 11008 x 4096 too (28.6 us, 33.2).  64 x 64 tiles were never better than the nearer
 // of their neighbours by more than 3 %.  The smaller tiles have no biased form, so fq_gemm_biased takes them where

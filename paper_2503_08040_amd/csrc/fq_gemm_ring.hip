@@ -12,11 +12,11 @@
 // Why so.  The multiplication alone (no loads, no LDS reads, no barrier) runs these tiles at the rate of the bare
 // instruction stream, 2.4 POP/s.  What a k-loop adds is what wavefronts cannot issue meanwhile: a direct load
 // holds its wavefront for some 30 cycles (1024 x 11008 x 4096, one 128 x 128 tile per compute unit, without
-// flagged blocks: 60 us with the loads among the multiplication, 54 us with loaders, 47 us without loads), scalar
-// bookkeeping at the barrier holds all of them at once (so the loaders do the bookkeeping), and two bodies of the
+// flagged blocks: 60.0 us with the loads among the multiplication, 51.6 without them; 54.8 us with loaders, 46.5 without
+// their loads), scalar bookkeeping at the barrier holds all of them at once (so the loaders do the bookkeeping), and two bodies of the
 // loop made the compiler keep the accumulators twice (so there is one body: an operand is fetched right behind
 // its last use, the accumulators are updated by an instruction that writes where it reads).  LDS reads are what
-// is left: 6 KiB per 32 x 32 x 128 step for 64 x 32, 4 KiB for 64 x 64 (without them 47 us as well).
+// is left: 6 KiB per 32 x 32 x 128 step for 64 x 32, 4 KiB for 64 x 64 (with loaders and without LDS reads 47.2 us).
 // Measured, bf16 output, against the tiles of fq_gemm_tile.hip (us):
 //   777 x 1544 x 2200, 5 % of the blocks flagged      10.5 ->  9.5   128 x 64, one per compute unit
 //   512 x 4096 x 4096, 5 %                            18.9 -> 16.3   128 x 64, one per compute unit
@@ -24,7 +24,8 @@
 //   1024 x 11008 x 4096, 10 %                         69.8 -> 62.1   128 x 128
 //   2048 x 4096 x 4096, 5 %                           46.8 -> 42.4   128 x 256
 // A second round of tiles has nothing to hide its start and end behind, and two or three small workgroups on a
-// compute unit do: from there on the kernels of fq_gemm_tile.hip are the faster ones (plan_small, fq_gemm.hip).
+// compute unit do: from there on the kernels of fq_gemm_tile.hip are the faster ones; on contractions of a few k-blocks
+// too, as nothing is multiplied here before the loaders have brought the first items (plan_small, fq_gemm.hip).
 #include <atomic>
 #include <type_traits>
 

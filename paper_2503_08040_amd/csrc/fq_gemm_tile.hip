@@ -19,7 +19,7 @@
 // latency: a third of a wavefront's time is waiting for loads (or the barrier) and a third the issue of its own
 // matrix and vector instructions, one after the other; 33 x 4096 x 11008 keeps the matrix cores busy 12 % of
 // the cycles.  So the 128 x 64 and 128 x 128 forms are for outputs of more than a round of the tiles of
-// fq_gemm_ring.hip and less than about a round of gemm_kernel's, where two or three workgroups on a compute unit
+// fq_gemm_ring.hip and less than about a round of gemm_kernel's (and for short contractions), where two or three workgroups on a compute unit
 // hide each other's latency and start and end at different times; plan_small in fq_gemm.hip has the rule.
 // Measured (GEMM alone, bf16 output, gemm_kernel -> the form chosen): 33 x 4096 x 11008 70.6 -> 12.2 us,
 // 256 x 11008 x 4096 182 -> 28.1 us (5 % of the blocks flagged), 1536 x 4096 x 4096 76 -> 34.1 us, 3072^3
