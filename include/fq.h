@@ -406,9 +406,9 @@ fq_status fq_gemm_tile_plan(int32_t rows_out, int32_t cols_out, int32_t compute_
  * chosen where the output is less than about a chip's worth of large tiles.  path[0] = 0: the large ones,
  * path[1] = the number of 256 x 256 tiles, path[2] and path[3] = the number of 128 x 384 tiles over the last
  * block columns or, where that ends earlier, the last block rows.  An A that cannot fall back (its criterion is
- * FQ_CRIT_NONE, whatever its capacity) takes the large tiles on somewhat smaller outputs already, and short contractions
- * (up to 15 k-blocks) can take other small tiles; which those are and which of two kernels runs tiles of one size,
- * fq_gemm_form says.  All zero for an empty output.  fq_gemm's
+ * FQ_CRIT_NONE, whatever its capacity) takes the large tiles on somewhat smaller outputs already, and shorter
+ * contractions (below 16 k-blocks, or while A's codes are less than 4 MiB) can take other small tiles; which those are
+ * and which of two kernels runs tiles of one size, fq_gemm_form says.  All zero for an empty output.  fq_gemm's
  * results do not depend on the tiles: every output element is accumulated in Alg. 1's order.
  */
 fq_status fq_gemm_path(int32_t rows_out, int32_t cols_out, int32_t compute_units, int biased,
